@@ -350,14 +350,15 @@ ssd_status ssd_tree_prep(const int32_t *parent_idx, int32_t n, int32_t *depth, u
  *     tolerance against the definition; their logits differ in the last bits.
  *   gemm_path: the per-sub-layer kernels' weight GEMMs, bfloat16 models
  *     only: 0 = automatic (by node count), 1 = vector ALU, 2 = matrix cores.
- *   weight_prefetch: 1 = every per-sub-layer bfloat16 pass the session
- *     enqueues (or a graph of it replays) gets a prefetcher kernel on a
- *     stream of the session's own; it follows progress signals the pass's
- *     kernels raise and loads each weight GEMM's fragments into the L2 of the
- *     XCD whose workgroups will read them, a few kernels ahead.  The pass
- *     never waits for it; it stops waiting for signals 50 ms after it starts.
- *     0 = off.  Results are bitwise the same either way.  ssd_kv_destroy
- *     waits for the session's prefetchers.
+ *   weight_prefetch: 1 = every per-sub-layer bfloat16 pass of at most 64
+ *     nodes that the session enqueues (or a graph of it replays) gets a
+ *     prefetcher kernel on a stream of the session's own; it follows progress
+ *     signals the pass's kernels raise and loads each weight GEMM's fragments
+ *     into the L2 of the XCD whose workgroups will read them, a few kernels
+ *     ahead.  The pass never waits for it; it stops waiting for signals 50 ms
+ *     after it starts.  Wider trees run without it.  0 = off.  Results are
+ *     bitwise the same either way.  ssd_kv_destroy waits for the session's
+ *     prefetchers.
  * A captured graph keeps the pass mode and GEMM path in force when it was
  * captured.  Errors: SSD_E_INVALID_ARG (null, or a value out of range). */
 typedef struct {

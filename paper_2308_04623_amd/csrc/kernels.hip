@@ -619,121 +619,277 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
 
 // ------------------------------------------------------------------ weight GEMM for wide trees
 //
-// Above 64 nodes a workgroup of gemm_kernel reads every node's activations
-// (N x K float16) for one or two row blocks of weights, so activation bytes
-// dominate what each CU pulls in.  Here a workgroup owns RBT row blocks x
-// kG2TT node tiles of the output over one k-range and reads RBT + kG2TT
-// fragments per k-step.  Its four waves split the k-steps (wave w: kc0 + w,
-// + 4, ...), each multiplying every weight fragment of a step into every
-// activation fragment of it on v_mfma_f32_16x16x32_f16, and the waves'
-// tiles are summed through LDS in wave order, one row block at a time.  The
-// workgroups of one row-block group are placed on one XCD (workgroup b runs
-// on XCD b % 8), so the weights they share come from HBM once and then from
-// that XCD's L2.  Block b: XCD x = b % 8; q = b / 8 names (group i = x + 8
+// Above 64 nodes.  A workgroup owns RBT row blocks x TT node tiles of the
+// output over one k-range and reads RBT + TT fragments per k-step; its NW
+// waves split the k-steps (wave w: kc0 + w, kc0 + w + NW, ...), each with U of
+// them in flight straight into registers, and are summed in wave order
+// through LDS, one 16-byte slot per lane.
+// What bounds it: every CU pulls in RBT + TT fragments of 1 KB per k-step, and
+// at 40 k-steps (GPT-2-L's d) the kernel takes about 0.9 us plus 27 ns per KB
+// of them, from 7 + 0.9 us at 4 x 2 to 15.5 us at 5 x 8; a second round of
+// workgroups on a CU costs as much again.  So wide_cfg picks the tile that
+// covers the 256 CUs in the fewest rounds with the fewest fragments.
+// MLP up (5120 x 1280) alone, weights from HBM: 128 nodes 13.7 -> 8.7 us,
+// 256 nodes 19.1 -> 10.6 us, 512 nodes 2 x 19.1 -> 15.5 us against the tile of
+// 2-4 row blocks x 4 node tiles with two k-steps in flight before it (which
+// re-read its last k-step to keep the loads branch-free; a scalar branch on
+// the step count costs nothing and makes deep pipelines pay).
+// The workgroups of one row-block group are placed on one XCD (workgroup b
+// runs on XCD b % 8), so the weights they share come from HBM once and then
+// from that XCD's L2.  Block b: XCD x = b % 8; q = b / 8 names (group i = x + 8
 // (q / (gt gy)), node-tile group j, k-split sk); groups past gx exit.
-constexpr int kG2TT = 4;  // node tiles per workgroup
 
-template <int RBT, int KIND, int U, int NW, bool Q8>
-__global__ __launch_bounds__(64 * NW) void gemm2d_kernel(const void* __restrict__ Wv, int KC, int RBtot, int NT,
-                                                         int kcs, int gx, int gt, int gy,
-                                                         const uint16_t* __restrict__ act, Epi ep) {
-  constexpr int TT = kG2TT;
+// four consecutive outputs o .. o + 3 of node nn (o % 4 == 0, all below M
+// except in the LM head, whose row count is any)
+__device__ __forceinline__ void epilogue4(const Epi& e, int kind, int sk, int nn, int o, f32x4 v) {
+  if (kind == EPI_PARTIAL) {
+    *(f32x4*)(e.part + (size_t)sk * e.part_stride + (size_t)nn * e.d + o) = v;
+    return;
+  }
+  if (kind == EPI_LOGITS) {
+    typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+    float* p = e.logits + (size_t)nn * e.ldl + o;
+    if (o + 4 <= e.M) {
+      *(f32x4_u*)p = v;
+    } else {
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        if (o + c < e.M) p[c] = v[c];
+    }
+    return;
+  }
+  if (e.bias) {
+    float bv[4];
+    ld4((const uint16_t*)e.bias, o, bv);
+    v += (f32x4){bv[0], bv[1], bv[2], bv[3]};
+  }
+  if (kind == EPI_GELU) {
+    const float g[4] = {gelu_tanh(v[0]), gelu_tanh(v[1]), gelu_tanh(v[2]), gelu_tanh(v[3])};
+    st_act4_u16((uint16_t*)e.out, nn, o, e.ldo, g, e.err);
+  } else if (o < e.d) {  // EPI_QKV (d and the head size are multiples of 4: one head and part)
+    *(f32x4*)(e.q + (size_t)nn * e.d + o) = v;
+  } else {
+    const int oo = o < 2 * e.d ? o - e.d : o - 2 * e.d, h = oo / e.DH, j = oo - h * e.DH;
+    uint16_t* dst = (uint16_t*)(o < 2 * e.d ? e.kt : e.vt);
+    *(u32x2*)(dst + ((size_t)h * e.max_nodes + nn) * e.DH + j) = (u32x2){f2bf2(v[0], v[1]), f2bf2(v[2], v[3])};
+  }
+}
+
+// the tile's place of a launch of gx row-block groups, gt node-tile groups and
+// gy k-splits (false: padding)
+struct WidePos {
+  int i, j, sk;
+};
+__device__ __forceinline__ bool wide_pos(int gx, int gt, int gy, WidePos& p) {
+  const int b = blockIdx.x, q = b >> 3, per = gt * gy, rem = q % per;
+  p = WidePos{(b & 7) + 8 * (q / per), rem / gy, rem % gy};
+  return p.i < gx;
+}
+
+template <int RBT, int TT, int NW, int U, bool Q8>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, 2))) void gemm_wide_kernel(
+    const void* __restrict__ Wv, int KC, int RBtot, int NT, int kcs, int gx, int gt, int gy,
+    const uint16_t* __restrict__ act, int kind, Epi ep) {
   using WT = typename std::conditional<Q8, u32x2, u32x4>::type;
-  const WT* Wp = (const WT*)Wv;
-  __shared__ float red[NW * TT * 16 * 16];
+  constexpr int RT = RBT * TT;
+  constexpr int PR = RT * NW <= 160 ? RT : RT / 2;  // tiles summed per round of 160 KB of LDS
+  static_assert(PR * NW <= 160 && (PR == RT || RT % 2 == 0), "the waves' tiles must fit LDS in two rounds");
+  __shared__ f32x4 red[NW * PR * 64];
   pass_signal(ep.sig);
-  const int b = blockIdx.x, x = b & 7, q = b >> 3, per = gt * gy;
-  const int i = x + 8 * (q / per), rem = q % per;
-  const int j = rem / gy, sk = rem % gy;
-  if (i >= gx) return;
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-  const int rb0 = i * RBT, t0 = j * TT;
-  const int kc0 = sk * kcs, kc1 = min(KC, kc0 + kcs);
+  WidePos p;
+  if (!wide_pos(gx, gt, gy, p)) return;
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int rb0 = p.i * RBT, t0 = p.j * TT;
+  const int kc0 = p.sk * kcs, kc1 = min(KC, kc0 + kcs);
   const int nsteps = kc1 - kc0 > w ? (kc1 - kc0 - w + NW - 1) / NW : 0;
   // row blocks past the matrix and node tiles past the tree read the last
   // one instead and are never stored
   const WT* wb[RBT];
   const u32x4* ab[TT];
 #pragma unroll
-  for (int r = 0; r < RBT; ++r) wb[r] = Wp + (size_t)min(rb0 + r, RBtot - 1) * KC * 64 + lane;
+  for (int r = 0; r < RBT; ++r)
+    wb[r] = (const WT*)Wv + ((size_t)min(rb0 + r, RBtot - 1) * KC + kc0 + w) * 64 + lane;
 #pragma unroll
-  for (int t = 0; t < TT; ++t) ab[t] = (const u32x4*)act + (size_t)min(t0 + t, NT - 1) * KC * 64 + lane;
+  for (int t = 0; t < TT; ++t) ab[t] = (const u32x4*)act + ((size_t)min(t0 + t, NT - 1) * KC + kc0 + w) * 64 + lane;
   WT wq[U][RBT];
   u32x4 bq[U][TT];
-  const int klast = kc1 - 1;
   auto load_step = [&](int s, int u) {
-    const int kc = min(kc0 + w + NW * s, klast);
 #pragma unroll
-    for (int r = 0; r < RBT; ++r) wq[u][r] = wb[r][(size_t)kc * 64];
+    for (int r = 0; r < RBT; ++r) wq[u][r] = wb[r][(size_t)s * (NW * 64)];
 #pragma unroll
-    for (int t = 0; t < TT; ++t) bq[u][t] = ab[t][(size_t)kc * 64];
+    for (int t = 0; t < TT; ++t) bq[u][t] = ab[t][(size_t)s * (NW * 64)];
   };
   f32x4 acc[RBT][TT];
 #pragma unroll
   for (int r = 0; r < RBT; ++r)
 #pragma unroll
     for (int t = 0; t < TT; ++t) acc[r][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  if (nsteps > 0) {
+  // (the step guards are scalar: w and nsteps are uniform per wave)
 #pragma unroll
-    for (int u = 0; u < U; ++u) load_step(u, u);
-    __builtin_amdgcn_sched_barrier(0);
-    for (int s0 = 0; s0 < nsteps; s0 += U) {
+  for (int u = 0; u < U; ++u)
+    if (u < nsteps) load_step(u, u);
+  __builtin_amdgcn_sched_barrier(0);
+  for (int s0 = 0; s0 < nsteps; s0 += U) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        // (the step guard is uniform per wave: a select, never a branch
-        // around an MFMA)
-        const bool ok = s0 + u < nsteps;
+    for (int u = 0; u < U; ++u) {
+      if (s0 + u < nsteps) {
 #pragma unroll
         for (int r = 0; r < RBT; ++r) {
-          const f16x8 wf = ok ? wfrag(wq[u][r]) : (f16x8)(_Float16)0.0f;
+          const f16x8 wf = wfrag(wq[u][r]);
 #pragma unroll
           for (int t = 0; t < TT; ++t)
             acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf, __builtin_bit_cast(f16x8, bq[u][t]), acc[r][t],
                                                                0, 0, 0);
         }
-        __builtin_amdgcn_sched_barrier(0);
-        load_step(s0 + u + U, u);
-        __builtin_amdgcn_sched_barrier(0);
       }
+      __builtin_amdgcn_sched_barrier(0);
+      if (s0 + u + U < nsteps) load_step(s0 + u + U, u);
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
-  Epi e2 = ep;
-  e2.split = sk;
+  // the waves' tiles summed in wave order, tile q by wave q % NW; lane l of a
+  // tile holds rows 4 (l / 16) .. + 3 of node l % 16
 #pragma unroll
-  for (int r = 0; r < RBT; ++r) {
-    if (rb0 + r >= RBtot) break;
-    // lane l of a tile holds rows 4 (l / 16) + c, node l % 16
+  for (int q0 = 0; q0 < RT; q0 += PR) {
+    if (q0) __syncthreads();
 #pragma unroll
-    for (int t = 0; t < TT; ++t)
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-        red[((w * TT + t) * 16 + (lane & 15)) * 16 + 4 * (lane >> 4) + c] = acc[r][t][c];
+    for (int q = 0; q < PR; ++q) red[(w * PR + q) * 64 + lane] = acc[(q0 + q) / TT][(q0 + q) % TT];
     __syncthreads();
-    for (int idx = tid; idx < TT * 256; idx += 64 * NW) {
-      const int row = idx & 15, node = t0 * 16 + (idx >> 4);
-      float sum = red[idx];
+    for (int q = w; q < PR; q += NW) {
+      const int r = (q0 + q) / TT, t = (q0 + q) % TT;
+      f32x4 s = red[q * 64 + lane];
 #pragma unroll
-      for (int ww = 1; ww < NW; ++ww) sum += red[ww * TT * 256 + idx];
-      const int o = (rb0 + r) * 16 + row;
-      if (o < ep.M && node < ep.N) {
-        if constexpr (Q8) sum *= ep.wscale[o];
-        epilogue<uint16_t, KIND>(e2, node, o, sum);
+      for (int ww = 1; ww < NW; ++ww) s += red[(ww * PR + q) * 64 + lane];
+      const int o = (rb0 + r) * 16 + 4 * (lane >> 4), n = (t0 + t) * 16 + (lane & 15);
+      if (o < ep.M && n < ep.N) {
+        if constexpr (Q8) s *= *(const f32x4*)(ep.wscale + o);
+        epilogue4(ep, kind, p.sk, ep.node0 + n, o, s);
       }
     }
-    __syncthreads();
   }
 }
 
-// row blocks per workgroup of the wide-tree GEMM for a kind and node-tile
-// group count: enough workgroups to cover the 256 CUs, as few activation
-// re-reads as that allows (the LM head, with thousands of row blocks, takes 8)
-static int g2_rbt(int kind, int gt) {
-  if (kind == EPI_LOGITS) return 8;
-  if (kind == EPI_PARTIAL) return gt <= 2 ? 1 : 2;
-  return gt <= 2 ? 2 : 4;
+// The LM head over a wide tree (float16 fragments): thousands of row blocks,
+// so the chip is full whatever the tile and re-reads decide.  A workgroup of 8
+// waves (4 x 2) owns 4 RW row blocks x 8 node tiles; every fragment of a
+// k-step is copied into LDS once (global_load_lds, ST - 1 steps ahead) and
+// read by the 2 or 4 waves that share it.  50257 x 1280, weights from HBM: 128
+// nodes 55 -> 30 us (RW 2), 256 nodes 89 -> 47 us, 512 nodes 168 -> 90 us (RW
+// 4) against 8 row blocks x 4 node tiles with each wave on its own k-steps;
+// the 129 MB of weights alone take 23 us at the rate of a large copy.
+template <int RW, int ST>
+__global__ __launch_bounds__(512) void gemm_head_kernel(const void* __restrict__ Wv, int KC, int RBtot, int NT, int gx,
+                                                        int gt, const uint16_t* __restrict__ act, Epi ep) {
+  constexpr int WR = 4, TW = 4, RBT = RW * WR, TT = 8, NW = 8, FR = RBT + TT, PER = FR / NW;
+  static_assert(FR % NW == 0, "every wave copies the same number of fragments");
+  __shared__ __align__(16) unsigned char lds[ST * FR * 1024];
+  WidePos p;
+  if (!wide_pos(gx, gt, 1, p)) return;
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int rb0 = p.i * RBT, t0 = p.j * TT, wr = w >> 1, wt = w & 1;
+  // this wave copies fragments w, w + 8, ... of a step: row blocks, then node
+  // tiles (those past the matrix or the tree repeat the last one)
+  const u32x4* src[PER];
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int f = w + q * NW;
+    src[q] = f < RBT ? (const u32x4*)Wv + (size_t)min(rb0 + f, RBtot - 1) * KC * 64 + lane
+                     : (const u32x4*)act + (size_t)min(t0 + f - RBT, NT - 1) * KC * 64 + lane;
+  }
+  auto issue = [&](int k) {
+    unsigned char* d = lds + (size_t)(k % ST) * FR * 1024;
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[q] + (size_t)k * 64),
+                                       (__attribute__((address_space(3))) void*)(d + (w + q * NW) * 1024), 16, 0, 0);
+  };
+  f32x4 acc[RW][TW];
+#pragma unroll
+  for (int r = 0; r < RW; ++r)
+#pragma unroll
+    for (int t = 0; t < TW; ++t) acc[r][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < ST - 1; ++s) issue(min(s, KC - 1));
+  for (int k = 0; k < KC; ++k) {
+    // This wave's copies of step k are complete when at most (ST - 2) PER are
+    // outstanding; the barrier then covers every wave's, and the waves' LDS
+    // reads of step k - 1, whose slot the next copies overwrite (each wave
+    // waited for its reads before the matrix products of that step).  Past
+    // the end the last step is copied again over itself, which keeps the
+    // count of outstanding copies.
+    constexpr int VM = (ST - 2) * PER;
+    __builtin_amdgcn_s_waitcnt((VM & 15) | ((VM >> 4) << 14) | (7 << 4) | (0 << 8));  // vmcnt(VM) lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    const u32x4* base = (const u32x4*)(lds + (size_t)(k % ST) * FR * 1024) + lane;
+    if (k + ST - 1 < KC) {
+      issue(k + ST - 1);
+    } else {
+      // (into the slot of step k - 1, which no one reads any more)
+      const int kl = KC - 1;
+      unsigned char* d = lds + (size_t)((k + ST - 1) % ST) * FR * 1024;
+#pragma unroll
+      for (int q = 0; q < PER; ++q)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[q] + (size_t)kl * 64),
+                                         (__attribute__((address_space(3))) void*)(d + (w + q * NW) * 1024), 16, 0, 0);
+    }
+    u32x4 wf[RW], af[TW];
+#pragma unroll
+    for (int r = 0; r < RW; ++r) wf[r] = base[(wr * RW + r) * 64];
+#pragma unroll
+    for (int t = 0; t < TW; ++t) af[t] = base[(RBT + wt * TW + t) * 64];
+#pragma unroll
+    for (int r = 0; r < RW; ++r)
+#pragma unroll
+      for (int t = 0; t < TW; ++t)
+        acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, wf[r]),
+                                                           __builtin_bit_cast(f16x8, af[t]), acc[r][t], 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < RW; ++r)
+#pragma unroll
+    for (int t = 0; t < TW; ++t) {
+      const int o = (rb0 + wr * RW + r) * 16 + 4 * (lane >> 4), n = (t0 + wt * TW + t) * 16 + (lane & 15);
+      if (o < ep.M && n < ep.N) epilogue4(ep, EPI_LOGITS, 0, ep.node0 + n, o, acc[r][t]);
+    }
+  // the copies still in flight land before the workgroup's LDS is given back
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
 bool gemm_wide(int vec, int N) { return !vec && N > 64; }
+
+// Tile and k-split of a wide GEMM of RB row blocks, KC k-steps and NT node
+// tiles.  The cost of a choice in KB that a CU pulls in: rounds of workgroups
+// on the busiest XCD (32 CUs; row-block groups are dealt to the XCDs in turn)
+// times the k-steps times RBT + TT, plus, for the residual GEMMs, 0.22 KB per
+// node and split for the float32 partials that are written and read again
+// (measured on the GPT-2-L shapes, see gemm_wide_kernel: MLP down over 128
+// nodes 8.7 us in 4 splits of 5 x 2, 8.0 us in 8 of 5 x 4 with 2.6 MB more
+// partials for the LayerNorm after it; over 80 nodes 8.3 us in 4 splits of
+// 5 x 2, 7.0 us in 8 of 5 x 3).  The LM head is cut into gemm_head_kernel's
+// tiles, or 5 x 4 for 8-bit weights (128 nodes 34 us; 5 x 8 42 us).
+static WideCfg wide_cfg(int kind, int RB, int KC, int N, bool q8) {
+  const int NT = (N + 15) / 16;
+  if (kind == EPI_LOGITS) {
+    if (q8) return WideCfg{5, 4, 1};
+    return NT <= 8 ? WideCfg{8, 8, 1} : WideCfg{16, 8, 1};
+  }
+  WideCfg best{5, 8, 1};
+  double bc = 1e30;
+  for (int S = 1; S <= (kind == EPI_PARTIAL ? kMaxSplits : 1); S *= 2)
+    for (int rbt = 4; rbt <= 5; ++rbt)
+      for (int tt : {2, 3, 4, 6, 8}) {
+        if (S > KC) continue;
+        const int gx = (RB + rbt - 1) / rbt, gt = (NT + tt - 1) / tt, kcs = (KC + S - 1) / S;
+        const int rounds = ((gx + 7) / 8 * gt * S + 31) / 32;
+        const double c = (double)rounds * kcs * (rbt + tt) + (kind == EPI_PARTIAL ? 0.22 * S * N : 0.0);
+        if (c < bc) {
+          bc = c;
+          best = WideCfg{rbt, tt, S};
+        }
+      }
+  return best;
+}
 
 // Tile shape per node count and GEMM kind (measured on the GPT-2-L shapes:
 // K = 1280 for QKV / MLP up / attention out, 5120 for MLP down).  At 17-32
@@ -755,7 +911,7 @@ GemmCfg gemm_cfg(int N, int vec, int kind) {
   while (nt * 16 < N) nt *= 2;
   c.nt = nt;
   c.nv = 0;
-  c.rb = nt <= 4 ? 2 : 1;
+  c.rb = 2;
   if (nt == 2) {
     c.nw = 8;
     c.rb = kind == EPI_QKV ? 1 : 2;
@@ -770,10 +926,7 @@ int gemm_split_kc(int M, int K, int N, int vec, int want_split, int* splits) {
     return KC;
   }
   if (gemm_wide(vec, N)) {
-    const int gt = ((N + 15) / 16 + kG2TT - 1) / kG2TT;
-    const int gx = ((M + 15) / 16 + g2_rbt(EPI_PARTIAL, gt) - 1) / g2_rbt(EPI_PARTIAL, gt);
-    int S = 1;
-    while (S * gx * gt < 256 && S < kMaxSplits) S *= 2;
+    const int S = wide_cfg(EPI_PARTIAL, (M + 15) / 16, KC, N, false).S;
     const int kcs = (KC + S - 1) / S;
     *splits = (KC + kcs - 1) / kcs;
     return kcs;
@@ -790,7 +943,7 @@ int gemm_split_kc(int M, int K, int N, int vec, int want_split, int* splits) {
 // row blocks per workgroup of the LM head (EPI_LOGITS on the matrix cores):
 // it has thousands of row blocks, so more of them per workgroup make the
 // activations (read once per workgroup) cost less than the weights
-static int head_rb(int nt) { return nt <= 2 ? 8 : nt == 4 ? 4 : nt == 8 ? 2 : 1; }
+static int head_rb(int nt) { return nt <= 2 ? 8 : 4; }
 
 GemmGeom gemm_geom(int kind, int vec, int M, int K, int N, int kcs) {
   GemmGeom g{};
@@ -801,8 +954,7 @@ GemmGeom gemm_geom(int kind, int vec, int M, int K, int N, int kcs) {
     // the wide-tree kernel as the prefetcher sees it: row-block groups
     // padded to a multiple of 8, so that group bx runs on XCD bx % 8 (plus
     // the launch's offset) like block bx of the plain kernel
-    const int gt = ((N + 15) / 16 + kG2TT - 1) / kG2TT;
-    g.RB = g2_rbt(kind, gt);
+    g.RB = wide_cfg(kind, g.RBtot, g.KC, N, false).rbt;
     g.gx = 8 * (((g.RBtot + g.RB - 1) / g.RB + 7) / 8);
     g.gy = (g.KC + kcs - 1) / kcs;
     return g;
@@ -838,66 +990,62 @@ static void gemm_go(int kind, const GemmGeom& g, const void* Wp, const uint16_t*
   }
 }
 
-template <int RBT, int KIND, int U, int NW>
-static void gemm2d_launch(const dim3& grid, const void* Wp, int KC, int RBtot, int NT, int kcs, int gx, int gt,
-                          int gy, const uint16_t* act, const Epi& ep, hipStream_t s) {
+template <int RBT, int TT, int NW, int U>
+static void wide_go(int grid, const void* Wp, int KC, int RBtot, int NT, int kcs, int gx, int gt, int gy,
+                    const uint16_t* act, int kind, const Epi& ep, hipStream_t s) {
   if (ep.wscale)
-    gemm2d_kernel<RBT, KIND, U, NW, true><<<grid, 64 * NW, 0, s>>>(Wp, KC, RBtot, NT, kcs, gx, gt, gy, act, ep);
+    gemm_wide_kernel<RBT, TT, NW, U, true><<<grid, 64 * NW, 0, s>>>(Wp, KC, RBtot, NT, kcs, gx, gt, gy, act, kind, ep);
   else
-    gemm2d_kernel<RBT, KIND, U, NW, false><<<grid, 64 * NW, 0, s>>>(Wp, KC, RBtot, NT, kcs, gx, gt, gy, act, ep);
+    gemm_wide_kernel<RBT, TT, NW, U, false><<<grid, 64 * NW, 0, s>>>(Wp, KC, RBtot, NT, kcs, gx, gt, gy, act, kind, ep);
 }
 
-template <int RBT, int U, int NW>
-static void gemm2d_go(int kind, const void* Wp, int KC, int RBtot, int NT, int kcs, int gx, int gt, int gy,
-                      const uint16_t* act, const Epi& ep, hipStream_t s) {
-  const dim3 grid(8 * ((gx + 7) / 8) * gt * gy);
-  switch (kind) {
-    case EPI_QKV: gemm2d_launch<RBT, EPI_QKV, U, NW>(grid, Wp, KC, RBtot, NT, kcs, gx, gt, gy, act, ep, s); break;
-    case EPI_PARTIAL:
-      gemm2d_launch<RBT, EPI_PARTIAL, U, NW>(grid, Wp, KC, RBtot, NT, kcs, gx, gt, gy, act, ep, s);
-      break;
-    case EPI_GELU: gemm2d_launch<RBT, EPI_GELU, U, NW>(grid, Wp, KC, RBtot, NT, kcs, gx, gt, gy, act, ep, s); break;
-    default: gemm2d_launch<RBT, EPI_LOGITS, U, NW>(grid, Wp, KC, RBtot, NT, kcs, gx, gt, gy, act, ep, s); break;
-  }
-}
-
+// Waves and k-steps in flight per tile: 8 waves where the sums of their tiles
+// fit LDS at once (MLP up over 256 nodes: 10.6 us, 4 waves 10.9), 4 at 8 node
+// tiles; as many k-steps as registers allow.  The 8-bit LM head, whose many
+// workgroups come in rounds, runs 4 waves (128 nodes 34 us, 8 waves 42 us).
 static hipError_t launch_gemm_wide(int kind, const void* Wp, int M, int K, const uint16_t* act, int kcs,
                                    const Epi& ep, hipStream_t s) {
-  const int KC = K / 32, RBtot = (M + 15) / 16, NT = (ep.N + 15) / 16;
-  const int gt = (NT + kG2TT - 1) / kG2TT, rbt = g2_rbt(kind, gt);
-  const int gx = (RBtot + rbt - 1) / rbt, gy = (KC + kcs - 1) / kcs;
+  const int KC = K / 32, RB = (M + 15) / 16, NT = (ep.N + 15) / 16;
+  const WideCfg c = wide_cfg(kind, RB, KC, ep.N, ep.wscale != nullptr);
+  const int gx = (RB + c.rbt - 1) / c.rbt, gt = (NT + c.tt - 1) / c.tt, gy = (KC + kcs - 1) / kcs;
   if (kind != EPI_PARTIAL && gy != 1) return hipErrorInvalidValue;
-  const void* W = Wp;
-  switch (rbt) {
-    case 1: gemm2d_go<1, 2, 4>(kind, W, KC, RBtot, NT, kcs, gx, gt, gy, act, ep, s); break;
-    case 2: gemm2d_go<2, 2, 4>(kind, W, KC, RBtot, NT, kcs, gx, gt, gy, act, ep, s); break;
-    case 4:
-      // (QKV at more than 128 nodes: 8 waves, each with half the k-steps, measured
-      // faster there; the other kinds and smaller trees are faster with 4)
-      if (kind == EPI_QKV)
-        gemm2d_launch<4, EPI_QKV, 2, 8>(dim3(8 * ((gx + 7) / 8) * gt * gy), W, KC, RBtot, NT, kcs, gx, gt, gy, act,
-                                        ep, s);
-      else
-        gemm2d_go<4, 2, 4>(kind, W, KC, RBtot, NT, kcs, gx, gt, gy, act, ep, s);
-      break;
-    default: gemm2d_go<8, 1, 4>(kind, W, KC, RBtot, NT, kcs, gx, gt, gy, act, ep, s); break;
+  const int grid = 8 * ((gx + 7) / 8) * gt * gy;
+  if (kind == EPI_LOGITS) {
+    if (ep.wscale) wide_go<5, 4, 4, 4>(grid, Wp, KC, RB, NT, kcs, gx, gt, gy, act, kind, ep, s);
+    else if (c.rbt == 8) gemm_head_kernel<2, 4><<<grid, 512, 0, s>>>(Wp, KC, RB, NT, gx, gt, act, ep);
+    else gemm_head_kernel<4, 3><<<grid, 512, 0, s>>>(Wp, KC, RB, NT, gx, gt, act, ep);
+    return hipGetLastError();
   }
+#define WIDE_CASE(R, T, NW, U) \
+  case 16 * R + T: wide_go<R, T, NW, U>(grid, Wp, KC, RB, NT, kcs, gx, gt, gy, act, kind, ep, s); break;
+  switch (16 * c.rbt + c.tt) {
+    WIDE_CASE(4, 2, 8, 3)
+    WIDE_CASE(4, 3, 8, 3)
+    WIDE_CASE(4, 4, 8, 3)
+    WIDE_CASE(4, 6, 8, 2)
+    WIDE_CASE(4, 8, 4, 4)
+    WIDE_CASE(5, 2, 8, 3)
+    WIDE_CASE(5, 3, 8, 3)
+    WIDE_CASE(5, 4, 8, 2)
+    WIDE_CASE(5, 6, 8, 2)
+    WIDE_CASE(5, 8, 4, 4)
+    default: return hipErrorInvalidValue;
+  }
+#undef WIDE_CASE
   return hipGetLastError();
 }
 
 hipError_t launch_gemm_bf16(int kind, int vec, const void* Wp, int M, int K, const uint16_t* act, int kcs,
                             const Epi& ep, hipStream_t s) {
   if (kcs <= 0) return hipErrorInvalidValue;
-  if (ep.N > (vec ? 16 : 256)) return hipErrorInvalidValue;
+  if (ep.N > (vec ? 16 : 1024)) return hipErrorInvalidValue;
   if (gemm_wide(vec, ep.N)) return launch_gemm_wide(kind, Wp, M, K, act, kcs, ep, s);
   const GemmGeom g = gemm_geom(kind, vec, M, K, ep.N, kcs);
   if (kind == EPI_LOGITS && !vec) {
     switch (gemm_cfg(ep.N, 0, kind).nt) {
       case 1: gemm_launch<1, 8, EPI_LOGITS, false, 0, 3>(g, Wp, act, ep, s); break;
       case 2: gemm_launch<2, 8, EPI_LOGITS, false, 0, 2>(g, Wp, act, ep, s); break;
-      case 4: gemm_launch<4, 4, EPI_LOGITS, false, 0, 2>(g, Wp, act, ep, s); break;
-      case 8: gemm_launch<8, 2, EPI_LOGITS, false, 0, 1>(g, Wp, act, ep, s); break;
-      default: gemm_launch<16, 1, EPI_LOGITS, false, 0, 1>(g, Wp, act, ep, s); break;
+      default: gemm_launch<4, 4, EPI_LOGITS, false, 0, 2>(g, Wp, act, ep, s); break;
     }
     return hipGetLastError();
   }
@@ -917,9 +1065,7 @@ hipError_t launch_gemm_bf16(int kind, int vec, const void* Wp, int M, int K, con
         else if (kind == EPI_GELU) gemm_launch<2, 2, EPI_GELU, false, 0, 3, 8>(g, Wp, act, ep, s);
         else gemm_launch<2, 2, EPI_PARTIAL, false, 0, 1, 8>(g, Wp, act, ep, s);
         break;
-      case 4: gemm_go<4, 2, false, 0, 3>(kind, g, Wp, act, ep, s); break;
-      case 8: gemm_go<8, 1, false, 0, 2>(kind, g, Wp, act, ep, s); break;
-      default: gemm_go<16, 1, false, 0, 1>(kind, g, Wp, act, ep, s); break;
+      default: gemm_go<4, 2, false, 0, 3>(kind, g, Wp, act, ep, s); break;
     }
   }
   return hipGetLastError();

@@ -682,7 +682,7 @@ static size_t fill_stage(char* host, int P, const int32_t* tokens, const int32_t
 
 // One weight GEMM of the pass over n nodes: fp32 models use the plain
 // kernel; bf16 models the vector-ALU kernel for few nodes (or when pinned)
-// and the matrix-core kernel otherwise, in node groups of 16 / 256.
+// (in node groups of 16) and the matrix-core kernels otherwise.
 static int gemm_vec(int path, int n) { return (path == 0 ? (n <= kVecMaxNodes ? 1 : 2) : path) == 1; }
 
 // k-steps per split of a weight GEMM over n nodes (one k-split for every
@@ -690,7 +690,7 @@ static int gemm_vec(int path, int n) { return (path == 0 ? (n <= kVecMaxNodes ? 
 static int gemm_kcs(int path, int n, int kind, int rows, int K) {
   const int vec = gemm_vec(path, n);
   int S = 1;
-  return gemm_split_kc(rows, K, std::min(n, vec ? 16 : 256), vec, kind == EPI_PARTIAL, &S);
+  return gemm_split_kc(rows, K, vec ? std::min(n, 16) : n, vec, kind == EPI_PARTIAL, &S);
 }
 
 // The prefetcher's plan for a bf16 pass over n nodes: the launch geometry of
@@ -699,7 +699,7 @@ static int gemm_kcs(int path, int n, int kind, int rows, int K) {
 static PrefetchPlan prefetch_plan(const ssd_model* m, const ssd_kv* kv, int path, int n) {
   PrefetchPlan pp{};
   const int d = m->cfg.d_model, M = m->cfg.d_mlp;
-  const int vec = gemm_vec(path, n), nn = std::min(n, vec ? 16 : 256);
+  const int vec = gemm_vec(path, n), nn = vec ? std::min(n, 16) : n;
   const int kinds[4] = {EPI_QKV, EPI_PARTIAL, EPI_GELU, EPI_PARTIAL};
   const int rows[4] = {3 * d, d, M, d}, Ks[4] = {d, d, d, M};
   for (int k = 0; k < 4; ++k) {
@@ -719,13 +719,19 @@ static PrefetchPlan prefetch_plan(const ssd_model* m, const ssd_kv* kv, int path
   return pp;
 }
 
+// Whether a per-sub-layer pass raises progress signals for the prefetcher.
+// Wide trees (more than 64 nodes) do without it: their GEMM workgroups fill a
+// CU's LDS and registers, so they would wait for its polling workgroups to
+// leave the CUs (up to its time-out).
+static bool pass_signals(const ssd_model* m, int path, int n) { return !m->f32 && !gemm_wide(gemm_vec(path, n), n); }
+
 // Accounts for the signals of one bf16 pass about to be enqueued and, when
 // weight prefetch is on, launches its prefetcher on the session's side
 // stream first (the pass never waits for it).
 static bool use_fused(const ssd_model* m, const ssd_kv* kv, int n);
 
 static ssd_status start_pass_prefetch(const ssd_model* m, ssd_kv* kv, int n, bool fused, int path) {
-  if (m->f32 || fused) return SSD_OK;
+  if (fused || !pass_signals(m, path, n)) return SSD_OK;
   const unsigned long long base = kv->sig_count;
   kv->sig_count += (unsigned long long)sigs_per_pass(m->cfg.n_layer);
   if (!kv->prefetch) return SSD_OK;
@@ -740,7 +746,7 @@ static hipError_t run_gemm(const ssd_model* m, int path, int n, int kind, const 
                            const float* wscale, int rows, int K, const void* act, const Epi& ep, hipStream_t s) {
   if (m->f32) return launch_gemm_f32(kind, (const float*)Wraw, rows, K, (const float*)act, K, ep, s);
   const int vec = gemm_vec(path, n);
-  const int group = vec ? 16 : 256;
+  const int group = vec ? 16 : n;
   const int kcs = gemm_kcs(path, n, kind, rows, K);
   for (int n0 = 0; n0 < n; n0 += group) {
     Epi e2 = ep;
@@ -761,7 +767,7 @@ static int resid_splits(const ssd_model* m, int path, int n, int rows, int K) {
   if (m->f32) return 0;
   const int vec = gemm_vec(path, n);
   int S = 1;
-  gemm_split_kc(rows, K, std::min(n, vec ? 16 : 256), vec, 1, &S);
+  gemm_split_kc(rows, K, vec ? std::min(n, 16) : n, vec, 1, &S);
   return S;
 }
 
@@ -822,9 +828,9 @@ static ssd_status enqueue_verify(const ssd_model* m, ssd_kv* kv, int32_t P, int3
   if (kv->pass_mode == 2) return fail(SSD_E_UNSUPPORTED, "the persistent pass does not apply to this model, session or tree");
   const int gp = kv->gemm_path;
   const bool q8 = m->q8;
-  // pass signals (bf16 models; none for a pass that starts past layer 0,
-  // which runs without the prefetcher)
-  unsigned long long* sig = f32 || l0 > 0 ? nullptr : kv->d_sig;
+  // pass signals (none for a pass that starts past layer 0, which runs
+  // without the prefetcher)
+  unsigned long long* sig = l0 > 0 || !pass_signals(m, gp, n) ? nullptr : kv->d_sig;
   kv->resid_fused = false;
   kv->last_n = n;
   kv->last_layers = L;

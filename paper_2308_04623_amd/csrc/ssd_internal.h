@@ -57,6 +57,12 @@ struct GemmCfg {
   int nt, rb, ck, nv, nw;  // nw: waves per workgroup
 };
 
+// tile of the wide-tree GEMM (more than 64 nodes): row blocks and node tiles
+// per workgroup, k-splits
+struct WideCfg {
+  int rbt, tt, S;
+};
+
 // launch geometry of one bf16 GEMM: block (bx, by) owns weight row blocks
 // bx RB .. bx RB + RB - 1 (rows past RBtot read row block RBtot - 1 and are
 // never stored) and k-steps by kcs .. by kcs + kcs - 1 (clamped to KC)
