@@ -131,9 +131,12 @@ __device__ __forceinline__ float block_sum256(float v, float* red4) {
   return (red4[0] + red4[1]) + (red4[2] + red4[3]);
 }
 
+// tanh GELU, 0.5 x (1 + tanh(u)) with u = sqrt(2/pi) (x + 0.044715 x^3), as
+// the equal x / (1 + exp(-2u)): one exponential and one reciprocal where
+// tanhf takes some 40 instructions, and no cancellation at negative x
 __device__ __forceinline__ float gelu_tanh(float x) {
-  const float c = 0.7978845608028654f;  // sqrt(2/pi)
-  return 0.5f * x * (1.0f + tanhf(c * (x + 0.044715f * x * x * x)));
+  const float c2 = 1.5957691216057308f;  // 2 sqrt(2/pi)
+  return x * __builtin_amdgcn_rcpf(1.0f + __expf(-c2 * (x + 0.044715f * x * x * x)));
 }
 
 // ------------------------------------------------------------------ embed
@@ -636,8 +639,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
 // the step count costs nothing and makes deep pipelines pay).
 // The workgroups of one row-block group are placed on one XCD (workgroup b
 // runs on XCD b % 8), so the weights they share come from HBM once and then
-// from that XCD's L2.  Block b: XCD x = b % 8; q = b / 8 names (group i = x + 8
-// (q / (gt gy)), node-tile group j, k-split sk); groups past gx exit.
+// from that XCD's L2.  With 2, 4 or 8 k-splits a split keeps to 4, 2 or 1 of
+// the XCDs, so an XCD reads only its splits' part of the activations (MLP
+// down over 512 nodes: 1.3 of 5.2 MB per XCD, against a 4 MB L2).  Block b: XCD
+// x = b % 8, split x % gy, and b / 8 names (group i = x / gy + (8 / gy) (b / 8
+// / gt), node-tile group j); groups past gx exit.  Another split count takes
+// splits in turn inside each XCD.
 
 // four consecutive outputs o .. o + 3 of node nn (o % 4 == 0, all below M
 // except in the LM head, whose row count is any)
@@ -680,10 +687,21 @@ __device__ __forceinline__ void epilogue4(const Epi& e, int kind, int sk, int nn
 struct WidePos {
   int i, j, sk;
 };
+__host__ __device__ __forceinline__ int wide_xcds(int gy) { return 8 % gy == 0 ? 8 / gy : 8; }
 __device__ __forceinline__ bool wide_pos(int gx, int gt, int gy, WidePos& p) {
-  const int b = blockIdx.x, q = b >> 3, per = gt * gy, rem = q % per;
-  p = WidePos{(b & 7) + 8 * (q / per), rem / gy, rem % gy};
+  const int x = blockIdx.x & 7, q = blockIdx.x >> 3, X = wide_xcds(gy);
+  if (8 % gy == 0) {
+    p = WidePos{x / gy + X * (q / gt), q % gt, x % gy};
+  } else {
+    const int rem = q % (gt * gy);
+    p = WidePos{x + 8 * (q / (gt * gy)), rem / gy, rem % gy};
+  }
   return p.i < gx;
+}
+// workgroups of a launch (per XCD, times 8)
+static int wide_blocks(int gx, int gt, int gy) {
+  const int X = wide_xcds(gy);
+  return 8 * ((gx + X - 1) / X) * gt * (8 % gy == 0 ? 1 : gy);
 }
 
 template <int RBT, int TT, int NW, int U, bool Q8>
@@ -861,7 +879,8 @@ bool gemm_wide(int vec, int N) { return !vec && N > 64; }
 // Tile and k-split of a wide GEMM of RB row blocks, KC k-steps and NT node
 // tiles.  The cost of a choice in KB that a CU pulls in: rounds of workgroups
 // on the busiest XCD (32 CUs; row-block groups are dealt to the XCDs in turn)
-// times the k-steps times RBT + TT, plus, for the residual GEMMs, 0.22 KB per
+// times the k-steps times RBT + TT (plus the tile itself, for the sum through
+// LDS: it breaks ties), plus, for the residual GEMMs, 0.22 KB per
 // node and split for the float32 partials that are written and read again
 // (measured on the GPT-2-L shapes, see gemm_wide_kernel: MLP down over 128
 // nodes 8.7 us in 4 splits of 5 x 2, 8.0 us in 8 of 5 x 4 with 2.6 MB more
@@ -881,8 +900,9 @@ static WideCfg wide_cfg(int kind, int RB, int KC, int N, bool q8) {
       for (int tt : {2, 3, 4, 6, 8}) {
         if (S > KC) continue;
         const int gx = (RB + rbt - 1) / rbt, gt = (NT + tt - 1) / tt, kcs = (KC + S - 1) / S;
-        const int rounds = ((gx + 7) / 8 * gt * S + 31) / 32;
-        const double c = (double)rounds * kcs * (rbt + tt) + (kind == EPI_PARTIAL ? 0.22 * S * N : 0.0);
+        const int rounds = (wide_blocks(gx, gt, (KC + kcs - 1) / kcs) + 255) / 256;
+        const double c =
+            (double)rounds * (kcs * (rbt + tt) + rbt * tt) + (kind == EPI_PARTIAL ? 0.22 * S * N : 0.0);
         if (c < bc) {
           bc = c;
           best = WideCfg{rbt, tt, S};
@@ -1009,7 +1029,7 @@ static hipError_t launch_gemm_wide(int kind, const void* Wp, int M, int K, const
   const WideCfg c = wide_cfg(kind, RB, KC, ep.N, ep.wscale != nullptr);
   const int gx = (RB + c.rbt - 1) / c.rbt, gt = (NT + c.tt - 1) / c.tt, gy = (KC + kcs - 1) / kcs;
   if (kind != EPI_PARTIAL && gy != 1) return hipErrorInvalidValue;
-  const int grid = 8 * ((gx + 7) / 8) * gt * gy;
+  const int grid = wide_blocks(gx, gt, gy);
   if (kind == EPI_LOGITS) {
     if (ep.wscale) wide_go<5, 4, 4, 4>(grid, Wp, KC, RB, NT, kcs, gx, gt, gy, act, kind, ep, s);
     else if (c.rbt == 8) gemm_head_kernel<2, 4><<<grid, 512, 0, s>>>(Wp, KC, RB, NT, gx, gt, act, ep);
@@ -1361,8 +1381,9 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
 //   operand.  Each leaves a part (max, sum of exponentials, unnormalised
 //   output) per (head, chunk, node).
 // attn_merge_kernel: DH / 4 threads (four output dims each) per (node, head): the
-//   chunks' parts merged in chunk order, then the node's root path (its
-//   ancestors and itself in the tree scratch, root first) folded in RK keys
+//   chunks' parts merged in chunk order, then the records of its root path's
+//   full 32-key blocks, then the rest of that path (its ancestors and itself
+//   in the tree scratch, root first) folded in RK keys
 //   at a time, each score four products per thread then a butterfly sum
 //   over the pair's threads; the output is written in the next GEMM's input
 //   layout, four columns per store.  The chunking depends on P
@@ -1543,6 +1564,161 @@ __global__ __launch_bounds__(64 * AT_MAXW) void attn_split_kernel(AttnArgs a) {
   if ((int)blockIdx.x < a.H * a.nsplit) attn_prefix_chunk<DH>(a, lds, blockIdx.x % a.H, blockIdx.x / a.H);
 }
 
+// Deep root paths (prompts fed as chains): the full 32-key blocks of a node's
+// root path (path entries 32 b .. 32 b + 31, b < (depth + 1) / 32), on the matrix
+// cores like the prefix.  Block (head h, 16-node tile t, path chunk c): wave w
+// takes path block b = 4 c + w.  Nodes whose paths agree at entry 32 b + 31
+// have the same block, so the wave serves its tile one distinct block at a
+// time (in a chain: one for all 16 nodes), keeping the others' state as it
+// is; the four waves' states are merged in wave order into a float32 record
+// (max, sum, -, -, output) per node.  The arithmetic of a node depends on its
+// own path only.  The merge walks what is left of the path, at most 31 keys.
+// A 512-token chain, per layer: the merge alone, 8 keys of one node at a time,
+// 124 us (64 dependent rounds for the last nodes).
+constexpr int kPathWaves = kPathChunk / 32;
+
+template <int DH>
+__global__ __launch_bounds__(64 * kPathWaves) void attn_path_kernel(AttnArgs a) {
+  constexpr int DPL = DH / 4, NL = DPL / 8;  // dims per lane of the V staging; 16-byte loads of each row
+  // V^T of a wave's block: row d holds the 32 keys of dim d (stride 40
+  // elements, and 64 bytes more per DPL rows, so the staging stores of one
+  // dim of every group land on different banks)
+  constexpr int VROW = 40, VW = DH * VROW + 4 * 32, REC = DH + 4;
+  __shared__ __align__(16) uint16_t vt_l[kPathWaves][VW];
+  __shared__ __align__(16) float st[kPathWaves][16][REC];
+  const int ntiles = (a.N + 15) >> 4;
+  const int h = blockIdx.x % a.H, t = (blockIdx.x / a.H) % ntiles, c = blockIdx.x / (a.H * ntiles);
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int i = lane & 15, g = lane >> 4, b = kPathWaves * c + w;
+  const int n = 16 * t + i, nc = min(n, a.N - 1);
+  const int fb = n < a.N ? (a.depth[nc] + 1) / 32 : 0, off = a.anc_off[nc];
+  if (__builtin_amdgcn_ballot_w64(fb > kPathWaves * c) == 0) return;  // (the same in every wave)
+  const bool mine = fb > b;
+  const int last = mine ? a.ancl[off + 32 * b + 31] : -1;
+  unsigned pend = (unsigned)__builtin_amdgcn_ballot_w64(mine) & 0xffffu;
+  u32x4 qh[DH / 32], ql[DH / 32];
+#pragma unroll
+  for (int kc2 = 0; kc2 < DH / 32; ++kc2) {
+    const float* qp = a.q + (size_t)nc * a.d + h * DH + 32 * kc2 + 8 * g;
+    const f32x4 f0 = *(const f32x4*)qp, f1 = *(const f32x4*)(qp + 4);
+    const float v[8] = {f0[0], f0[1], f0[2], f0[3], f1[0], f1[1], f1[2], f1[3]};
+    pack_hilo8(v, qh[kc2], ql[kc2]);
+  }
+  const uint16_t* ktb = (const uint16_t*)a.kt + (size_t)h * a.max_nodes * DH;
+  const uint16_t* vtb = (const uint16_t*)a.vt + (size_t)h * a.max_nodes * DH;
+  uint16_t* vl = vt_l[w];
+  float m = -INFINITY, l = 0.f;
+  f32x4 o[DH / 16];
+#pragma unroll
+  for (int tt = 0; tt < DH / 16; ++tt) o[tt] = (f32x4){0, 0, 0, 0};
+  while (pend) {
+    const int lead = __builtin_ctz(pend);
+    const int lastL = __builtin_amdgcn_readlane(last, lead);
+    const int* ids = a.ancl + __builtin_amdgcn_readlane(off, lead) + 32 * b;
+    const bool in = mine && last == lastL;
+    pend &= ~(unsigned)__builtin_amdgcn_ballot_w64(in);
+    // K operand rows: path entries 8 (i / 4) + i % 4 (+ 4 for the second
+    // tile); V: entries 2 (lane / 4), + 1, dims DPL (lane % 4) .. of each
+    const int e0 = 8 * (i >> 2) + (i & 3), vr = 2 * (lane >> 2), vd = DPL * (lane & 3);
+    const int id0 = ids[e0], id1 = ids[e0 + 4], iv0 = ids[vr], iv1 = ids[vr + 1];
+    u32x4 k0[DH / 32], k1[DH / 32], va0[NL], va1[NL];
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+      va0[j] = *(const u32x4*)(vtb + (size_t)iv0 * DH + vd + 8 * j);
+      va1[j] = *(const u32x4*)(vtb + (size_t)iv1 * DH + vd + 8 * j);
+    }
+#pragma unroll
+    for (int kc2 = 0; kc2 < DH / 32; ++kc2) {
+      k0[kc2] = *(const u32x4*)(ktb + (size_t)id0 * DH + 32 * kc2 + 8 * g);
+      k1[kc2] = *(const u32x4*)(ktb + (size_t)id1 * DH + 32 * kc2 + 8 * g);
+    }
+    wave_sync_lds();  // (the block before has been read)
+#pragma unroll
+    for (int j = 0; j < NL; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        uint16_t* p = vl + (vd + 8 * j + 2 * e) * VROW + 32 * (lane & 3) + vr;
+        *(uint32_t*)p = (va0[j][e] & 0xffffu) | (va1[j][e] << 16);
+        *(uint32_t*)(p + VROW) = (va0[j][e] >> 16) | (va1[j][e] & 0xffff0000u);
+      }
+    wave_sync_lds();
+    f32x4 s0 = (f32x4){0, 0, 0, 0}, s1 = (f32x4){0, 0, 0, 0};
+#pragma unroll
+    for (int kc2 = 0; kc2 < DH / 32; ++kc2) {
+      s0 = mfma16(k0[kc2], qh[kc2], s0);
+      s0 = mfma16(k0[kc2], ql[kc2], s0);
+      s1 = mfma16(k1[kc2], qh[kc2], s1);
+      s1 = mfma16(k1[kc2], ql[kc2], s1);
+    }
+    // lane: node 16 t + i, path entries 32 b + 8 g + e (e < 4 from s0)
+    float sv[8];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      sv[r] = s0[r] * a.scale;
+      sv[4 + r] = s1[r] * a.scale;
+    }
+    float mb = sv[0];
+#pragma unroll
+    for (int e = 1; e < 8; ++e) mb = fmaxf(mb, sv[e]);
+    mb = fmaxf(mb, __shfl_xor(mb, 16));
+    mb = fmaxf(mb, __shfl_xor(mb, 32));
+    float pv[8], ps = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      pv[e] = __expf(sv[e] - mb);
+      ps += pv[e];
+    }
+    ps += __shfl_xor(ps, 16);
+    ps += __shfl_xor(ps, 32);
+    u32x4 ph, pl;
+    pack_hilo8(pv, ph, pl);
+#pragma unroll
+    for (int tt = 0; tt < DH / 16; ++tt) {
+      const int d = 16 * tt + i;
+      const u32x4 va = *(const u32x4*)(vl + d * VROW + 32 * (d / DPL) + 8 * g);
+      f32x4 r = mfma16(va, ph, (f32x4){0, 0, 0, 0});
+      r = mfma16(va, pl, r);
+      // (nodes of another block keep theirs, whatever these keys hold)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[tt][e] = in ? r[e] : o[tt][e];
+    }
+    m = in ? mb : m;
+    l = in ? ps : l;
+  }
+  if (g == 0) {
+    st[w][i][0] = m;
+    st[w][i][1] = l;
+  }
+#pragma unroll
+  for (int tt = 0; tt < DH / 16; ++tt) *(f32x4*)&st[w][i][4 + 16 * tt + 4 * g] = o[tt];
+  __syncthreads();
+  // the waves' states in wave order: 16 threads per node, DH / 16 dims each
+  constexpr int DP = DH / 16;
+  const int nl = tid >> 4, d0 = DP * (tid & 15);
+  float M = -INFINITY, L = 0.f, O[DP];
+#pragma unroll
+  for (int e = 0; e < DP; ++e) O[e] = 0.f;
+#pragma unroll
+  for (int j = 0; j < kPathWaves; ++j) {
+    const float mj = st[j][nl][0];
+    if (mj == -INFINITY) continue;  // (not a block of this node's path)
+    const float mn = fmaxf(M, mj), al = __expf(M - mn), wj = __expf(mj - mn);
+    L = fmaf(L, al, st[j][nl][1] * wj);
+#pragma unroll
+    for (int e = 0; e < DP; ++e) O[e] = fmaf(O[e], al, st[j][nl][4 + d0 + e] * wj);
+    M = mn;
+  }
+  if (16 * t + nl < a.N && M != -INFINITY) {
+    float* rec = a.ppart + (((size_t)h * a.npath + c) * a.N + 16 * t + nl) * REC;
+    if (d0 == 0) {
+      rec[0] = M;
+      rec[1] = L;
+    }
+#pragma unroll
+    for (int e = 0; e < DP; ++e) rec[4 + d0 + e] = O[e];
+  }
+}
+
 // one wave per block: at 128 nodes x 20 heads that is 640 blocks, so every CU
 // takes part (256-thread blocks left 96 of the 256 CUs idle)
 constexpr int kMergeThreads = 64;
@@ -1590,8 +1766,21 @@ __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnArgs a) {
       M = mn;
     }
   }
-  // the root path, root first, RK keys per batch
-  for (int j0 = 0; j0 <= rdep; j0 += RK) {
+  // the full 32-key blocks of the root path (attn_path_kernel's records, one
+  // per chunk), then the rest of it, RK keys per batch
+  const int fb = (rdep + 1) / 32, np = (32 * fb + kPathChunk - 1) / kPathChunk;
+  const float* prec = a.ppart + ((size_t)h * a.npath * a.N + n) * (DH + 4);
+  for (int c = 0; c < np; ++c) {
+    const float* pr = prec + (size_t)c * a.N * (DH + 4);
+    const f32x2_t ml = *(const f32x2_t*)pr;
+    const f32x4 ov = *(const f32x4*)(pr + 4 + d0);
+    const float mn = fmaxf(M, ml[0]), al = __expf(M - mn), wj = __expf(ml[0] - mn);
+    L = fmaf(L, al, ml[1] * wj);
+#pragma unroll
+    for (int e = 0; e < DPT; ++e) O[e] = fmaf(O[e], al, ov[e] * wj);
+    M = mn;
+  }
+  for (int j0 = 32 * fb; j0 <= rdep; j0 += RK) {
     if (j0 > 0) {
 #pragma unroll
       for (int jj = 0; jj < RK; ++jj) {
@@ -1646,13 +1835,17 @@ hipError_t launch_attn(int f32, int DH, const AttnArgs& a, hipStream_t s) {
     if (a.N <= 0 || a.N > a.max_nodes || (DH != 64 && DH != 32)) return hipErrorInvalidValue;
     if (a.P > 0 && (a.CL <= 0 || a.CL > AT_STAGE || a.CL % 32 || a.nsplit != (a.P + a.CL - 1) / a.CL))
       return hipErrorInvalidValue;
-    const int blocks = max(1, a.H * a.nsplit);
+    if (a.npath > 0 && !a.ppart) return hipErrorInvalidValue;
+    const int blocks = a.sig ? max(1, a.H * a.nsplit) : a.H * a.nsplit;
     const int mblocks = (a.N * a.H * (DH / 4) + kMergeThreads - 1) / kMergeThreads;
+    const int pblocks = a.H * ((a.N + 15) / 16) * a.npath;
     if (DH == 64) {
-      attn_split_kernel<64><<<blocks, 64 * AT_MAXW, 0, s>>>(a);
+      if (blocks) attn_split_kernel<64><<<blocks, 64 * AT_MAXW, 0, s>>>(a);
+      if (pblocks) attn_path_kernel<64><<<pblocks, 64 * kPathWaves, 0, s>>>(a);
       attn_merge_kernel<64><<<mblocks, kMergeThreads, 0, s>>>(a);
     } else {
-      attn_split_kernel<32><<<blocks, 64 * AT_MAXW, 0, s>>>(a);
+      if (blocks) attn_split_kernel<32><<<blocks, 64 * AT_MAXW, 0, s>>>(a);
+      if (pblocks) attn_path_kernel<32><<<pblocks, 64 * kPathWaves, 0, s>>>(a);
       attn_merge_kernel<32><<<mblocks, kMergeThreads, 0, s>>>(a);
     }
     return hipGetLastError();

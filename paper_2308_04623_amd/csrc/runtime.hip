@@ -107,6 +107,7 @@ struct ssd_kv {
   void* act_f = nullptr;  // GELU outputs [npad][d_mlp]
   float* part = nullptr;  // split-K partial sums [kMaxSplits][max_nodes][d]
   float* apart = nullptr;  // attention partials (see AttnArgs::part)
+  float* ppart = nullptr;  // root-path records (see AttnArgs::ppart)
   int* d_tree = nullptr;  // the staged tree (see stage_bytes)
   int* d_accept_tree = nullptr;  // tokens[N] parents[N] depth[N] for accept
   int* d_argmax = nullptr;
@@ -544,6 +545,9 @@ extern "C" ssd_status ssd_kv_create(const ssd_model* m, int32_t max_ctx, int32_t
   const size_t ap_f32 = (size_t)c.n_head * ((max_ctx + 63) / 64) * max_nodes * (m->dh + 2);
   const size_t ap_bf16 = (size_t)c.n_head * attn_max_nsplit(max_ctx, c.n_head) * max_nodes * (m->dh + 4);
   const size_t o_apart = take((m->f32 ? ap_f32 : ap_bf16) * 4);
+  // root-path records of the bf16 kernels (a node's depth is below max_nodes)
+  const size_t o_ppart =
+      take(m->f32 ? 0 : (size_t)c.n_head * attn_npath(max_nodes - 1) * max_nodes * (m->dh + 4) * 4);
   const size_t o_tree = take(stage_bytes(max_nodes));
   const size_t o_at = take((size_t)3 * max_nodes * 4), o_am = take((size_t)max_nodes * 4);
   const size_t o_amw = take(std::max(argmax_work_bytes(max_nodes, V), topk_work_bytes(max_nodes, V)));
@@ -565,6 +569,7 @@ extern "C" ssd_status ssd_kv_create(const ssd_model* m, int32_t max_ctx, int32_t
   kv->act_f = b + o_f;
   kv->part = (float*)(b + o_part);
   kv->apart = (float*)(b + o_apart);
+  kv->ppart = (float*)(b + o_ppart);
   kv->d_tree = (int*)(b + o_tree);
   kv->d_accept_tree = (int*)(b + o_at);
   kv->d_argmax = (int*)(b + o_am);
@@ -846,6 +851,10 @@ static ssd_status enqueue_verify(const ssd_model* m, ssd_kv* kv, int32_t P, int3
   const int s_o = resid_splits(m, gp, n, d, d), s_pr = resid_splits(m, gp, n, d, M);
   const size_t kv_layer = (size_t)H * DH;  // elements per K/V row across heads
 
+  // (the staged depths, see fill_stage)
+  const int32_t* dep_h = (const int32_t*)stage_host + 2 * maxn;
+  const int npath = attn_npath(*std::max_element(dep_h, dep_h + n));
+
   int pend_S = 0;               // partials waiting to be added to x
   const void* pend_bias = nullptr;
   for (int l = l0; l < L; ++l) {
@@ -887,6 +896,8 @@ static ssd_status enqueue_verify(const ssd_model* m, ssd_kv* kv, int32_t P, int3
     a.max_ctx = kv->max_ctx;
     a.max_nodes = maxn;
     a.scale = 1.0f / std::sqrt((float)DH);
+    a.ppart = kv->ppart;
+    a.npath = f32 ? 0 : npath;
     a.CL = attn_chunk(P, H);
     a.nsplit = attn_nsplit(P, H);
     a.sig = sig;

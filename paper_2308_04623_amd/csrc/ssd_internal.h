@@ -120,6 +120,8 @@ struct AttnArgs {
   // bf16 models
   int CL;               // cache rows per prefix chunk (attn_chunk(P, H))
   int nsplit;           // prefix chunks (attn_nsplit(P, H))
+  float* ppart;         // records of the root paths' full blocks [H][npath][N][DH + 4]: max, sum, -, -, output
+  int npath;            // path chunks of the deepest node's full blocks (attn_npath(its depth))
   unsigned long long* sig;  // pass signal counter (nullptr: none); both kernels signal
   unsigned* err;            // session error counter: float16 outputs out of range (nullptr: none)
 };
@@ -145,6 +147,11 @@ inline int attn_max_nsplit(int max_ctx, int H) {
   for (int P = 1; P <= max_ctx; P += (P < 8192 ? 1 : 256)) mx = attn_nsplit(P, H) > mx ? attn_nsplit(P, H) : mx;
   return attn_nsplit(max_ctx, H) > mx ? attn_nsplit(max_ctx, H) : mx;
 }
+
+// bf16 attention: chunks of kPathChunk root-path entries that hold a full
+// 32-entry block of the path of a node at the given depth
+constexpr int kPathChunk = 128;
+inline int attn_npath(int depth) { return ((depth + 1) / 32 * 32 + kPathChunk - 1) / kPathChunk; }
 
 // ---- launchers (kernels.hip); all enqueue on `s` and return the launch status
 hipError_t launch_embed(int f32, const void* wte, const void* wpe, const int* tokens, const int* pos, int N, int d,

@@ -79,3 +79,81 @@ def test_wide_pass_against_oracle(sides, name, n):
 @pytest.mark.parametrize("n", [65, 129, 257])
 def test_wide_pass_8bit_against_oracle(sides, n):
     sides("dh32", True).check(recent_tree(n), P)
+
+
+# root paths around full 32-entry blocks and 128-entry chunks: chains (one
+# block for a whole 16-node tile), a comb whose tiles hold two paths, and
+# four interleaved chains (a tile's nodes in four different blocks)
+def comb(n):
+    return np.array([-1] + [i - 1 if i % 2 else max(0, i - 2) for i in range(1, n)], np.int32)
+
+
+def chains(n, k=4):
+    return np.array([-1] + [max(0, i - k) for i in range(1, n)], np.int32)
+
+
+DEEP = {"chain": W.chain_tree, "comb": comb, "chains": chains}
+
+
+@pytest.mark.parametrize("tree,n", [("chain", 65), ("chain", 128), ("chain", 129), ("chain", 161), ("chain", 600),
+                                    ("comb", 140), ("chains", 300), ("chains", 1000)])
+@pytest.mark.parametrize("name", ["dh64", "dh32"])
+@pytest.mark.parametrize("prefix", [0, P])
+def test_deep_root_paths_against_oracle(sides, name, tree, n, prefix):
+    sides(name, False).check(DEEP[tree](n), prefix)
+
+
+def test_deep_node_independent_of_its_tree(sides):
+    """The last node of a 100-node chain has the same logits, bit for bit, when
+    the chain is interleaved with three others in the same 16-node tiles."""
+    side = sides("dh64", False)
+    cfg, ssd = side.cfg, side.ssd
+    n, k = 400, 4
+    par = chains(n, k)
+    toks = W.tree_tokens(par, cfg.vocab, seed=1)
+    path, i = [], n - 1
+    while i != -1:
+        path.append(i)
+        i = int(par[i])
+    path = path[::-1]
+    s = ssd.Session(side.m, MAX_CTX, n, ssd.to_device(side.kc, cfg), ssd.to_device(side.vc, cfg))
+    a = s.verify(P, toks, par)[n - 1].cpu().numpy()
+    # (padded with leaves of the root to the same node count: the k-splits of the GEMMs follow the node count)
+    cpar = np.concatenate([W.chain_tree(len(path)), np.zeros(n - len(path), np.int32)])
+    ctoks = np.concatenate([toks[path], toks[:n - len(path)]])
+    b = s.verify(P, ctoks, cpar)[len(path) - 1].cpu().numpy()
+    assert np.array_equal(a, b)
+
+
+def test_commit_of_a_long_path_and_of_unaligned_buffers(sides):
+    """Committed rows are the tree rows, bit for bit, and no other row of the
+    cache changes: a long path, and buffers only 2-byte aligned."""
+    import torch
+    side = sides("dh64", False)
+    cfg, ssd = side.cfg, side.ssd
+    n = 200
+    par = W.chain_tree(n)
+    toks = W.tree_tokens(par, cfg.vocab, seed=9)
+    s = ssd.Session(side.m, MAX_CTX, n, ssd.to_device(side.kc, cfg), ssd.to_device(side.vc, cfg))
+    s.verify(P, toks, par)
+    path = torch.tensor(np.random.default_rng(4).permutation(n)[:150], dtype=torch.int32, device="cuda")
+    plen = torch.tensor([150], dtype=torch.int32, device="cuda")
+    idx = path.long()
+    want = [c.clone() for c in (s.k_cache, s.v_cache)]
+    for w, t in zip(want, (s.k_tree, s.v_tree)):
+        w[:, :, P:P + 150] = t[:, :, idx]
+    s.commit(P, path, plen)
+    for w, c in zip(want, (s.k_cache, s.v_cache)):
+        assert torch.equal(w.view(torch.int16), c.view(torch.int16))
+    # the same rows through a session whose cache starts 2 bytes past a 16-byte boundary
+    def shifted(t):
+        flat = torch.zeros(t.numel() + 8, dtype=t.dtype, device="cuda")[1:1 + t.numel()]
+        return flat.copy_(t.reshape(-1)).view(t.shape)
+    kc, vc = (shifted(ssd.to_device(a, cfg)) for a in (side.kc, side.vc))
+    u = ssd.Session(side.m, MAX_CTX, n, kc, vc)
+    u.k_tree.copy_(s.k_tree)
+    u.v_tree.copy_(s.v_tree)
+    u.commit(P, path, plen)
+    for w, c in zip(want, (kc, vc)):
+        assert torch.equal(w.view(torch.int16), c.view(torch.int16))
+    assert s.error_count() == 0 and u.error_count() == 0
