@@ -344,27 +344,57 @@ __device__ __forceinline__ void epilogue(const Epi& e, int n, int o, float acc) 
 
 // ------------------------------------------------------------------ GEMM, fp32 models
 
-// One thread per (node, output row); only used for the small fp32 model.
+// A workgroup of 1024 threads owns 16 output rows x 16 nodes: K steps of up to
+// kF32K columns of both operands are staged in LDS (16-byte loads; a row
+// stride 4 words past a multiple of 64 puts the 16 rows that a wave reads on
+// different banks) and each output is summed by four threads, a quarter of
+// the columns each, in order, then the quarters in order.
+// Only small float32 models run here, so latency bounds it: the toy model's
+// four GEMMs (128-512 rows and columns, 15 nodes) took 18-30 us each with one
+// thread per output walking its weight row alone.
+constexpr int kF32K = 512, kF32S = kF32K + 4;
+
 template <int KIND>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ W, int M, int K,
-                                                       const float* __restrict__ act, int lda, Epi ep) {
-  const int o = blockIdx.x * 256 + threadIdx.x, n = blockIdx.y;
-  if (o >= M) return;
-  const float* wr = W + (size_t)o * K;
-  const float* ar = act + (size_t)n * lda;
+__global__ __launch_bounds__(1024) void gemm_f32_kernel(const float* __restrict__ W, int M, int K,
+                                                        const float* __restrict__ act, int lda, Epi ep) {
+  __shared__ __align__(16) float wl[16][kF32S], al[16][kF32S];
+  __shared__ float red[3][256];
+  const int tid = threadIdx.x, o0 = blockIdx.x * 16, n0 = blockIdx.y * 16;
+  const int ol = tid & 15, nl = (tid >> 4) & 15, kq = tid >> 8;
   float acc = 0.f;
-  for (int k = 0; k < K; ++k) acc = fmaf(ar[k], wr[k], acc);
-  epilogue<float, KIND>(ep, n, o, acc);
+  for (int k0 = 0; k0 < K; k0 += kF32K) {
+    const int kn = min(kF32K, K - k0), u = kn >> 2;  // (K is a multiple of 32)
+    if (k0) __syncthreads();
+    // (rows past the matrix or the tree repeat the last one; not stored)
+    for (int i = tid; i < 16 * u; i += 1024) {
+      const int r = i / u, c = 4 * (i - r * u);
+      *(f32x4*)&wl[r][c] = *(const f32x4*)(W + (size_t)min(o0 + r, M - 1) * K + k0 + c);
+      *(f32x4*)&al[r][c] = *(const f32x4*)(act + (size_t)min(n0 + r, ep.N - 1) * lda + k0 + c);
+    }
+    __syncthreads();
+    const int kb = kq * (kn >> 2);
+#pragma unroll 4
+    for (int k = kb; k < kb + (kn >> 2); k += 4) {
+      const f32x4 a4 = *(const f32x4*)&al[nl][k], w4 = *(const f32x4*)&wl[ol][k];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = fmaf(a4[e], w4[e], acc);
+    }
+  }
+  if (kq) red[kq - 1][tid & 255] = acc;
+  __syncthreads();
+  if (kq == 0 && o0 + ol < M && n0 + nl < ep.N)
+    epilogue<float, KIND>(ep, n0 + nl, o0 + ol, ((acc + red[0][tid]) + red[1][tid]) + red[2][tid]);
 }
 
 hipError_t launch_gemm_f32(int kind, const float* W, int M, int K, const float* act, int lda, const Epi& ep,
                            hipStream_t s) {
-  dim3 grid((M + 255) / 256, ep.N);
+  if (K % 32) return hipErrorInvalidValue;
+  dim3 grid((M + 15) / 16, (ep.N + 15) / 16);
   switch (kind) {
-    case EPI_QKV: gemm_f32_kernel<EPI_QKV><<<grid, 256, 0, s>>>(W, M, K, act, lda, ep); break;
-    case EPI_RESID: gemm_f32_kernel<EPI_RESID><<<grid, 256, 0, s>>>(W, M, K, act, lda, ep); break;
-    case EPI_GELU: gemm_f32_kernel<EPI_GELU><<<grid, 256, 0, s>>>(W, M, K, act, lda, ep); break;
-    default: gemm_f32_kernel<EPI_LOGITS><<<grid, 256, 0, s>>>(W, M, K, act, lda, ep); break;
+    case EPI_QKV: gemm_f32_kernel<EPI_QKV><<<grid, 1024, 0, s>>>(W, M, K, act, lda, ep); break;
+    case EPI_RESID: gemm_f32_kernel<EPI_RESID><<<grid, 1024, 0, s>>>(W, M, K, act, lda, ep); break;
+    case EPI_GELU: gemm_f32_kernel<EPI_GELU><<<grid, 1024, 0, s>>>(W, M, K, act, lda, ep); break;
+    default: gemm_f32_kernel<EPI_LOGITS><<<grid, 1024, 0, s>>>(W, M, K, act, lda, ep); break;
   }
   return hipGetLastError();
 }
