@@ -2310,80 +2310,150 @@ hipError_t launch_greedy_walk(const int* tokens, const int* parents, const int* 
 //
 // For CDF-first tree assembly: query q draws from softmax(logits[rows[q]] / T)
 // over the whole vocabulary at the uniform U[q] by inverse CDF in ascending
-// token id.  One workgroup per query: thread t owns the contiguous ids
-// [t C, t C + C); the row's maximum, then each thread's sum of the
-// normalised probabilities in id order, then thread 0 walks the threads'
-// sums in order to the crossing and scans that thread's ids (fp64
-// throughout).  If rounding leaves no crossing, the last id with positive
-// probability.
-constexpr int kPickThreads = 1024;
+// token id, in float64.  Two kernels: every chunk of kPickChunk ids of every
+// distinct row leaves its maximum and its sum of exp(x / T - maximum); then
+// one workgroup per query walks the chunks' probabilities in order to the
+// crossing and scans that chunk alone.  If rounding leaves no crossing, the
+// last id with positive probability.
+// The float64 exponentials bound it, so they are spread over the chip and
+// computed once per row: 54 queries of 32 rows of 50257 took 173 us with one
+// workgroup per query computing every exponential twice and one thread
+// adding up the other 1023's sums.
+constexpr int kPickChunk = 2048, kPickPer = kPickChunk / 256;
 
-__global__ __launch_bounds__(kPickThreads) void cdf_pick_kernel(CdfPickArgs a) {
-  __shared__ double part[kPickThreads];
-  __shared__ double red[kPickThreads / 64];
-  const int q = blockIdx.x, tid = threadIdx.x, V = a.V;
-  const float* row = a.logits + (size_t)a.rows[q] * V;
-  const int C = (V + kPickThreads - 1) / kPickThreads, v0 = tid * C, v1 = min(V, v0 + C);
+// sums of v over the threads before this one and over all 256 (a wave's
+// prefix, then the waves in order)
+__device__ __forceinline__ double scan256(double v, double* red4, double& total) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  double inc = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const double t = __shfl_up(inc, o);
+    if (lane >= o) inc += t;
+  }
+  if (lane == 63) red4[w] = inc;
+  __syncthreads();
+  double before = 0.0;
+  for (int i = 0; i < w; ++i) before += red4[i];
+  total = ((red4[0] + red4[1]) + red4[2]) + red4[3];
+  __syncthreads();
+  return before + (inc - v);
+}
+
+__global__ __launch_bounds__(256) void cdf_part_kernel(CdfPickArgs a) {
+  __shared__ double red[4];
+  const int c = blockIdx.x, r = blockIdx.y, tid = threadIdx.x, V = a.V;
+  const float* row = a.logits + (size_t)a.rows[r] * V;
+  const int v0 = c * kPickChunk;
+  float x[kPickPer];
+#pragma unroll
+  for (int k = 0; k < kPickPer; ++k) x[k] = row[min(v0 + tid + 256 * k, V - 1)];
   double mx = -INFINITY;
-  for (int v = v0; v < v1; ++v) mx = fmax(mx, (double)row[v] / a.T);
+#pragma unroll
+  for (int k = 0; k < kPickPer; ++k)
+    if (v0 + tid + 256 * k < V) mx = fmax(mx, (double)x[k] / a.T);
   for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
   if ((tid & 63) == 0) red[tid >> 6] = mx;
   __syncthreads();
+  mx = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+  __syncthreads();
+  double e = 0.0, tot;
+#pragma unroll
+  for (int k = 0; k < kPickPer; ++k)
+    if (v0 + tid + 256 * k < V && mx != -INFINITY) e += exp((double)x[k] / a.T - mx);
+  scan256(e, red, tot);
   if (tid == 0) {
-    double m = red[0];
-    for (int w = 1; w < kPickThreads / 64; ++w) m = fmax(m, red[w]);
-    red[0] = m;
-  }
-  __syncthreads();
-  mx = red[0];
-  double e = 0.0;
-  for (int v = v0; v < v1; ++v) e += exp((double)row[v] / a.T - mx);
-  part[tid] = e;
-  __syncthreads();
-  if (tid == 0) {
-    double S = 0.0;
-    for (int t = 0; t < kPickThreads; ++t) S += part[t];
-    red[1] = S;
-  }
-  __syncthreads();
-  const double S = red[1];
-  double c = 0.0;
-  for (int v = v0; v < v1; ++v) c += exp((double)row[v] / a.T - mx) / S;
-  __syncthreads();
-  part[tid] = c;
-  __syncthreads();
-  if (tid == 0) {
-    const double U = a.U[q];
-    double run = 0.0;
-    int pick = -1;
-    for (int t = 0; t < kPickThreads && pick < 0; ++t) {
-      if (run + part[t] > U) {
-        double c3 = run;
-        for (int v = t * C; v < min(V, t * C + C); ++v) {
-          c3 += exp((double)row[v] / a.T - mx) / S;
-          if (c3 > U) {
-            pick = v;
-            break;
-          }
-        }
-      }
-      run += part[t];
-    }
-    if (pick < 0) {
-      pick = 0;
-      for (int v = V - 1; v >= 0; --v)
-        if (exp((double)row[v] / a.T - mx) / S > 0.0) {
-          pick = v;
-          break;
-        }
-    }
-    a.out[q] = pick;
+    double* p = a.part + ((size_t)r * a.C + c) * 2;
+    p[0] = mx;
+    p[1] = tot;
   }
 }
 
+__global__ __launch_bounds__(256) void cdf_pick_kernel(CdfPickArgs a) {
+  __shared__ double red[4], pm[kPickMaxChunks], ps[kPickMaxChunks];
+  __shared__ int hit[4];
+  const int q = blockIdx.x, tid = threadIdx.x, V = a.V, C = a.C, r = a.qrow[q];
+  const float* row = a.logits + (size_t)a.rows[r] * V;
+  const double U = a.U[q];
+  // the chunks' (maximum, sum): in LDS, or past 2M ids where they lie
+  const double* part = a.part + (size_t)r * C * 2;
+  const bool in_lds = C <= kPickMaxChunks;
+  double M = -INFINITY, S = 0.0, run = 0.0;
+  if (in_lds) {
+    for (int c = tid; c < C; c += 256) {
+      pm[c] = part[2 * c];
+      ps[c] = part[2 * c + 1];
+    }
+    __syncthreads();
+    for (int c = 0; c < C; ++c) M = fmax(M, pm[c]);
+    __syncthreads();
+    for (int c = tid; c < C; c += 256) ps[c] *= exp(pm[c] - M);
+    __syncthreads();
+  } else {
+    for (int c = 0; c < C; ++c) M = fmax(M, part[2 * c]);
+  }
+  // (every thread walks the chunks alike: 25 of them for 50257 ids)
+  auto mass = [&](int c) { return in_lds ? ps[c] : part[2 * c + 1] * exp(part[2 * c] - M); };
+  for (int c = 0; c < C; ++c) S += mass(c);
+  int cx = -1;
+  for (int c = 0; c < C; ++c) {
+    const double pc = mass(c) / S;
+    if (run + pc > U) {
+      cx = c;
+      break;
+    }
+    run += pc;
+  }
+  // in the crossing chunk (or, rounding having left none, from the last chunk
+  // down): thread t holds ids v0 + 8 t .. + 7 and its running sum
+  for (int c = cx >= 0 ? cx : C - 1; c >= 0; --c) {
+    const int v0 = c * kPickChunk + tid * kPickPer;
+    double p[kPickPer], sum = 0.0, tot;
+    int last = -1;
+#pragma unroll
+    for (int i = 0; i < kPickPer; ++i) {
+      p[i] = v0 + i < V ? exp((double)row[min(v0 + i, V - 1)] / a.T - M) / S : 0.0;
+      sum += p[i];
+      if (p[i] > 0.0) last = v0 + i;
+    }
+    double acc = run + scan256(sum, red, tot);
+    int first = 0x7fffffff;
+    if (c == cx) {
+#pragma unroll
+      for (int i = 0; i < kPickPer; ++i) {
+        acc += p[i];
+        if (acc > U && first == 0x7fffffff && v0 + i < V) first = v0 + i;
+      }
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+      first = min(first, __shfl_xor(first, o));
+      last = max(last, __shfl_xor(last, o));
+    }
+    if ((tid & 63) == 0) {
+      hit[tid >> 6] = first;
+      red[tid >> 6] = (double)last;
+    }
+    __syncthreads();
+    first = min(min(hit[0], hit[1]), min(hit[2], hit[3]));
+    last = (int)fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+    __syncthreads();
+    const int pick = first != 0x7fffffff ? first : last;
+    if (pick >= 0) {
+      if (tid == 0) a.out[q] = pick;
+      return;
+    }
+  }
+  if (tid == 0) a.out[q] = 0;
+}
+
+size_t cdf_work_bytes(int V) { return (size_t)kMaxPicks * ((V + kPickChunk - 1) / kPickChunk) * 16; }
+
 hipError_t launch_cdf_pick(const CdfPickArgs& a, hipStream_t s) {
-  if (a.n < 1 || a.n > kMaxPicks || a.V < 1 || !(a.T > 0.f)) return hipErrorInvalidValue;
-  cdf_pick_kernel<<<a.n, kPickThreads, 0, s>>>(a);
+  if (a.n < 1 || a.n > kMaxPicks || a.nrows < 1 || a.nrows > a.n || a.V < 1 || !(a.T > 0.f) || !a.part)
+    return hipErrorInvalidValue;
+  if (a.C != (a.V + kPickChunk - 1) / kPickChunk) return hipErrorInvalidValue;
+  cdf_part_kernel<<<dim3(a.C, a.nrows), 256, 0, s>>>(a);
+  cdf_pick_kernel<<<a.n, 256, 0, s>>>(a);
   return hipGetLastError();
 }
 

@@ -111,7 +111,7 @@ struct ssd_kv {
   int* d_tree = nullptr;  // the staged tree (see stage_bytes)
   int* d_accept_tree = nullptr;  // tokens[N] parents[N] depth[N] for accept
   int* d_argmax = nullptr;
-  void* d_amwork = nullptr;  // argmax / top-k partials
+  void* d_amwork = nullptr;  // argmax / top-k / inverse-CDF partials
   void* d_sw = nullptr;   // the sampling walk's exchange area (sample_work_bytes, zeroed at creation)
   unsigned* d_err = nullptr;
   // pinned staging ring
@@ -550,7 +550,8 @@ extern "C" ssd_status ssd_kv_create(const ssd_model* m, int32_t max_ctx, int32_t
       take(m->f32 ? 0 : (size_t)c.n_head * attn_npath(max_nodes - 1) * max_nodes * (m->dh + 4) * 4);
   const size_t o_tree = take(stage_bytes(max_nodes));
   const size_t o_at = take((size_t)3 * max_nodes * 4), o_am = take((size_t)max_nodes * 4);
-  const size_t o_amw = take(std::max(argmax_work_bytes(max_nodes, V), topk_work_bytes(max_nodes, V)));
+  const size_t o_amw = take(
+      std::max({argmax_work_bytes(max_nodes, V), topk_work_bytes(max_nodes, V), cdf_work_bytes(V)}));
   const size_t o_sw = take(sample_work_bytes());
   const size_t o_err = take(256);
   const size_t o_sig = take(256);  // signal counter, XCD of block 0, sink
@@ -1447,9 +1448,14 @@ extern "C" ssd_status ssd_cdf_pick(ssd_kv* kv, const float* logits, int32_t n_ro
   for (int q = 0; q < n_queries; ++q) {
     if (rows[q] < 0 || rows[q] >= n_rows) return fail(SSD_E_INVALID_ARG, "row outside [0, n_rows)");
     if (!(uniforms[q] >= 0.0 && uniforms[q] < 1.0)) return fail(SSD_E_INVALID_ARG, "uniform outside [0, 1)");
-    a.rows[q] = rows[q];
+    // (queries of one row share its sums)
+    const int* known = std::find(a.rows, a.rows + a.nrows, rows[q]);
+    a.qrow[q] = (int)(known - a.rows);
+    if (a.qrow[q] == a.nrows) a.rows[a.nrows++] = rows[q];
     a.U[q] = uniforms[q];
   }
+  a.C = (vocab + 2047) / 2048;
+  a.part = (double*)kv->d_amwork;
   HIP_TRY(launch_cdf_pick(a, (hipStream_t)stream));
   return SSD_OK;
 }

@@ -213,17 +213,21 @@ hipError_t launch_sample_accept(const int* tokens, const int* parents, int N, in
                                 const float* draft, double temperature, uint64_t seed, int mode, int topk, void* work,
                                 unsigned* err, int* path, int* path_len, int* next, hipStream_t s);
 // inverse-CDF picks for CDF-first tree assembly: out[q] = the token drawn
-// from softmax(logits[rows[q]] / T) (whole vocabulary V) at uniform U[q], by
-// ascending token id
-constexpr int kMaxPicks = 64;
+// from softmax(logits[rows[qrow[q]]] / T) (whole vocabulary V) at uniform U[q],
+// by ascending token id; rows holds the queries' distinct rows, part
+// cdf_work_bytes(V) bytes of device scratch, C the chunks of 2048 ids (whose
+// sums a workgroup keeps in LDS up to kPickMaxChunks)
+constexpr int kMaxPicks = 64, kPickMaxChunks = 1024;
 struct CdfPickArgs {
   const float* logits;
-  int V, n;
+  int V, n, nrows, C;
   float T;
-  int rows[kMaxPicks];
+  int rows[kMaxPicks], qrow[kMaxPicks];
   double U[kMaxPicks];
+  double* part;
   int* out;
 };
+size_t cdf_work_bytes(int V);
 hipError_t launch_cdf_pick(const CdfPickArgs& a, hipStream_t s);
 hipError_t launch_commit(int f32, void* kc, void* vc, const void* kt, const void* vt, int LH, int max_ctx,
                          int max_nodes, int DH, int P, const int* path, const int* path_len, unsigned* err,
