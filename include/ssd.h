@@ -264,7 +264,7 @@ ssd_status ssd_tree_accept(ssd_kv *kv, const ssd_tree *tree, const float *draft_
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  It
  * needs no session and calls no allocating routine: its scratch (the staged
  * tree, argmax partials, the sampling walk's exchange area) is one
- * file-scope device array of 209,408 bytes that every GPU the library runs on holds
+ * file-scope device array of 213,248 bytes that every GPU the library runs on holds
  * until the process ends, and the tree reaches the device inside the kernel
  * arguments.  Limits: n_nodes <= 256 and vocab <= 65536 (SSD_E_CAPACITY
  * beyond).  All calls on one GPU share that GPU's array: calls that overlap

@@ -2495,33 +2495,42 @@ __device__ __forceinline__ unsigned mono_key(float f) {
 // the vocabulary slice [2048 g, 2048 g + 2048) of the current node's target
 // p, residual r and draft row q in LDS (float64), thread t the 8 entries
 // 8t .. 8t + 7 of the slice.  Every decision needs a few sums over the whole
-// vocabulary; the workgroups exchange their slices' values in rounds: each
-// stores a record, waits for its stores, raises its round flag, and waits
-// for all G flags of the round, then reads every record and combines them
-// in slice order, so all workgroups hold the same sums and take the same
-// branches.  Records alternate between two buffers by round parity: a
-// workgroup writes round k + 2 only after every workgroup has raised round
-// k + 1, which each does after reading round k.
+// vocabulary; the workgroups exchange their slices' values in rounds and
+// combine them in slice order, so all workgroups hold the same sums and take
+// the same branches.
+//
+// Exchange: a value travels as 8-byte words {round tag, 4 bytes of data}, each
+// stored and loaded whole, and a reader polls the words themselves until
+// they carry the round's tag: no flag follows the data, so a round is one
+// store and one polled load, with nothing to wait for in between.  Words
+// alternate between two buffers by round parity: a workgroup writes round k + 2
+// only after it has read every workgroup's round k + 1, which each wrote after
+// reading round k.  Tags are epoch * 65536 + round, the epoch read from ctl[0]
+// at start (the last workgroup to finish raises it, and clears the words
+// when its 16 bits wrap), so nothing is cleared between calls.
 //
 // Placement: 8 G workgroups are launched and those of index 8 g take slice
 // g (the others leave at once), so that with the usual round-robin dispatch
 // all G share one XCD.  The first round exchanges each workgroup's XCD; if
-// they agree, later rounds keep records and flags in that XCD's L2 (plain
-// stores; readers drop their CU's L1 first), otherwise every access is
-// device-coherent (sc1) throughout.
+// they agree, later rounds keep their words in that XCD's L2 (plain stores),
+// otherwise every store is device-coherent (sc1) throughout.
 //
 // Rounds per node: the radix select of the top-k cut (4, plus 1 for the
-// tie ranks), the softmax statistics (max, rescaled sum, draft sum: 1), then
-// one per tested child: the owner of the child's token decides, and every
-// workgroup adds up its slice's residual as it would be after a rejection;
-// on rejection every workgroup applies it.  The extra token takes one more
-// round (slice sums, then a scan of the crossing slice).
+// ranks when not all ties at the cut are kept), the softmax statistics (max,
+// rescaled sum, draft sum: 1), then one per tested child: the owner of the
+// child's token decides, and every workgroup adds up its slice's residual as
+// it would be after a rejection; on rejection every workgroup applies it.  The
+// extra token takes one more round (slice sums, then a scan of the crossing
+// slice).
 //
-// Round flags carry epoch * 65536 + round, the epoch read from ctl[0] at
-// start (the last workgroup to finish raises it), so nothing is cleared
-// between calls.  Every wait is bounded; a wait that times out (the
-// workgroups could not all run at once) raises ctl[2], every workgroup
-// leaves, *path_len is set to 0 and err (when given) counts it.
+// What bounds it is the chain of rounds.  Whole calls over 50257 tokens, against
+// records published by a flag after their stores completed and 256-step
+// scans by one thread: drawn children of a 256-node tree 144 -> 94 us,
+// top-50 over chosen children 119 -> 64 us.
+//
+// Every wait is bounded; a wait that times out (the workgroups could not all
+// run at once) raises ctl[2], every workgroup leaves, *path_len is set to 0
+// and err (when given) counts it.
 // mode: 1 siblings drawn without replacement from draft row u, 2 drawn
 // independently, 3 chosen (each child proposed with certainty; no draft
 // rows), 4 CDF-first (no draft rows: the oracle's token at node u is the
@@ -2531,13 +2540,15 @@ __device__ __forceinline__ unsigned mono_key(float f) {
 // the cut to the lower id).
 
 constexpr int SW_THREADS = 256, SW_SLICE = 2048, SW_PER = SW_SLICE / SW_THREADS, SW_MAXG = 64, SW_REC = 4;
+constexpr int SW_HW = 128;     // words of a workgroup's 256-bin histogram, two 16-bit counts each
 constexpr int SW_MAXN = 1024;  // nodes (the tree's parents sit in LDS)
-enum { SWC_EPOCH = 0, SWC_DONE = 1, SWC_ABORT = 2, SWC_FLAGS = 64 };
-// work layout (bytes): ctl + flags (u32[SWC_FLAGS + SW_MAXG]), records
-// double[2][SW_MAXG][SW_REC], histograms u32[2][SW_MAXG][256]
-constexpr size_t kSwRecOfs = (SWC_FLAGS + SW_MAXG) * 4;
-constexpr size_t kSwHistOfs = kSwRecOfs + (size_t)2 * SW_MAXG * SW_REC * 8;
-constexpr size_t kSwBytes = kSwHistOfs + (size_t)2 * SW_MAXG * 256 * 4;
+enum { SWC_EPOCH = 0, SWC_DONE = 1, SWC_ABORT = 2, SWC_WORDS = 64 };
+typedef unsigned long long sw_word;  // {tag, data}: tag in the high half
+// work layout (bytes): control words (u32[SWC_WORDS]), records
+// sw_word[2][SW_MAXG][2 SW_REC], histograms sw_word[2][SW_MAXG][SW_HW]
+constexpr size_t kSwRecOfs = SWC_WORDS * 4;
+constexpr size_t kSwHistOfs = kSwRecOfs + (size_t)2 * SW_MAXG * 2 * SW_REC * 8;
+constexpr size_t kSwBytes = kSwHistOfs + (size_t)2 * SW_MAXG * SW_HW * 8;
 
 struct SwArgs {
   const int* tokens;
@@ -2558,12 +2569,12 @@ struct SwArgs {
 
 struct SwState {
   unsigned* ctl;
-  unsigned* flags;
-  double* rec;     // [2][SW_MAXG][SW_REC]
-  unsigned* hist;  // [2][SW_MAXG][256]
+  sw_word* rec;    // [2][SW_MAXG][2 SW_REC]
+  sw_word* hist;   // [2][SW_MAXG][SW_HW]
   unsigned tagbase;
   int k;           // rounds done
-  bool local;      // every workgroup on one XCD: records and flags through its L2
+  bool local;      // every workgroup on one XCD: words through its L2
+  int* fail;       // LDS: a wait of this workgroup gave up
 };
 
 __device__ __forceinline__ unsigned sw_xcc() {
@@ -2571,38 +2582,93 @@ __device__ __forceinline__ unsigned sw_xcc() {
   asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(x));
   return x & 15;
 }
-__device__ __forceinline__ double* sw_rec(SwState& st, int par, int g) {
-  return st.rec + ((size_t)par * SW_MAXG + g) * SW_REC;
+// (a plain store into the XCD's L2, or a device-coherent one; the load misses
+// the L1 and reads what either left)
+__device__ __forceinline__ void sw_st(const SwState& st, sw_word* p, unsigned v) {
+  const sw_word x = ((sw_word)(st.tagbase + (unsigned)st.k + 1u) << 32) | v;
+  if (st.local) __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  else __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ unsigned* sw_hist(SwState& st, int par, int g) {
-  return st.hist + ((size_t)par * SW_MAXG + g) * 256;
+__device__ __forceinline__ sw_word sw_ld(const sw_word* p) {
+  return __hip_atomic_load((sw_word*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// local: plain stores into the XCD's L2, read with non-temporal loads
-// (which do not hit lines the reader's L1 kept from an earlier round);
-// otherwise device-coherent (sc1) accesses
-template <typename T>
-__device__ __forceinline__ void sw_st(const SwState& st, T* p, T v) {
-  if (st.local) *(__attribute__((address_space(1))) T*)p = v;
-  else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// word j of this workgroup's record for the round in progress
+__device__ __forceinline__ void sw_put(const SwState& st, int g, int j, double v) {
+  sw_word* p = st.rec + (((size_t)(st.k & 1) * SW_MAXG + g) * SW_REC + j) * 2;
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  sw_st(st, p, (unsigned)u);
+  sw_st(st, p + 1, (unsigned)(u >> 32));
 }
-template <typename T>
-__device__ __forceinline__ T sw_ld(const SwState& st, const T* p) {
-  if (st.local) return __builtin_nontemporal_load((const __attribute__((address_space(1))) T*)p);
-  return __hip_atomic_load((T*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+
+// Loads the word at p (the caller's) until it carries the round's tag, for
+// the active lanes of a wave together; on an abort or a timeout the wave
+// gives up and marks *st.fail.
+__device__ __forceinline__ unsigned sw_wait(const SwArgs& a, SwState& st, const sw_word* p) {
+  const unsigned tag = st.tagbase + (unsigned)st.k + 1u;
+  const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
+  for (int it = 1;; ++it) {
+    const sw_word x = sw_ld(p);
+    if (__all((unsigned)(x >> 32) == tag)) return (unsigned)x;
+    if (it & 15) continue;
+    // (the abort word and the clock, every 16th look)
+    bool stop = __hip_atomic_load(st.ctl + SWC_ABORT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+    if (!stop && __builtin_amdgcn_s_memrealtime() - t0 > a.timeout) {
+      stop = true;
+      if ((threadIdx.x & 63) == 0 && __hip_atomic_exchange(st.ctl + SWC_ABORT, 1u, __ATOMIC_RELAXED,
+                                                           __HIP_MEMORY_SCOPE_AGENT) == 0u && a.err)
+        __hip_atomic_fetch_add(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (__any(stop)) {
+      *(volatile int*)st.fail = 1;
+      return 0;
+    }
+  }
+}
+
+// Closes a round of records of nv values: every workgroup's record into gb
+// (two buffers by round parity, so the next round's values never overwrite
+// what a slower thread still reads).  False (in every thread) on an abort or
+// timeout.
+typedef double SwGather[SW_MAXG][SW_REC];
+__device__ __forceinline__ bool sw_gather(const SwArgs& a, SwState& st, int nv, SwGather* gb) {
+  const int par = st.k & 1;
+  unsigned* out = (unsigned*)gb[par];
+  for (int i0 = threadIdx.x & ~63; i0 < a.G * 2 * nv; i0 += SW_THREADS) {
+    const int i = min(i0 + (int)(threadIdx.x & 63), a.G * 2 * nv - 1);
+    const int gg = i / (2 * nv), j = i - gg * 2 * nv;
+    const unsigned v = sw_wait(a, st, st.rec + ((size_t)par * SW_MAXG + gg) * (2 * SW_REC) + j);
+    out[gg * 2 * SW_REC + j] = v;
+    if (*(volatile int*)st.fail) break;
+  }
+  __syncthreads();
+  ++st.k;
+  return *(volatile int*)st.fail == 0;
 }
 
 // Fixed-order sums and maxima over the workgroup: each wave's value by a
 // butterfly, lane 0's result taken (every lane then holds the same value),
-// then the four waves in order; every thread returns the same value.
+// then the four waves in order; every thread returns the same value.  red
+// holds two buffers of 8, used in turn, so one barrier per call is enough.
 __device__ __forceinline__ double sw_wave_sum(double v) {
+#pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
   return __shfl(v, 0);
 }
 __device__ __forceinline__ double sw_wave_max(double v) {
+#pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
   return __shfl(v, 0);
 }
-__device__ void sw_sum2(double& a, double& b, double* red) {
+struct SwRed {
+  double* buf;  // LDS [2][8]
+  int turn;
+  __device__ __forceinline__ double* next() {
+    turn ^= 8;
+    return buf + turn;
+  }
+};
+__device__ __forceinline__ void sw_sum2(double& a, double& b, SwRed& rd) {
+  double* red = rd.next();
   const double wa = sw_wave_sum(a), wb = sw_wave_sum(b);
   const int w = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) {
@@ -2612,89 +2678,52 @@ __device__ void sw_sum2(double& a, double& b, double* red) {
   __syncthreads();
   a = (red[0] + red[1]) + (red[2] + red[3]);
   b = (red[4] + red[5]) + (red[6] + red[7]);
-  __syncthreads();
 }
-__device__ double sw_max(double v, double* red) {
+__device__ __forceinline__ double sw_max(double v, SwRed& rd) {
+  double* red = rd.next();
   const double wv = sw_wave_max(v);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = wv;
   __syncthreads();
-  const double r = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
-  __syncthreads();
-  return r;
+  return fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
 }
-
-// Publishes this workgroup's round (its record stores issued before) and
-// waits for every workgroup's; false on abort or timeout (in every thread).
-__device__ bool sw_round(const SwArgs& a, SwState& st, int g, int* shok) {
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  const unsigned tag = st.tagbase + (unsigned)st.k + 1u;
-  if (threadIdx.x == 0) sw_st(st, st.flags + g, tag);
-  if (threadIdx.x < 64) {
-    const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
-    bool ok = false;
-    for (;;) {
-      bool mine = true;
-      for (int i = threadIdx.x; i < a.G; i += 64)
-        mine = mine && (int)(__hip_atomic_load(st.flags + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - tag) >= 0;
-      if (__all(mine)) {
-        ok = true;
-        break;
-      }
-      if (__hip_atomic_load(st.ctl + SWC_ABORT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
-      if (__builtin_amdgcn_s_memrealtime() - t0 > a.timeout) {
-        if (threadIdx.x == 0 && __hip_atomic_exchange(st.ctl + SWC_ABORT, 1u, __ATOMIC_RELAXED,
-                                                      __HIP_MEMORY_SCOPE_AGENT) == 0u && a.err)
-          __hip_atomic_fetch_add(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        break;
-      }
-      __builtin_amdgcn_s_sleep(1);
-    }
-    if (threadIdx.x == 0) *shok = ok;
-  }
-  __syncthreads();
-  const bool ok = *shok != 0;
-  if (ok && st.local) asm volatile("buffer_inv sc0" ::: "memory");
-  __syncthreads();
-  ++st.k;
-  return ok;
-}
-
-// every workgroup's record of round parity par into LDS (thread i loads
-// workgroup i's), for the combining thread to read in slice order
-__device__ __forceinline__ void sw_gather(SwState& st, int par, int G, double (*gb)[SW_REC]) {
-  for (int i = threadIdx.x; i < G; i += SW_THREADS)
+// sum of v over the threads before this one, and over all
+__device__ __forceinline__ double sw_scan(double v, SwRed& rd, double& total) {
+  double* red = rd.next();
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  double inc = v;
 #pragma unroll
-    for (int j = 0; j < SW_REC; ++j) gb[i][j] = sw_ld(st, sw_rec(st, par, i) + j);
+  for (int o = 1; o < 64; o <<= 1) {
+    const double t = __shfl_up(inc, o);
+    if (lane >= o) inc += t;
+  }
+  if (lane == 63) red[w] = inc;
   __syncthreads();
+  double before = 0.0;
+  for (int i = 0; i < w; ++i) before += red[i];
+  total = ((red[0] + red[1]) + red[2]) + red[3];
+  return before + (inc - v);
 }
 
-// the first child of u above index c0 (N if none): every thread tests its
-// share of the candidates, then the smallest hit over the workgroup
-__device__ __forceinline__ int sw_next_child(const int* par_l, int N, int u, int c0, int* shmin) {
-  int best = N;
-  for (int c = c0 + 1 + (int)threadIdx.x; c < N; c += SW_THREADS)
-    if (par_l[c] == u) {
-      best = c;
-      break;
-    }
-  for (int o = 32; o > 0; o >>= 1) best = min(best, __shfl_xor(best, o));
-  if ((threadIdx.x & 63) == 0) shmin[threadIdx.x >> 6] = best;
-  __syncthreads();
-  const int r = min(min(shmin[0], shmin[1]), min(shmin[2], shmin[3]));
-  __syncthreads();
-  return r;
+// the first child of u above index c0 (N if none); every wave looks alike
+__device__ __forceinline__ int sw_next_child(const int* par_l, int N, int u, int c0) {
+  const int lane = threadIdx.x & 63;
+  for (int c = c0 + 1; c < N; c += 64) {
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(c + lane < N && par_l[min(c + lane, N - 1)] == u);
+    if (m) return c + __builtin_ctzll(m);
+  }
+  return N;
 }
 
 // The smallest v whose running sum of w exceeds target, summed per thread
-// in index order, per slice over threads in order, then over slices in order
-// (if rounding leaves none, the last v with positive w), returned to every
-// workgroup: one round for the slice sums, one for the pick of the slice's
-// owner.  ok turns false (in every thread) on an abort or timeout.
-__device__ int sw_pick_all(const SwArgs& a, SwState& st, int g, int G, const double* w, double target, int b0,
-                           double* cs, double* red, double (*gb)[SW_REC], int* shi, bool& ok) {
+// in index order, per slice over threads, then over slices in order (if
+// rounding leaves none, the last v with positive w): one round for the slice
+// sums, after which the workgroup that holds v (every other thread and
+// workgroup gets -1) returns it in one or more of its threads.  ok turns
+// false (in every thread) on an abort or timeout.
+__device__ __forceinline__ int sw_pick(const SwArgs& a, SwState& st, int g, int G, const double* w, double target,
+                                       int b0, SwRed& rd, SwGather* gb, int* shi, bool& ok) {
   const int tid = threadIdx.x;
-  double c1 = 0.0;
+  double c1 = 0.0, Wg;
   int lastpos = -1;
 #pragma unroll
   for (int i = 0; i < SW_PER; ++i) {
@@ -2702,107 +2731,86 @@ __device__ int sw_pick_all(const SwArgs& a, SwState& st, int g, int G, const dou
     c1 += wv;
     if (wv > 0.0) lastpos = b0 + i;
   }
-  cs[tid] = c1;
-  const int lp = (int)sw_max((double)lastpos, red);
-  int par = st.k & 1;
+  const double before = sw_scan(c1, rd, Wg);
+  const int lp = (int)sw_max((double)lastpos, rd);
+  const int par = st.k & 1;
   if (tid == 0) {
-    double Wg = 0.0;
-    for (int t = 0; t < SW_THREADS; ++t) Wg += cs[t];
-    double* rc = sw_rec(st, par, g);
-    sw_st(st, rc, Wg);
-    sw_st(st, rc + 1, (double)lp);
+    sw_put(st, g, 0, Wg);
+    sw_put(st, g, 1, (double)lp);
+    shi[5] = 0x7fffffff;
   }
-  ok = sw_round(a, st, g, shi + 1);
+  ok = sw_gather(a, st, 2, gb);
   if (!ok) return -1;
-  sw_gather(st, par, G, gb);
-  if (tid == 0) {
-    double run = 0.0;
-    int gx = -1, choice = -1;
-    for (int gg = 0; gg < G; ++gg) {
-      if (run + gb[gg][0] > target) {
-        gx = gg;
+  // the slice where the running sum crosses the target
+  double run = 0.0;
+  int gx = -1;
+  for (int gg = 0; gg < G; ++gg) {
+    const double s = gb[par][gg][0];
+    if (run + s > target) {
+      gx = gg;
+      break;
+    }
+    run += s;
+  }
+  if (gx < 0) {
+    // rounding left no crossing: the last token with positive weight
+    int x = 0;
+    for (int gg = G - 1; gg >= 0; --gg)
+      if (gb[par][gg][1] >= 0.0) {
+        x = (int)gb[par][gg][1];
         break;
       }
-      run += gb[gg][0];
-    }
-    if (gx == g) {
-      double c2 = run;
-      for (int t = 0; t < SW_THREADS && choice < 0; ++t) {
-        if (c2 + cs[t] > target) {
-          double c3 = c2;
-          for (int i = 0; i < SW_PER; ++i) {
-            c3 += w[t * SW_PER + i];
-            if (c3 > target) {
-              choice = g * SW_SLICE + t * SW_PER + i;
-              break;
-            }
-          }
-        }
-        c2 += cs[t];
-      }
-      if (choice < 0) choice = lp >= 0 ? lp : g * SW_SLICE;
-    } else if (gx < 0) {
-      // rounding left no crossing: the last token with positive weight
-      choice = 0;
-      for (int gg = G - 1; gg >= 0; --gg)
-        if (gb[gg][1] >= 0.0) {
-          choice = (int)gb[gg][1];
-          break;
-        }
-    }
-    shi[5] = gx;
-    shi[6] = choice;
+    return x / SW_SLICE == g ? x : -1;
   }
-  __syncthreads();
-  const int gx = shi[5];
-  if (gx < 0) {
-    const int x = shi[6];
-    __syncthreads();
-    return x;
+  if (gx != g) return -1;
+  double c2 = run + before;
+  int first = 0x7fffffff;
+#pragma unroll
+  for (int i = 0; i < SW_PER; ++i) {
+    c2 += w[tid * SW_PER + i];
+    if (first == 0x7fffffff && c2 > target) first = b0 + i;
   }
-  par = st.k & 1;
-  if (tid == 0) sw_st(st, sw_rec(st, par, g), g == gx ? (double)shi[6] : 0.0);
-  ok = sw_round(a, st, g, shi + 1);
-  if (!ok) return -1;
-  sw_gather(st, par, G, gb);
-  const int x = (int)gb[gx][0];
+  if (first != 0x7fffffff) atomicMin(&shi[5], first);
   __syncthreads();
-  return x;
+  const int x = shi[5];
+  return x != 0x7fffffff ? x : lp >= 0 ? lp : g * SW_SLICE;  // (rounding left no crossing in the slice)
 }
 
 __global__ __launch_bounds__(SW_THREADS) void sample_accept_kernel(SwArgs a) {
   if (blockIdx.x & 7) return;  // (see Placement above)
   __shared__ double r[SW_SLICE], p[SW_SLICE], q[SW_SLICE];
-  __shared__ double red[8], cs[SW_THREADS];
+  __shared__ double red[16];
   __shared__ unsigned hl[256];
   __shared__ int shi[8];
-  __shared__ double shd[8];
-  __shared__ double gb[SW_MAXG][SW_REC];
-  __shared__ int par_l[SW_MAXN], shmin[4];
+  __shared__ double shd[4];
+  __shared__ SwGather gb[2];
+  __shared__ int par_l[SW_MAXN], fail;
   const int tid = threadIdx.x, g = blockIdx.x >> 3, G = a.G, V = a.V;
   for (int i = tid; i < a.N; i += SW_THREADS) par_l[i] = a.parents[i];
   const int b0 = g * SW_SLICE + tid * SW_PER;  // this thread's first vocabulary index
   const bool wor = a.mode == 1, det = a.mode == 3, cdf = a.mode == 4;
   const bool cut = a.topk > 0 && a.topk < V;
+  SwRed rd{red, 0};
   SwState st;
   st.ctl = (unsigned*)a.work;
-  st.flags = st.ctl + SWC_FLAGS;
-  st.rec = (double*)(a.work + kSwRecOfs);
-  st.hist = (unsigned*)(a.work + kSwHistOfs);
+  st.rec = (sw_word*)(a.work + kSwRecOfs);
+  st.hist = (sw_word*)(a.work + kSwHistOfs);
   st.k = 0;
   st.local = false;
-  if (tid == 0) shi[0] = (int)__hip_atomic_load(st.ctl + SWC_EPOCH, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  st.fail = &fail;
+  if (tid == 0) {
+    shi[0] = (int)__hip_atomic_load(st.ctl + SWC_EPOCH, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    fail = 0;
+  }
   __syncthreads();
   st.tagbase = ((unsigned)shi[0] + 1u) * 65536u;
   // round 0: where every workgroup runs
-  if (tid == 0) sw_st(st, sw_rec(st, 0, g), (double)sw_xcc());
-  bool ok = sw_round(a, st, g, shi + 1);
+  if (tid == 0) sw_put(st, g, 0, (double)sw_xcc());
+  bool ok = sw_gather(a, st, 1, gb);
   if (ok) {
-    sw_gather(st, 0, G, gb);
     bool same = true;
-    for (int i = 0; i < G; ++i) same = same && gb[i][0] == gb[0][0];
+    for (int i = 0; i < G; ++i) same = same && gb[0][i][0] == gb[0][0][0];
     st.local = same;
-    __syncthreads();
   }
   int u = 0, len = 1, cdf_x = 0;
   if (ok && g == 0 && tid == 0) a.path[0] = 0;
@@ -2812,79 +2820,107 @@ __global__ __launch_bounds__(SW_THREADS) void sample_accept_kernel(SwArgs a) {
     float lg[SW_PER];
     unsigned key[SW_PER];
     bool keep[SW_PER];
+    double qv[SW_PER], rv[SW_PER];
 #pragma unroll
     for (int i = 0; i < SW_PER; ++i) {
       const int v = b0 + i;
       lg[i] = v < V ? a.logits[(size_t)u * V + v] : 0.f;
       keep[i] = v < V;
       key[i] = mono_key(lg[i]);
-      q[tid * SW_PER + i] = (!det && !cdf && v < V) ? (double)a.draft[(size_t)u * V + v] : 0.0;
+      qv[i] = (!det && !cdf && v < V) ? (double)a.draft[(size_t)u * V + v] : 0.0;
     }
     if (cut) {
       // radix select of the topk-th largest key over all slices, 8 bits a pass
       unsigned prefix = 0, mask = 0;
-      int need = a.topk;
+      int need = a.topk, ties = 0;
       for (int pass = 0; pass < 4; ++pass) {
-        const int shift = 24 - 8 * pass;
+        const int shift = 24 - 8 * pass, par = st.k & 1;
         hl[tid] = 0;
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < SW_PER; ++i)
           if (keep[i] && (key[i] & mask) == prefix) atomicAdd(&hl[(key[i] >> shift) & 255u], 1u);
         __syncthreads();
-        const int par = st.k & 1;
-        sw_st(st, sw_hist(st, par, g) + tid, hl[tid]);
-        ok = sw_round(a, st, g, shi + 1);
-        if (!ok) break;
-        unsigned tot = 0;
-        for (int gg = 0; gg < G; ++gg) tot += sw_ld(st, sw_hist(st, par, gg) + tid);
-        hl[tid] = tot;
+        // (counts are at most SW_SLICE: two per word)
+        if (tid < SW_HW)
+          sw_st(st, st.hist + ((size_t)par * SW_MAXG + g) * SW_HW + tid, hl[2 * tid] | (hl[2 * tid + 1] << 16));
+        // thread t adds up digits 2 (t % 128), + 1 of every second slice
+        unsigned lo = 0, hi = 0;
+        for (int gg = tid >> 7; gg < G; gg += 2) {
+          const unsigned v = sw_wait(a, st, st.hist + ((size_t)par * SW_MAXG + gg) * SW_HW + (tid & 127));
+          lo += v & 0xffffu;
+          hi += v >> 16;
+          if (*(volatile int*)st.fail) break;
+        }
         __syncthreads();
-        if (tid == 0) {
-          int cum = 0, dgt = 255;
-          for (; dgt > 0; --dgt) {
-            if (cum + (int)hl[dgt] >= need) break;
-            cum += (int)hl[dgt];
+        ++st.k;
+        ok = *(volatile int*)st.fail == 0;
+        if (!ok) break;
+        if (tid >= 128) {
+          hl[2 * (tid & 127)] = lo;
+          hl[2 * (tid & 127) + 1] = hi;
+        }
+        __syncthreads();
+        if (tid < 128) {
+          hl[2 * tid] += lo;
+          hl[2 * tid + 1] += hi;
+        }
+        __syncthreads();
+        // the digit of the need-th largest: wave 0, lane l holds digits
+        // 255 - 4 l .. 252 - 4 l and the count of every larger digit
+        if (tid < 64) {
+          unsigned c4[4], sum = 0;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sum += c4[e] = hl[255 - 4 * tid - e];
+          unsigned inc = sum;
+#pragma unroll
+          for (int o = 1; o < 64; o <<= 1) {
+            const unsigned t = __shfl_up(inc, o);
+            if (tid >= o) inc += t;
           }
-          shi[2] = dgt;
-          shi[3] = need - cum;
+          unsigned cum = inc - sum;
+          // (digit 0 takes what is left, as when fewer than need are held)
+          if ((cum < (unsigned)need && inc >= (unsigned)need) || (tid == 63 && inc < (unsigned)need)) {
+            int e = 0;
+            for (; e < 3; ++e) {
+              if (cum + c4[e] >= (unsigned)need) break;
+              cum += c4[e];
+            }
+            shi[2] = 255 - 4 * tid - e;
+            shi[3] = need - (int)cum;
+            shi[4] = (int)c4[e];
+          }
         }
         __syncthreads();
         prefix |= (unsigned)shi[2] << shift;
         mask |= 255u << shift;
         need = shi[3];
-        __syncthreads();
+        ties = shi[4];
       }
       if (!ok) break;
-      // tie ranks at the cut: ties in lower slices, lower threads, then in order
-      int cnt = 0;
+      if (ties == need) {
+        // every key at the cut is kept
 #pragma unroll
-      for (int i = 0; i < SW_PER; ++i) cnt += keep[i] && key[i] == prefix;
-      cs[tid] = (double)cnt;
-      __syncthreads();
-      if (tid == 0) {
-        double run = 0.0;
-        for (int t = 0; t < SW_THREADS; ++t) {
-          const double c = cs[t];
-          cs[t] = run;
-          run += c;
+        for (int i = 0; i < SW_PER; ++i) keep[i] = keep[i] && key[i] >= prefix;
+      } else {
+        // tie ranks at the cut: ties in lower slices, lower threads, then in order
+        int cnt = 0;
+#pragma unroll
+        for (int i = 0; i < SW_PER; ++i) cnt += keep[i] && key[i] == prefix;
+        double tot;
+        const double before = sw_scan((double)cnt, rd, tot);
+        const int par = st.k & 1;
+        if (tid == 0) sw_put(st, g, 0, tot);
+        ok = sw_gather(a, st, 1, gb);
+        if (!ok) break;
+        double base = before;
+        for (int gg = 0; gg < g; ++gg) base += gb[par][gg][0];
+        int rank = (int)base;
+#pragma unroll
+        for (int i = 0; i < SW_PER; ++i) {
+          if (!keep[i] || key[i] > prefix) continue;
+          keep[i] = key[i] == prefix && rank++ < need;
         }
-        shd[0] = run;
-      }
-      __syncthreads();
-      int rank = (int)cs[tid];
-      const int par = st.k & 1;
-      if (tid == 0) sw_st(st, sw_rec(st, par, g), shd[0]);
-      ok = sw_round(a, st, g, shi + 1);
-      if (!ok) break;
-      sw_gather(st, par, G, gb);
-      double base = 0.0;
-      for (int gg = 0; gg < g; ++gg) base += gb[gg][0];
-      rank += (int)base;
-#pragma unroll
-      for (int i = 0; i < SW_PER; ++i) {
-        if (!keep[i] || key[i] > prefix) continue;
-        keep[i] = key[i] == prefix && rank++ < need;
       }
     }
     // ---- softmax statistics over the kept entries, and the draft row's sum
@@ -2892,48 +2928,43 @@ __global__ __launch_bounds__(SW_THREADS) void sample_accept_kernel(SwArgs a) {
 #pragma unroll
     for (int i = 0; i < SW_PER; ++i)
       if (keep[i]) mloc = fmax(mloc, (double)lg[i] / a.T);
-    const double m_g = sw_max(mloc, red);
-    double sl = 0.0, ql = 0.0;
+    const double m_g = sw_max(mloc, rd);
+    double sl = 0.0, ql = 0.0, ex[SW_PER];
 #pragma unroll
     for (int i = 0; i < SW_PER; ++i) {
-      if (keep[i]) sl += exp((double)lg[i] / a.T - m_g);
-      ql += q[tid * SW_PER + i];
+      ex[i] = keep[i] ? exp((double)lg[i] / a.T - m_g) : 0.0;
+      sl += ex[i];
+      ql += qv[i];
     }
-    sw_sum2(sl, ql, red);
+    sw_sum2(sl, ql, rd);
+    const int sp = st.k & 1;
+    if (tid == 0) {
+      sw_put(st, g, 0, m_g);
+      sw_put(st, g, 1, sl);
+      sw_put(st, g, 2, ql);
+    }
+    ok = sw_gather(a, st, 3, gb);
+    if (!ok) break;
+    double M = -INFINITY, S = 0.0;
+    for (int gg = 0; gg < G; ++gg) M = fmax(M, gb[sp][gg][0]);
+    // (one slice's rescaled sum per lane, then added in slice order)
     {
-      const int par = st.k & 1;
-      if (tid == 0) {
-        double* rc = sw_rec(st, par, g);
-        sw_st(st, rc, m_g);
-        sw_st(st, rc + 1, sl);
-        sw_st(st, rc + 2, ql);
+      const int lane = tid & 63;
+      const double mg = lane < G ? gb[sp][lane][0] : -INFINITY;
+      const double sg = mg != -INFINITY ? gb[sp][lane][1] * exp(mg - M) : 0.0;
+      Zq = 0.0;
+      for (int gg = 0; gg < G; ++gg) {
+        S += __shfl(sg, gg);
+        Zq += gb[sp][gg][2];
       }
-      ok = sw_round(a, st, g, shi + 1);
-      if (!ok) break;
-      sw_gather(st, par, G, gb);
-      if (tid == 0) {
-        double M = -INFINITY;
-        for (int gg = 0; gg < G; ++gg) M = fmax(M, gb[gg][0]);
-        double S = 0.0, Sq = 0.0;
-        for (int gg = 0; gg < G; ++gg) {
-          const double mg = gb[gg][0];
-          if (mg != -INFINITY) S += gb[gg][1] * exp(mg - M);
-          Sq += gb[gg][2];
-        }
-        shd[1] = M;
-        shd[2] = S;
-        shd[3] = Sq;
-      }
-      __syncthreads();
     }
-    const double M = shd[1], S = shd[2];
-    Zq = shd[3];
-    __syncthreads();
 #pragma unroll
     for (int i = 0; i < SW_PER; ++i) {
       const double pv = keep[i] ? exp((double)lg[i] / a.T - M) / S : 0.0;
+      rv[i] = pv;
       p[tid * SW_PER + i] = pv;
       r[tid * SW_PER + i] = pv;
+      q[tid * SW_PER + i] = qv[i];
     }
     __syncthreads();
     Z = 1.0;
@@ -2941,34 +2972,40 @@ __global__ __launch_bounds__(SW_THREADS) void sample_accept_kernel(SwArgs a) {
     if (cdf) {
       // ---- the oracle's token at u: the inverse CDF of p at u's own
       // uniform; the walk follows the first child that carries it
-      cdf_x = sw_pick_all(a, st, g, G, p, philox_uniform(a.seed, 2, (uint64_t)u), b0, cs, red, gb, shi, ok);
+      const int x = sw_pick(a, st, g, G, p, philox_uniform(a.seed, 2, (uint64_t)u), b0, rd, gb, shi, ok);
       if (!ok) break;
-      for (int c = sw_next_child(par_l, a.N, u, u, shmin); c < a.N; c = sw_next_child(par_l, a.N, u, c, shmin))
+      const int par = st.k & 1;
+      if (tid == 0) sw_put(st, g, 0, (double)x);
+      ok = sw_gather(a, st, 1, gb);
+      if (!ok) break;
+      cdf_x = 0;
+      for (int gg = 0; gg < G; ++gg) cdf_x = max(cdf_x, (int)gb[par][gg][0]);
+      for (int c = sw_next_child(par_l, a.N, u, u); c < a.N; c = sw_next_child(par_l, a.N, u, c))
         if (a.tokens[c] == cdf_x) {
           accepted = c;
           break;
         }
     }
-    // ---- the children of u, in index order
-    for (int c = cdf ? a.N : sw_next_child(par_l, a.N, u, u, shmin); c < a.N;
-         c = sw_next_child(par_l, a.N, u, c, shmin)) {
+    // ---- the children of u, in index order (rv, qv: this thread's residual
+    // and draft entries; r, q in LDS for the owner of a child's token)
+    for (int c = cdf ? a.N : sw_next_child(par_l, a.N, u, u); c < a.N; c = sw_next_child(par_l, a.N, u, c)) {
       const int x = a.tokens[c];
       const int owner = x / SW_SLICE, xl = x - owner * SW_SLICE;
       // this slice's residual as it would be after rejecting x
-      double zl = 0.0, zql = 0.0;
+      double zl = 0.0, zql = 0.0, tv[SW_PER];
 #pragma unroll
       for (int i = 0; i < SW_PER; ++i) {
-        const int l = tid * SW_PER + i, v = b0 + i;
-        double t;
-        if (det) t = v == x ? 0.0 : r[l];
-        else {
-          const double dd = r[l] / Z - q[l] / Zq;
-          t = dd > 0.0 ? dd : 0.0;
+        const int v = b0 + i;
+        if (det) {
+          tv[i] = v == x ? 0.0 : rv[i];
+        } else {
+          const double dd = rv[i] / Z - qv[i] / Zq;
+          tv[i] = dd > 0.0 ? dd : 0.0;
         }
-        zl += t;
-        zql += v == x ? 0.0 : q[l];
+        zl += tv[i];
+        zql += v == x ? 0.0 : qv[i];
       }
-      sw_sum2(zl, zql, red);
+      sw_sum2(zl, zql, rd);
       const int par = st.k & 1;
       if (tid == 0) {
         double acc = 0.0;
@@ -2984,36 +3021,27 @@ __global__ __launch_bounds__(SW_THREADS) void sample_accept_kernel(SwArgs a) {
           }
           acc = yes ? 1.0 : 0.0;
         }
-        double* rc = sw_rec(st, par, g);
-        sw_st(st, rc, zl);
-        sw_st(st, rc + 1, zql);
-        sw_st(st, rc + 2, acc);
+        sw_put(st, g, 0, zl);
+        sw_put(st, g, 1, zql);
+        sw_put(st, g, 2, acc);
       }
-      ok = sw_round(a, st, g, shi + 1);
+      ok = sw_gather(a, st, 3, gb);
       if (!ok) break;
-      sw_gather(st, par, G, gb);
       double zs = 0.0, zqs = 0.0;
       for (int gg = 0; gg < G; ++gg) {
-        zs += gb[gg][0];
-        zqs += gb[gg][1];
+        zs += gb[par][gg][0];
+        zqs += gb[par][gg][1];
       }
-      const bool yes = gb[owner][2] != 0.0;
-      __syncthreads();  // (gb is rewritten by the next round's gather)
-      if (yes) {
+      if (gb[par][owner][2] != 0.0) {
         accepted = c;
         break;
       }
       // rejected: apply the residual every workgroup summed
 #pragma unroll
       for (int i = 0; i < SW_PER; ++i) {
-        const int l = tid * SW_PER + i, v = b0 + i;
-        if (det) {
-          if (v == x) r[l] = 0.0;
-        } else {
-          const double dd = r[l] / Z - q[l] / Zq;
-          r[l] = dd > 0.0 ? dd : 0.0;
-          if (wor && v == x) q[l] = 0.0;
-        }
+        rv[i] = tv[i];
+        r[tid * SW_PER + i] = tv[i];
+        if (wor && b0 + i == x) q[tid * SW_PER + i] = qv[i] = 0.0;
       }
       Z = zs;
       if (wor) Zq = zqs;
@@ -3033,71 +3061,12 @@ __global__ __launch_bounds__(SW_THREADS) void sample_accept_kernel(SwArgs a) {
     }
   } else if (ok) {
     // ---- extra token: the smallest v whose running sum of w exceeds U2 * Z
-    // (w = r, or p when rounding left no residual mass), summed per thread in
-    // index order, per slice over threads in order, then over slices in order
+    // (w = r, or p when rounding left no residual mass)
     const double U2 = philox_uniform(a.seed, 1, (uint64_t)u);
     const bool use_r = Z > 0.0;
-    const double* w = use_r ? r : p;
-    const double target = U2 * (use_r ? Z : 1.0);
-    double c1 = 0.0;
-    int lastpos = -1;
-#pragma unroll
-    for (int i = 0; i < SW_PER; ++i) {
-      const double wv = w[tid * SW_PER + i];
-      c1 += wv;
-      if (wv > 0.0) lastpos = b0 + i;
-    }
-    cs[tid] = c1;
-    const int lp = (int)sw_max((double)lastpos, red);
-    const int par = st.k & 1;
-    if (tid == 0) {
-      double Wg = 0.0;
-      for (int t = 0; t < SW_THREADS; ++t) Wg += cs[t];
-      double* rc = sw_rec(st, par, g);
-      sw_st(st, rc, Wg);
-      sw_st(st, rc + 1, (double)lp);
-    }
-    ok = sw_round(a, st, g, shi + 1);
-    if (ok) sw_gather(st, par, G, gb);
+    const int x = sw_pick(a, st, g, G, use_r ? r : p, U2 * (use_r ? Z : 1.0), b0, rd, gb, shi, ok);
     if (ok && tid == 0) {
-      // the slice where the running sum crosses the target
-      double run = 0.0;
-      int gx = -1;
-      for (int gg = 0; gg < G; ++gg) {
-        if (run + gb[gg][0] > target) {
-          gx = gg;
-          break;
-        }
-        run += gb[gg][0];
-      }
-      int choice = -1;
-      if (gx == g) {
-        // in it, the thread chunk, then the entry
-        double c2 = run;
-        for (int t = 0; t < SW_THREADS && choice < 0; ++t) {
-          if (c2 + cs[t] > target) {
-            double c3 = c2;
-            for (int i = 0; i < SW_PER; ++i) {
-              c3 += w[t * SW_PER + i];
-              if (c3 > target) {
-                choice = g * SW_SLICE + t * SW_PER + i;
-                break;
-              }
-            }
-          }
-          c2 += cs[t];
-        }
-        if (choice < 0) choice = lp >= 0 ? lp : g * SW_SLICE;  // rounding left no crossing in the slice
-      } else if (gx < 0 && g == 0) {
-        // rounding left no crossing: the last token with positive weight
-        choice = 0;
-        for (int gg = G - 1; gg >= 0; --gg)
-          if (gb[gg][1] >= 0.0) {
-            choice = (int)gb[gg][1];
-            break;
-          }
-      }
-      if (choice >= 0) *a.next = choice;
+      if (x >= 0) *a.next = x;
       if (g == 0) *a.path_len = len;
     }
   }
@@ -3107,10 +3076,23 @@ __global__ __launch_bounds__(SW_THREADS) void sample_accept_kernel(SwArgs a) {
     if (!ok && g == 0) *a.path_len = 0;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     const unsigned prev = __hip_atomic_fetch_add(st.ctl + SWC_DONE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (prev == (unsigned)G - 1) {
+    shi[1] = prev == (unsigned)G - 1;
+  }
+  __syncthreads();
+  if (shi[1]) {
+    if (((st.tagbase >> 16) & 0xffffu) == 0xffffu) {
+      // (the next epoch's tags start over: no word may carry an old one)
+      sw_word* wds = (sw_word*)(a.work + kSwRecOfs);
+      for (size_t i = tid; i < (kSwBytes - kSwRecOfs) / 8; i += SW_THREADS)
+        __hip_atomic_store(wds + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+    }
+    if (tid == 0) {
       __hip_atomic_store(st.ctl + SWC_DONE, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __hip_atomic_store(st.ctl + SWC_ABORT, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(st.ctl + SWC_EPOCH, (st.tagbase >> 16), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(st.ctl + SWC_EPOCH, (st.tagbase >> 16) & 0xffffu, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 }

@@ -206,7 +206,7 @@ hipError_t launch_greedy_walk(const int* tokens, const int* parents, const int* 
 // slice sums through work (sample_work_bytes(), zeroed once before the first
 // use and then owned by the sampler: one call at a time per work area); on a
 // wait that times out *path_len = 0 and err (if given) counts it
-constexpr size_t kSampleWorkBytes = (64 + 64) * 4 + (size_t)2 * 64 * 4 * 8 + (size_t)2 * 64 * 256 * 4;
+constexpr size_t kSampleWorkBytes = 64 * 4 + (size_t)2 * 64 * 8 * 8 + (size_t)2 * 64 * 128 * 8;
 constexpr int kSampleMaxVocab = 64 * 2048;  // the sampling walk's vocabulary limit
 size_t sample_work_bytes();
 hipError_t launch_sample_accept(const int* tokens, const int* parents, int N, int V, const float* logits,

@@ -1,0 +1,62 @@
+"""The sampling walk's exchange and top-k cut at the edges of their slices:
+one slice, one full, one token more, the most the exchange area holds; ties
+that straddle slices; many calls in a row on one exchange area.  Paths and
+tokens equal the oracle's, bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2308_04623_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+VMAX = 131072  # 64 slices of 2048
+
+
+@pytest.fixture(scope="module")
+def session():
+    from paper_2308_04623_amd import ssd
+    cfg = W.GPT2Config(n_layer=1, d_model=64, n_head=2, d_mlp=64, vocab=VMAX, n_pos=64, dtype="bf16")
+    return ssd.Session(ssd.Model(cfg, W.make_weights(cfg, 0)), 0, 64)
+
+
+def check(session, V, mode, k, T, seed, ties):
+    import torch
+    from paper_2308_04623_amd import ssd
+    g = np.random.default_rng([V, k, seed])
+    par = W.branching_tree([3, 2, 2, 1], 20)
+    n = len(par)
+    lg = (g.standard_normal((n, V)) * 3).astype(np.float32)
+    if ties:
+        lg = np.round(lg)
+    toks = g.integers(0, V, n).astype(np.int32)
+    top = np.argsort(-lg, axis=1, kind="stable")[:, :8]
+    for i in range(1, n):
+        toks[i] = top[par[i], i % min(8, V)]
+    q = None
+    if mode in ("SAMPLE_WOR", "SAMPLE_IID"):
+        q = g.dirichlet(np.ones(V), n).astype(np.float32)
+        for i in range(1, n):
+            q[par[i], toks[i]] += 0.2
+        q /= q.sum(1, keepdims=True)
+    want = oracle.tree_accept(getattr(oracle, mode), toks, par, lg, draft_probs=q, temperature=T, seed=seed, top_k=k)
+    path, plen, nxt = session.accept(toks, par, torch.from_numpy(lg).cuda(), mode=getattr(ssd, mode),
+                                     draft_probs=None if q is None else torch.from_numpy(q).cuda(), temperature=T,
+                                     seed=seed, top_k=k)
+    m = int(plen.item())
+    assert path[:m].cpu().numpy().tolist() == want[0].tolist() and int(nxt.item()) == want[1]
+
+
+@pytest.mark.parametrize("V", [9, 2048, 2049, 50257, VMAX])
+@pytest.mark.parametrize("mode,k,ties", [("SAMPLE_WOR", 0, False), ("SAMPLE_DET", 7, True), ("SAMPLE_DET", 300, True),
+                                         ("SAMPLE_CDF", 5, True), ("SAMPLE_IID", 40, False)])
+def test_walk_edges(session, V, mode, k, ties):
+    for seed in range(3):
+        check(session, V, mode, k, 1.0, seed, ties)
+
+
+def test_many_calls_on_one_exchange_area(session):
+    """Round tags of consecutive calls differ: no call reads another's words."""
+    for seed in range(60):
+        check(session, 4096 if seed % 3 else 9, "SAMPLE_DET", 3 if seed % 2 else 0, 0.8, seed, bool(seed % 5))
+    assert session.error_count() == 0
