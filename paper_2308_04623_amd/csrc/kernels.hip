@@ -121,6 +121,39 @@ __device__ __forceinline__ void pass_signal(unsigned long long* sig) {
     __hip_atomic_fetch_add(sig, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// XCDs that one k-split of a wide GEMM keeps to
+__host__ __device__ __forceinline__ int wide_xcds(int gy) { return 8 % gy == 0 ? 8 / gy : 8; }
+
+// Extra blocks (pf.first on) of the small kernels between the wide GEMMs read
+// a later GEMM's weights, so that it finds them in L2: a GEMM over 128 nodes
+// takes 2.0 to 2.9 us less with its weights there, and the LayerNorm and
+// attention kernels leave the memory idle.  Block first + b is on the XCD of
+// block b of the GEMM (workgroups go round the XCDs in turn from the same
+// one at every launch), whose workgroups read row-block groups x / gy, + X,
+// ... of k-split x % gy (see wide_pos).  The XCD's bytes are dealt to its
+// waves in pieces of 1 KB, copied into a scrap of LDS (1 KB per wave), so they cost no
+// registers and the wave only waits once, at its end.
+// Results do not depend on it.
+__device__ __forceinline__ void prefetch_weights(const Prefetch& pf, unsigned char* scrap) {
+  const int b = blockIdx.x - pf.first, x = b & 7, nw = blockDim.x >> 6;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int waves = (((int)gridDim.x - pf.first) >> 3) * nw, w = (b >> 3) * nw + wv;
+  const int X = wide_xcds(pf.gy);
+  const bool own = 8 % pf.gy == 0;  // (another split count: an XCD reads every split)
+  const size_t off = own ? (size_t)(x % pf.gy) * pf.step : 0;
+  const int i0 = own ? x / pf.gy : x, run = (int)min((size_t)(own ? pf.step : pf.row_bytes), pf.row_bytes - off);
+  const int per = (run + 1023) >> 10, rows = i0 < pf.gx ? (pf.gx - i0 + X - 1) / X * pf.rbt : 0;
+  if (run < 1024) return;
+  for (int f = w; f < rows * per; f += waves) {
+    const int r = f / per, q = f - r * per, rb = (i0 + X * (r / pf.rbt)) * pf.rbt + r % pf.rbt;
+    if (rb >= pf.RBtot) break;
+    const unsigned char* src = pf.W + (size_t)rb * pf.row_bytes + off + min(q << 10, run - 1024) + 16 * lane;
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                     (__attribute__((address_space(3))) void*)(scrap + 1024 * wv), 16, 0, 0);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
 // sum over a 256-thread block, identical result in every thread, fixed order
 __device__ __forceinline__ float block_sum256(float v, float* red4) {
   v = wave_sum(v);
@@ -204,10 +237,15 @@ __global__ __launch_bounds__(256) void ln_resid_kernel(float* __restrict__ x, in
                                                        int S, size_t pstride, const T* __restrict__ bias,
                                                        const T* __restrict__ g, const T* __restrict__ b, float eps,
                                                        OUT* __restrict__ a, int lda, unsigned long long* sig,
-                                                       unsigned* err) {
+                                                       unsigned* err, int N, Prefetch pf) {
   constexpr int PS = SPL > 0 ? SPL : 1;
   __shared__ float red[4];
   pass_signal(sig);
+  if ((int)blockIdx.x >= N) {
+    __shared__ __align__(16) unsigned char scrap[4 * 1024];
+    if (pf.W && (int)blockIdx.x >= pf.first) prefetch_weights(pf, scrap);
+    return;
+  }
   const int n = blockIdx.x, tid = threadIdx.x, nc = d >> 2;
   float* xr = x + (size_t)n * d;
   const float* pr = part + (size_t)n * d;
@@ -274,33 +312,40 @@ __global__ __launch_bounds__(256) void ln_resid_kernel(float* __restrict__ x, in
   }
 }
 
+// workgroups added to a kernel to prefetch: one of 256 threads per CU
+constexpr int kPfWgs = 256;
+
 template <typename T, int E, int SPL>
 static void ln_go(float* x, int N, int d, const float* part, int S, size_t pstride, const void* bias, const void* g,
-                  const void* b, float eps, void* a, int lda, unsigned long long* sig, unsigned* err, hipStream_t s) {
-  ln_resid_kernel<T, T, E, SPL><<<N, 256, 0, s>>>(x, d, part, S, pstride, (const T*)bias, (const T*)g, (const T*)b,
-                                                  eps, (T*)a, lda, sig, err);
+                  const void* b, float eps, void* a, int lda, unsigned long long* sig, unsigned* err,
+                  const Prefetch& pf0, hipStream_t s) {
+  Prefetch pf = pf0;
+  pf.first = (N + 7) / 8 * 8;
+  const int grid = pf.W ? pf.first + kPfWgs : N;
+  ln_resid_kernel<T, T, E, SPL><<<grid, 256, 0, s>>>(x, d, part, S, pstride, (const T*)bias, (const T*)g, (const T*)b,
+                                                     eps, (T*)a, lda, sig, err, N, pf);
 }
 
 template <typename T, int E>
 static void ln_go_s(float* x, int N, int d, const float* part, int S, size_t pstride, const void* bias,
                     const void* g, const void* b, float eps, void* a, int lda, unsigned long long* sig,
-                    unsigned* err, hipStream_t s) {
-  if (S == 0) ln_go<T, E, 0>(x, N, d, part, S, pstride, bias, g, b, eps, a, lda, sig, err, s);
-  else if (S == 1) ln_go<T, E, 1>(x, N, d, part, S, pstride, bias, g, b, eps, a, lda, sig, err, s);
-  else if (S == 2) ln_go<T, E, 2>(x, N, d, part, S, pstride, bias, g, b, eps, a, lda, sig, err, s);
-  else if (S == 4) ln_go<T, E, 4>(x, N, d, part, S, pstride, bias, g, b, eps, a, lda, sig, err, s);
-  else if (S == 8) ln_go<T, E, 8>(x, N, d, part, S, pstride, bias, g, b, eps, a, lda, sig, err, s);
-  else ln_go<T, E, -1>(x, N, d, part, S, pstride, bias, g, b, eps, a, lda, sig, err, s);
+                    unsigned* err, const Prefetch& pf, hipStream_t s) {
+  if (S == 0) ln_go<T, E, 0>(x, N, d, part, S, pstride, bias, g, b, eps, a, lda, sig, err, pf, s);
+  else if (S == 1) ln_go<T, E, 1>(x, N, d, part, S, pstride, bias, g, b, eps, a, lda, sig, err, pf, s);
+  else if (S == 2) ln_go<T, E, 2>(x, N, d, part, S, pstride, bias, g, b, eps, a, lda, sig, err, pf, s);
+  else if (S == 4) ln_go<T, E, 4>(x, N, d, part, S, pstride, bias, g, b, eps, a, lda, sig, err, pf, s);
+  else if (S == 8) ln_go<T, E, 8>(x, N, d, part, S, pstride, bias, g, b, eps, a, lda, sig, err, pf, s);
+  else ln_go<T, E, -1>(x, N, d, part, S, pstride, bias, g, b, eps, a, lda, sig, err, pf, s);
 }
 
 template <typename T>
 static hipError_t ln_go_e(float* x, int N, int d, const float* part, int S, size_t pstride, const void* bias,
                           const void* g, const void* b, float eps, void* a, int lda, unsigned long long* sig,
-                          unsigned* err, hipStream_t s) {
+                          unsigned* err, const Prefetch& pf, hipStream_t s) {
   if (d % 32) return hipErrorInvalidValue;
   switch ((d + 1023) / 1024) {
-    case 1: ln_go_s<T, 1>(x, N, d, part, S, pstride, bias, g, b, eps, a, lda, sig, err, s); break;
-    case 2: ln_go_s<T, 2>(x, N, d, part, S, pstride, bias, g, b, eps, a, lda, sig, err, s); break;
+    case 1: ln_go_s<T, 1>(x, N, d, part, S, pstride, bias, g, b, eps, a, lda, sig, err, pf, s); break;
+    case 2: ln_go_s<T, 2>(x, N, d, part, S, pstride, bias, g, b, eps, a, lda, sig, err, pf, s); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -308,10 +353,10 @@ static hipError_t ln_go_e(float* x, int N, int d, const float* part, int S, size
 
 hipError_t launch_ln(int f32, float* x, int N, int d, const float* part, int S, size_t pstride, const void* bias,
                      const void* g, const void* b, float eps, void* a, int lda, unsigned long long* sig,
-                     unsigned* err, hipStream_t s) {
+                     unsigned* err, const Prefetch& pf, hipStream_t s) {
   if (S > 0 && !bias) return hipErrorInvalidValue;
-  if (f32) return ln_go_e<float>(x, N, d, part, S, pstride, bias, g, b, eps, a, lda, sig, err, s);
-  return ln_go_e<uint16_t>(x, N, d, part, S, pstride, bias, g, b, eps, a, lda, sig, err, s);
+  if (f32) return ln_go_e<float>(x, N, d, part, S, pstride, bias, g, b, eps, a, lda, sig, err, pf, s);
+  return ln_go_e<uint16_t>(x, N, d, part, S, pstride, bias, g, b, eps, a, lda, sig, err, pf, s);
 }
 
 // ------------------------------------------------------------------ GEMM epilogues
@@ -717,7 +762,6 @@ __device__ __forceinline__ void epilogue4(const Epi& e, int kind, int sk, int nn
 struct WidePos {
   int i, j, sk;
 };
-__host__ __device__ __forceinline__ int wide_xcds(int gy) { return 8 % gy == 0 ? 8 / gy : 8; }
 __device__ __forceinline__ bool wide_pos(int gx, int gt, int gy, WidePos& p) {
   const int x = blockIdx.x & 7, q = blockIdx.x >> 3, X = wide_xcds(gy);
   if (8 % gy == 0) {
@@ -1038,6 +1082,21 @@ static void gemm_go(int kind, const GemmGeom& g, const void* Wp, const uint16_t*
       if constexpr (VEC) gemm_launch<NT, RB, EPI_LOGITS, VEC, NV, U>(g, Wp, act, ep, s);
       break;
   }
+}
+
+Prefetch wide_prefetch(int kind, const void* Wp, int M, int K, int N, bool q8) {
+  const int KC = K / 32, RB = (M + 15) / 16, frag = q8 ? 512 : 1024;
+  const WideCfg c = wide_cfg(kind, RB, KC, N, q8);
+  const int kcs = (KC + c.S - 1) / c.S;
+  Prefetch pf{};
+  pf.W = (const unsigned char*)Wp;
+  pf.row_bytes = (size_t)KC * frag;
+  pf.step = kcs * frag;
+  pf.RBtot = RB;
+  pf.rbt = c.rbt;
+  pf.gx = (RB + c.rbt - 1) / c.rbt;
+  pf.gy = (KC + kcs - 1) / kcs;
+  return pf;
 }
 
 template <int RBT, int TT, int NW, int U>
@@ -1587,9 +1646,13 @@ __device__ __forceinline__ void attn_prefix_chunk(const AttnArgs& a, uint16_t* l
 }
 
 template <int DH>
-__global__ __launch_bounds__(64 * AT_MAXW) void attn_split_kernel(AttnArgs a) {
+__global__ __launch_bounds__(64 * AT_MAXW) void attn_split_kernel(AttnArgs a, Prefetch pf) {
   __shared__ __align__(16) uint16_t lds[AT_STAGE * (DH + 8) + DH * (AT_STAGE + 8)];  // K rows + V^T
   pass_signal(a.sig);
+  if (pf.W && (int)blockIdx.x >= pf.first) {
+    prefetch_weights(pf, (unsigned char*)lds);
+    return;
+  }
   // (an empty prefix launches one block, for the pass signal only)
   if ((int)blockIdx.x < a.H * a.nsplit) attn_prefix_chunk<DH>(a, lds, blockIdx.x % a.H, blockIdx.x / a.H);
 }
@@ -1754,10 +1817,15 @@ __global__ __launch_bounds__(64 * kPathWaves) void attn_path_kernel(AttnArgs a) 
 constexpr int kMergeThreads = 64;
 
 template <int DH>
-__global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnArgs a) {
+__global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnArgs a, Prefetch pf) {
   // TPP threads per (node, head), DPT = 4 consecutive dims each
   constexpr int RB = part_bytes<DH>(), DPT = 4, TPP = DH / DPT, PER = kMergeThreads / TPP, B = 16, RK = 8;
   pass_signal(a.sig);
+  if (pf.W && (int)blockIdx.x >= pf.first) {
+    __shared__ __align__(16) unsigned char scrap[1024];
+    prefetch_weights(pf, scrap);
+    return;
+  }
   const int pair = blockIdx.x * PER + threadIdx.x / TPP, d0 = DPT * (threadIdx.x % TPP);
   if (pair >= a.N * a.H) return;  // (a whole pair's threads together)
   const int n = pair / a.H, h = pair - n * a.H, ns = a.nsplit;
@@ -1860,7 +1928,7 @@ __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnArgs a) {
   st_act4_u16((uint16_t*)a.out, n, h * DH + d0, a.ldo, outv, a.err);
 }
 
-hipError_t launch_attn(int f32, int DH, const AttnArgs& a, hipStream_t s) {
+hipError_t launch_attn(int f32, int DH, const AttnArgs& a, const Prefetch (&pf0)[2], hipStream_t s) {
   if (!f32) {
     if (a.N <= 0 || a.N > a.max_nodes || (DH != 64 && DH != 32)) return hipErrorInvalidValue;
     if (a.P > 0 && (a.CL <= 0 || a.CL > AT_STAGE || a.CL % 32 || a.nsplit != (a.P + a.CL - 1) / a.CL))
@@ -1869,14 +1937,20 @@ hipError_t launch_attn(int f32, int DH, const AttnArgs& a, hipStream_t s) {
     const int blocks = a.sig ? max(1, a.H * a.nsplit) : a.H * a.nsplit;
     const int mblocks = (a.N * a.H * (DH / 4) + kMergeThreads - 1) / kMergeThreads;
     const int pblocks = a.H * ((a.N + 15) / 16) * a.npath;
+    Prefetch ps = pf0[0], pm = pf0[1];
+    if (!blocks) ps.W = nullptr;  // (no kernel of its own for a prefetch)
+    ps.first = (blocks + 7) / 8 * 8;
+    pm.first = (mblocks + 7) / 8 * 8;
+    // (one-wave blocks in the merge: as many waves as the other kernels add)
+    const int sgrid = ps.W ? ps.first + kPfWgs / 2 : blocks, mgrid = pm.W ? pm.first + 4 * kPfWgs : mblocks;
     if (DH == 64) {
-      if (blocks) attn_split_kernel<64><<<blocks, 64 * AT_MAXW, 0, s>>>(a);
+      if (sgrid) attn_split_kernel<64><<<sgrid, 64 * AT_MAXW, 0, s>>>(a, ps);
       if (pblocks) attn_path_kernel<64><<<pblocks, 64 * kPathWaves, 0, s>>>(a);
-      attn_merge_kernel<64><<<mblocks, kMergeThreads, 0, s>>>(a);
+      attn_merge_kernel<64><<<mgrid, kMergeThreads, 0, s>>>(a, pm);
     } else {
-      if (blocks) attn_split_kernel<32><<<blocks, 64 * AT_MAXW, 0, s>>>(a);
+      if (sgrid) attn_split_kernel<32><<<sgrid, 64 * AT_MAXW, 0, s>>>(a, ps);
       if (pblocks) attn_path_kernel<32><<<pblocks, 64 * kPathWaves, 0, s>>>(a);
-      attn_merge_kernel<32><<<mblocks, kMergeThreads, 0, s>>>(a);
+      attn_merge_kernel<32><<<mgrid, kMergeThreads, 0, s>>>(a, pm);
     }
     return hipGetLastError();
   }

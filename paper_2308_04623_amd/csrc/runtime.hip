@@ -856,11 +856,27 @@ static ssd_status enqueue_verify(const ssd_model* m, ssd_kv* kv, int32_t P, int3
   const int32_t* dep_h = (const int32_t*)stage_host + 2 * maxn;
   const int npath = attn_npath(*std::max_element(dep_h, dep_h + n));
 
+  // Wide passes with weight prefetch on: LayerNorm 1 brings in the QKV weights,
+  // the attention split the out-projection's, the merge the MLP
+  // down-projection's and LayerNorm 2 the up-projection's.
+  Prefetch pf_qkv{}, pf_o{}, pf_fc{}, pf_pr{};
+  const bool pf_on = kv->prefetch && !f32 && gemm_wide(gemm_vec(gp, n), n);
+  if (pf_on) {
+    pf_qkv = wide_prefetch(EPI_QKV, nullptr, 3 * d, d, n, q8);
+    pf_o = wide_prefetch(EPI_PARTIAL, nullptr, d, d, n, q8);
+    pf_fc = wide_prefetch(EPI_GELU, nullptr, M, d, n, q8);
+    pf_pr = wide_prefetch(EPI_PARTIAL, nullptr, d, M, n, q8);
+  }
+  auto prefetch = [&](Prefetch pf, const std::vector<const void*>& w, int l) {
+    if (pf_on) pf.W = (const unsigned char*)w[l];
+    return pf;
+  };
+
   int pend_S = 0;               // partials waiting to be added to x
   const void* pend_bias = nullptr;
   for (int l = l0; l < L; ++l) {
     HIP_TRY(launch_ln(f32, kv->x, n, d, kv->part, pend_S, pstride, pend_bias, m->ln1_g[l], m->ln1_b[l], c.ln_eps,
-                      kv->act_a, ld_d, sig, kv->d_err, s));
+                      kv->act_a, ld_d, sig, kv->d_err, prefetch(pf_qkv, m->p_qkv, l), s));
     Epi e{};
     e.sig = sig;
     e.bias = m->b_qkv[l];
@@ -903,7 +919,8 @@ static ssd_status enqueue_verify(const ssd_model* m, ssd_kv* kv, int32_t P, int3
     a.nsplit = attn_nsplit(P, H);
     a.sig = sig;
     a.err = kv->d_err;
-    HIP_TRY(launch_attn(f32, DH, a, s));
+    const Prefetch pfa[2] = {prefetch(pf_o, m->p_o, l), prefetch(pf_pr, m->p_pr, l)};
+    HIP_TRY(launch_attn(f32, DH, a, pfa, s));
 
     Epi eo{};
     eo.sig = sig;
@@ -918,7 +935,7 @@ static ssd_status enqueue_verify(const ssd_model* m, ssd_kv* kv, int32_t P, int3
                      kv->act_o, eo, s));
 
     HIP_TRY(launch_ln(f32, kv->x, n, d, kv->part, f32 ? 0 : s_o, pstride, m->b_o[l], m->ln2_g[l], m->ln2_b[l],
-                      c.ln_eps, kv->act_a, ld_d, sig, kv->d_err, s));
+                      c.ln_eps, kv->act_a, ld_d, sig, kv->d_err, prefetch(pf_fc, m->p_fc, l), s));
     Epi ef{};
     ef.sig = sig;
     ef.err = kv->d_err;
@@ -946,7 +963,7 @@ static ssd_status enqueue_verify(const ssd_model* m, ssd_kv* kv, int32_t P, int3
     pend_bias = m->b_pr[l];
   }
   HIP_TRY(launch_ln(f32, kv->x, n, d, kv->part, pend_S, pstride, pend_bias, m->lnf_g, m->lnf_b, c.ln_eps, kv->act_a,
-                    ld_d, nullptr, kv->d_err, s));
+                    ld_d, nullptr, kv->d_err, Prefetch{}, s));
   Epi eh{};
   eh.bias = nullptr;
   eh.N = n;

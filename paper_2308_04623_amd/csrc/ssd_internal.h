@@ -63,6 +63,16 @@ struct WideCfg {
   int rbt, tt, S;
 };
 
+// A later wide GEMM's weights, for the kernels before it to bring into the
+// L2s that will be read (see prefetch_weights in kernels.hip)
+struct Prefetch {
+  const unsigned char* W;  // packed fragments (nullptr: nothing to do)
+  size_t row_bytes;        // of one 16-row block over all k-steps
+  int step;                // bytes of a row block in one k-split
+  int RBtot, rbt, gx, gy;  // the launch: row blocks, per group, groups, k-splits
+  int first;               // the first block that prefetches (a multiple of 8)
+};
+
 // launch geometry of one bf16 GEMM: block (bx, by) owns weight row blocks
 // bx RB .. bx RB + RB - 1 (rows past RBtot read row block RBtot - 1 and are
 // never stored) and k-steps by kcs .. by kcs + kcs - 1 (clamped to KC)
@@ -160,7 +170,7 @@ hipError_t launch_embed(int f32, const void* wte, const void* wpe, const int* to
 // buffer a (lda: fp32 row stride, or bf16 k-steps d / 32; see st_act)
 hipError_t launch_ln(int f32, float* x, int N, int d, const float* part, int S, size_t pstride, const void* bias,
                      const void* g, const void* b, float eps, void* a, int lda, unsigned long long* sig,
-                     unsigned* err, hipStream_t s);
+                     unsigned* err, const Prefetch& pf, hipStream_t s);
 hipError_t launch_gemm_f32(int kind, const float* W, int M, int K, const float* act, int lda, const Epi& ep,
                            hipStream_t s);
 GemmCfg gemm_cfg(int N, int vec, int kind);
@@ -176,7 +186,10 @@ GemmGeom gemm_geom(int kind, int vec, int M, int K, int N, int kcs);
 // split (grid.y = ceil(K/32 / kcs))
 hipError_t launch_gemm_bf16(int kind, int vec, const void* Wp, int M, int K, const uint16_t* act, int kcs,
                             const Epi& ep, hipStream_t s);
-hipError_t launch_attn(int f32, int DH, const AttnArgs& a, hipStream_t s);
+// pf: what the split and the merge kernel of a bf16 model prefetch
+hipError_t launch_attn(int f32, int DH, const AttnArgs& a, const Prefetch (&pf)[2], hipStream_t s);
+// the prefetch of a wide GEMM (more than 64 nodes) of M x K packed weights
+Prefetch wide_prefetch(int kind, const void* Wp, int M, int K, int N, bool q8);
 hipError_t launch_prefetcher(const PrefetchPlan& pp, hipStream_t s);
 // bad: device counter of packed 16-byte groups holding a weight past float16's range
 hipError_t launch_pack_bf16(const uint16_t* W, int M, int K, void* out, unsigned* bad, hipStream_t s);
