@@ -1019,8 +1019,8 @@ __device__ __forceinline__ bool gemm_rb(const FusedArgs& a, const Wg& w, const W
 
 // one task of 1..4 row blocks, loads in flight per wave sized to the
 // register budget (at four tiles one row block keeps 8 steps in flight and
-// two keep 6; four row blocks keep 8 at one tile, 5 at two, 3 at four: deeper
-// would spill); three code bodies serve every stage
+// two keep 6, at three tiles 10 and 7; four row blocks keep 8 at one tile,
+// 5 at two, 4 at three, 3 at four: deeper would spill); three code bodies serve every stage
 // Runs the pre-stage (wave 0) when the workgroup has no GEMM task.
 template <bool Q8, bool RE>
 __device__ __forceinline__ bool pre_only(const FusedArgs& a, const Wg& w, const PreSpec& ps) {
@@ -1043,12 +1043,12 @@ __device__ __forceinline__ bool gemm_task(const FusedArgs& a, const Wg& w, const
                                           HeadBest& hb, bool track) {
   if (nrb <= 0) return pre_only<Q8, RE>(a, w, ps);
   if (nrb == 1)
-    return gemm_rb<NT, 1, NT <= 2 ? 10 : 8, Q8, RE>(a, w, ws, epi, l, rbs, rb_first, 1, bias, Wp, KC, M, kc0, kc1, act,
+    return gemm_rb<NT, 1, NT <= 3 ? 10 : 8, Q8, RE>(a, w, ws, epi, l, rbs, rb_first, 1, bias, Wp, KC, M, kc0, kc1, act,
                                            act_kc, red, ps, wofs, hb, track);
   if (nrb == 2)
-    return gemm_rb<NT, 2, NT <= 2 ? 10 : 6, Q8, RE>(a, w, ws, epi, l, rbs, rb_first, 2, bias, Wp, KC, M, kc0, kc1, act,
+    return gemm_rb<NT, 2, NT <= 2 ? 10 : NT == 3 ? 7 : 6, Q8, RE>(a, w, ws, epi, l, rbs, rb_first, 2, bias, Wp, KC, M, kc0, kc1, act,
                                            act_kc, red, ps, wofs, hb, track);
-  return gemm_rb<NT, 4, NT == 1 ? 8 : NT == 2 ? 5 : 3, Q8, RE>(a, w, ws, epi, l, rbs, rb_first, nrb, bias, Wp, KC, M, kc0,
+  return gemm_rb<NT, 4, NT == 1 ? 8 : NT == 2 ? 5 : NT == 3 ? 4 : 3, Q8, RE>(a, w, ws, epi, l, rbs, rb_first, nrb, bias, Wp, KC, M, kc0,
                                                             kc1, act, act_kc, red, ps, wofs, hb, track);
 }
 
@@ -1443,7 +1443,7 @@ __device__ __forceinline__ void compute_wg(const FusedArgs& a, unsigned char* ld
   // LayerNorm) when they fit.  The up-projection's closing wait covers the
   // copy; with one tile that stage is too short to hide it.
   const bool wpr_staged = NT >= 2 && n_wpr > 0 && n_wpr * (kf1 - kf0) <= WST_FRAGS;
-  const bool wpr_early = wpr_staged && NT == 4;  // (see the out-projection stage)
+  const bool wpr_early = wpr_staged && NT >= 3;  // (see the out-projection stage)
   // likewise the out-projection's weights during LN1 + QKV, above the
   // parameter table (the attention stage between uses the LDS below it)
   const int wo_ofs = A_REGION + A_PART_BYTES + A_Q_BYTES + 256 + L * kLwSlots * 8;
@@ -1769,11 +1769,13 @@ hipError_t fused_prepare() {
   const int lds = (int)fused_lds_bytes(kFMaxL);
   const void* fns[] = {
       (const void*)fz::pass_kernel<1, false, false>, (const void*)fz::pass_kernel<2, false, false>,
-      (const void*)fz::pass_kernel<4, false, false>, (const void*)fz::pass_kernel<1, true, false>,
-      (const void*)fz::pass_kernel<2, true, false>,  (const void*)fz::pass_kernel<4, true, false>,
+      (const void*)fz::pass_kernel<3, false, false>, (const void*)fz::pass_kernel<4, false, false>,
+      (const void*)fz::pass_kernel<1, true, false>,  (const void*)fz::pass_kernel<2, true, false>,
+      (const void*)fz::pass_kernel<3, true, false>,  (const void*)fz::pass_kernel<4, true, false>,
       (const void*)fz::pass_kernel<1, false, true>,  (const void*)fz::pass_kernel<2, false, true>,
-      (const void*)fz::pass_kernel<4, false, true>,  (const void*)fz::pass_kernel<1, true, true>,
-      (const void*)fz::pass_kernel<2, true, true>,   (const void*)fz::pass_kernel<4, true, true>};
+      (const void*)fz::pass_kernel<3, false, true>,  (const void*)fz::pass_kernel<4, false, true>,
+      (const void*)fz::pass_kernel<1, true, true>,   (const void*)fz::pass_kernel<2, true, true>,
+      (const void*)fz::pass_kernel<3, true, true>,   (const void*)fz::pass_kernel<4, true, true>};
   hipError_t e = hipSuccess;
   for (size_t i = 0; i < sizeof(fns) / sizeof(fns[0]) && e == hipSuccess; ++i)
     e = hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -1795,6 +1797,7 @@ static void launch_tiles(const FusedArgs& a, int nt, dim3 grid, size_t lds, hipS
   switch (nt) {
     case 1: fz::pass_kernel<1, Q8, RE><<<grid, fz::NTH, lds, s>>>(a); break;
     case 2: fz::pass_kernel<2, Q8, RE><<<grid, fz::NTH, lds, s>>>(a); break;
+    case 3: fz::pass_kernel<3, Q8, RE><<<grid, fz::NTH, lds, s>>>(a); break;
     default: fz::pass_kernel<4, Q8, RE><<<grid, fz::NTH, lds, s>>>(a); break;
   }
 }

@@ -34,9 +34,9 @@ def recent_tree(n, back=8):
 
 
 class Side:
-    def __init__(self, cfg, q8):
+    def __init__(self, cfg, q8, MAX_CTX=MAX_CTX, P=P):
         from paper_2308_04623_amd import ssd
-        self.cfg, self.ssd = cfg, ssd
+        self.cfg, self.ssd, self.ctx = cfg, ssd, MAX_CTX
         w = W.make_weights(cfg, 3, perturb_affine=True)
         self.om = oracle.Model(cfg, w, q8=q8)
         self.kc, self.vc = W.random_kv_cache(cfg, MAX_CTX, P, seed=3)
@@ -47,7 +47,7 @@ class Side:
         toks = W.tree_tokens(par, cfg.vocab, seed=n)
         kt, vt = self.om.kv(n), self.om.kv(n)
         ref = oracle.tree_verify(self.om, self.kc, self.vc, prefix, toks, par, kt, vt)
-        s = ssd.Session(self.m, MAX_CTX, n, ssd.to_device(self.kc, cfg), ssd.to_device(self.vc, cfg))
+        s = ssd.Session(self.m, self.ctx, n, ssd.to_device(self.kc, cfg), ssd.to_device(self.vc, cfg))
         lg = s.verify(prefix, toks, par).cpu().numpy()
         assert np.abs(lg - ref).max() < TOL
         for got, want in ((s.k_tree, kt), (s.v_tree, vt)):
@@ -101,6 +101,17 @@ DEEP = {"chain": W.chain_tree, "comb": comb, "chains": chains}
 @pytest.mark.parametrize("prefix", [0, P])
 def test_deep_root_paths_against_oracle(sides, name, tree, n, prefix):
     sides(name, False).check(DEEP[tree](n), prefix)
+
+
+# prefixes around the 32-row blocks and the 8 waves of the tile kernel, then on
+# both sides of the length where the prefix is shared out over more workgroups
+@pytest.mark.parametrize("prefix", [1, 31, 32, 33, 256, 257, 777, 4096, 4097, 4300])
+@pytest.mark.parametrize("name", ["dh64", "dh32"])
+def test_prefix_lengths_against_oracle(prefix, name):
+    side = Side(SHAPES[name].with_(n_pos=4500), False, MAX_CTX=4301, P=prefix)
+    side.check(recent_tree(81), prefix)
+    if prefix >= 4096:
+        side.check(comb(140), prefix)
 
 
 def test_deep_node_independent_of_its_tree(sides):
