@@ -44,6 +44,15 @@
 //    that every other wait also watches, so all workgroups leave the kernel,
 //    and the session's error counter records it.
 //
+//  * A single node (the SM instances: plain decoding) is hand-offs and little
+//    else, so every workgroup runs the LayerNorm row itself, on its own copy of
+//    the residual stream in LDS, and leaves it in LDS for its GEMM; and the
+//    out-projection's workgroups merge the attention parts of their heads
+//    themselves, instead of a tile's last unit.  That takes a store, a flag
+//    and a load out of each, for 10 KB of sums that every CU then reads
+//    (GPT-2-L over 512 rows: 1038 -> 950 us; the rows of two nodes already
+//    cost more than the hand-off, 1047 -> 1055 us, and keep it).
+//
 // Arithmetic per output is fixed by the matrix, the k-range of the XCD and
 // the workgroup-internal split, never by the node count or a node's slot, so
 // a node's logits do not depend on the rest of the tree.
@@ -145,6 +154,19 @@ __device__ __forceinline__ void st_act4(gw<uint16_t> p, int n, int k, int ld, fl
   *(gw<u32x2>)(p + f * 512 + ((n & 15) + 16 * ((k & 31) >> 3)) * 8 + (k & 7)) = (u32x2){lo, hi};
 }
 
+// the same into a one-tile fragment buffer in LDS (err may be null: every
+// workgroup stores the same rows, one counts)
+__device__ __forceinline__ void st_act4_lds(__attribute__((address_space(3))) uint16_t* p, int n, int k, float v0,
+                                            float v1, float v2, float v3, unsigned* err) {
+  if (err) f16_range(fmaxf(fmaxf(fabsf(v0), fabsf(v1)), fmaxf(fabsf(v2), fabsf(v3))) + (v0 + v1 + v2 + v3) * 0.f, err);
+  const uint32_t lo = (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)v0) |
+                      ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)v1) << 16);
+  const uint32_t hi = (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)v2) |
+                      ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)v3) << 16);
+  *(__attribute__((address_space(3))) u32x2*)(p + (k >> 5) * 512 + (n + 16 * ((k & 31) >> 3)) * 8 + (k & 7)) =
+      (u32x2){lo, hi};
+}
+
 constexpr int CP_SC1 = 16;  // cache policy of a device-coherent load (sc1)
 
 __device__ __forceinline__ float gelu_tanh(float x) {
@@ -221,6 +243,8 @@ __device__ __forceinline__ unsigned ld_flag(const unsigned* p) {
   return __hip_atomic_load((unsigned*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ bool tag_reached(unsigned v, unsigned tag) { return (int)(v - tag) >= 0; }
+
+constexpr int SM_ACT = 16 * 1024;  // SM: byte offset of the LayerNorm rows in LDS, one fragment tile (d / 32 KB)
 
 // ------------------------------------------------------------------ waits and signals
 
@@ -472,10 +496,15 @@ __device__ __forceinline__ void xs_add(const FusedArgs& a, int k, int n, int o, 
 // Wave 0 polls with nothing else in flight (a wave's loads complete in
 // order, so anything issued before would delay the poll); every load of
 // every row is issued together right after it.
-template <int C, int R, bool RE>
+// SM: the one row in every workgroup; the residual stream and the GEMM input
+// are the workgroup's own, in LDS (xl, actl); rank 0 clears the sums; last:
+// XCD 0's rank 0 leaves the residual row in memory (the final LayerNorm).
+template <int C, int R, bool RE, bool SM>
 __device__ __forceinline__ bool ln_rows_q(const FusedArgs& a, const Wg& w, const WaitSpec& ws, int n0, int mode,
                                           gptr<uint16_t> bias, int kin, unsigned zmask, gptr<uint16_t> g,
-                                          gptr<uint16_t> b, uint16_t* act) {
+                                          gptr<uint16_t> b, uint16_t* act, bool last) {
+  static_assert(!SM || R == 1, "one node");
+  constexpr int RS = kFRanks;  // distance of a workgroup's rows
   const int d = a.d, nc = d / 4, tid = opq_tid(), wv = tid >> 6;
   float* red = (float*)(w.sh + 16);  // [R][8]
   if (mode != 0 && ws.on) {
@@ -490,9 +519,12 @@ __device__ __forceinline__ bool ln_rows_q(const FusedArgs& a, const Wg& w, const
   }
   int nr[R];
 #pragma unroll
-  for (int j = 0; j < R; ++j) nr[j] = min(n0 + j * kFRanks, a.N - 1);  // (rows past N repeat the last; not stored)
+  for (int j = 0; j < R; ++j) nr[j] = min(n0 + j * RS, a.N - 1);  // (rows past N repeat the last; not stored)
   const gptr<u32x2> g4 = (gptr<u32x2>)opq(g), b4 = (gptr<u32x2>)opq(b);
   const gw<uint16_t> actg = opq(act);
+  // SM: the residual row, above the parameter table
+  lds_f32* xl = (lds_f32*)((unsigned char*)w.lwt + (size_t)a.L * kLwSlots * 8);
+  __attribute__((address_space(3))) uint16_t* actl = (__attribute__((address_space(3))) uint16_t*)(w.lds + SM_ACT);
   int cc[C];
 #pragma unroll
   for (int i = 0; i < C; ++i) cc[i] = min(tid + QW * 64 * i, nc - 1);
@@ -554,9 +586,14 @@ __device__ __forceinline__ bool ln_rows_q(const FusedArgs& a, const Wg& w, const
     for (int i = 0; i < C; ++i) cr[i] = c4[cc[i]];
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-      const gptr<f32x4> xr = (gptr<f32x4>)opq(a.xr + ((size_t)w.x * kFMaxN + nr[j]) * d);
+      if constexpr (SM) {
 #pragma unroll
-      for (int i = 0; i < C; ++i) xv[j][i] = xr[cc[i]];
+        for (int i = 0; i < C; ++i) xv[j][i] = *(const lds_f32x4*)(xl + j * d + 4 * cc[i]);
+      } else {
+        const gptr<f32x4> xr = (gptr<f32x4>)opq(a.xr + ((size_t)w.x * kFMaxN + nr[j]) * d);
+#pragma unroll
+        for (int i = 0; i < C; ++i) xv[j][i] = xr[cc[i]];
+      }
     }
     // the sum plus the bias in the same units, rounded once to float
     auto fx = [](unsigned lo, unsigned hi, float bv) {
@@ -577,10 +614,15 @@ __device__ __forceinline__ bool ln_rows_q(const FusedArgs& a, const Wg& w, const
   // columns); issued after every load above
 #pragma unroll
   for (int zb = 0; zb < 3; ++zb)
-    if (zmask >> zb & 1u)
+    if (zmask >> zb & 1u) {
+      if constexpr (SM) {
+        if (w.r == 0) xs_zero(a, w, zb, 0);
+      } else {
 #pragma unroll
-      for (int j = 0; j < R; ++j)
-        if (n0 + j * kFRanks < a.N) xs_zero(a, w, zb, n0 + j * kFRanks);
+        for (int j = 0; j < R; ++j)
+          if (n0 + j * RS < a.N) xs_zero(a, w, zb, n0 + j * RS);
+      }
+    }
   float sm[R];
 #pragma unroll
   for (int j = 0; j < R; ++j) {
@@ -589,7 +631,12 @@ __device__ __forceinline__ bool ln_rows_q(const FusedArgs& a, const Wg& w, const
 #pragma unroll
     for (int i = 0; i < C; ++i) {
       if (tid + QW * 64 * i < nc) {
-        if (n0 + j * kFRanks < a.N) xr[tid + QW * 64 * i] = v[j][i];
+        if constexpr (SM) {
+          *(lds_f32x4*)(xl + j * d + 4 * (tid + QW * 64 * i)) = v[j][i];
+          if (last && w.x == 0 && w.r == 0) xr[tid + QW * 64 * i] = v[j][i];
+        } else if (n0 + j * RS < a.N) {
+          xr[tid + QW * 64 * i] = v[j][i];
+        }
         sj += ((v[j][i][0] + v[j][i][1]) + (v[j][i][2] + v[j][i][3]));
       }
     }
@@ -615,7 +662,7 @@ __device__ __forceinline__ bool ln_rows_q(const FusedArgs& a, const Wg& w, const
   q_barrier(w);
 #pragma unroll
   for (int j = 0; j < R; ++j) {
-    if (n0 + j * kFRanks >= a.N) break;
+    if (n0 + j * RS >= a.N) break;
     const float rden =
         1.0f / sqrtf(((red[8 * j + 4] + red[8 * j + 5]) + (red[8 * j + 6] + red[8 * j + 7])) / d + a.eps);
 #pragma unroll
@@ -624,7 +671,8 @@ __device__ __forceinline__ bool ln_rows_q(const FusedArgs& a, const Wg& w, const
       if (c < nc) {
         const f32x4 gv = bf4(gr[i]), bv = bf4(br[i]);
         const f32x4 y = (v[j][i] - mean[j]) * rden * gv + bv;
-        st_act4(actg, nr[j], 4 * c, d / 32, y[0], y[1], y[2], y[3], a.err);
+        if constexpr (SM) st_act4_lds(actl, nr[j], 4 * c, y[0], y[1], y[2], y[3], w.x == 0 && w.r == 0 ? a.err : nullptr);
+        else st_act4(actg, nr[j], 4 * c, d / 32, y[0], y[1], y[2], y[3], a.err);
       }
     }
   }
@@ -709,7 +757,7 @@ __device__ __forceinline__ void unit_done(const FusedArgs& a, const Wg& w, int l
 // What waves 0..3 do before a weight GEMM while the other waves' weight loads
 // are in flight: a LayerNorm stage's rows; then they publish that stage.
 struct PreSpec {
-  int kind;  // 0 nothing, 1 LayerNorm rows
+  int kind;  // 0 nothing, 1 LayerNorm rows, 2 (SM) merge of the XCD's heads
   int l, fid;
   WaitSpec ws;
   int mode;
@@ -778,21 +826,82 @@ __device__ __forceinline__ void stage_frags(gptr<u32x4> W, const int* rbs, int n
   }
 }
 
+// SM, run by waves 0..3: once every attention unit of the XCD has published
+// its part, the parts of the XCD's heads are merged (32 threads per head, two
+// dims each, the arithmetic of merge_tile) into the out-projection's input in
+// this workgroup's LDS.
+__device__ __forceinline__ bool merge_own_heads(const FusedArgs& a, const Wg& w, const WaitSpec& ws) {
+  const int tid = opq_tid(), wv = tid >> 6, S = a.att_units, h0 = a.xh[2 * w.x], nh = a.xh[2 * w.x + 1] - h0;
+  if (wv == 0) {
+    const bool ok = poll_w0(a, w, ws.id, ws.wx, ws.tag);
+    if (tid == 0) w.sh[5] = ok;
+  }
+  q_barrier(w);
+  if (w.sh[5] == 0) return false;
+  if (wv > 0) asm volatile("buffer_inv sc0" ::: "memory");
+  for (int i = tid; i < 32 * nh; i += QW * 64) {
+    const int h = h0 + (i >> 5), d0 = 2 * (i & 31);
+    float M = -INFINITY, Ls = 0.f, O0 = 0.f, O1 = 0.f;
+    constexpr int MJ = 4;  // parts loaded per round trip
+    for (int j0 = 0; j0 <= S; j0 += MJ) {
+      f32x2_t ml[MJ], ov[MJ];
+#pragma unroll
+      for (int jj = 0; jj < MJ; ++jj) {
+        const gptr<float> rec = (gptr<float>)part_rec(a, h, 0, min(j0 + jj, S), 0);
+        ml[jj] = ld_x((gptr<f32x2_t>)rec);
+        ov[jj] = ld_x((gptr<f32x2_t>)(rec + 4 + d0));
+      }
+#pragma unroll
+      for (int jj = 0; jj < MJ; ++jj) {
+        if (j0 + jj > S) break;
+        const float mj = ml[jj][0], lj = ml[jj][1];
+        if (mj == -INFINITY) continue;
+        const float mn = fmaxf(M, mj);
+        const float al = __expf(M - mn), wj = __expf(mj - mn);
+        Ls = fmaf(Ls, al, lj * wj);
+        O0 = fmaf(O0, al, ov[jj][0] * wj);
+        O1 = fmaf(O1, al, ov[jj][1] * wj);
+        M = mn;
+      }
+    }
+    O0 /= Ls;
+    O1 /= Ls;
+    if (w.r == 0) f16_range(fmaxf(fabsf(O0), fabsf(O1)) + (O0 + O1) * 0.f, a.err);
+    const int k = h * DH + d0;
+    ((__attribute__((address_space(3))) uint32_t*)(w.lds + SM_ACT))[((k >> 5) * 512 + 128 * ((k & 31) >> 3) + (k & 7)) >> 1] =
+        (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)O0) |
+        ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)O1) << 16);
+  }
+  return true;
+}
+
 // Run by waves 0..3 together: the LayerNorm rows, then the stage is
 // published (the four waves' stores complete, then wave 0 writes the flag).
-template <bool Q8, bool RE>
+template <bool Q8, bool RE, bool SM>
 __device__ __forceinline__ bool do_pre(const FusedArgs& a, const Wg& w, const PreSpec& ps) {
   if (ps.kind == 0) return true;
   bool ok = true;
-  if (ps.kind == 1 && w.r < a.N) {
+  if constexpr (SM) {
+    if (ps.kind == 2) return merge_own_heads(a, w, ps.ws);
+    const bool last = ps.l == a.L;
+    ok = a.d <= 1024
+             ? ln_rows_q<1, 1, RE, SM>(a, w, ps.ws, 0, ps.mode, ps.bias, ps.kin, ps.zmask, ps.g, ps.b, ps.act, last)
+             : ln_rows_q<2, 1, RE, SM>(a, w, ps.ws, 0, ps.mode, ps.bias, ps.kin, ps.zmask, ps.g, ps.b, ps.act, last);
+    // (the row stays in this workgroup's LDS: nothing to publish but the first
+    // layer's clearing of the sums)
+    if (!ok || ps.mode != 0) {
+      stamp(a, w, ps.l, ps.fid, 2);
+      return ok;
+    }
+  } else if (ps.kind == 1 && w.r < a.N) {
     // this rank's rows: w.r and (at more than 32 nodes) w.r + 32, together
     const bool two = w.r + kFRanks < a.N;
     if (a.d <= 1024)
-      ok = two ? ln_rows_q<1, 2, RE>(a, w, ps.ws, w.r, ps.mode, ps.bias, ps.kin, ps.zmask, ps.g, ps.b, ps.act)
-               : ln_rows_q<1, 1, RE>(a, w, ps.ws, w.r, ps.mode, ps.bias, ps.kin, ps.zmask, ps.g, ps.b, ps.act);
+      ok = two ? ln_rows_q<1, 2, RE, SM>(a, w, ps.ws, w.r, ps.mode, ps.bias, ps.kin, ps.zmask, ps.g, ps.b, ps.act, false)
+               : ln_rows_q<1, 1, RE, SM>(a, w, ps.ws, w.r, ps.mode, ps.bias, ps.kin, ps.zmask, ps.g, ps.b, ps.act, false);
     else
-      ok = two ? ln_rows_q<2, 2, RE>(a, w, ps.ws, w.r, ps.mode, ps.bias, ps.kin, ps.zmask, ps.g, ps.b, ps.act)
-               : ln_rows_q<2, 1, RE>(a, w, ps.ws, w.r, ps.mode, ps.bias, ps.kin, ps.zmask, ps.g, ps.b, ps.act);
+      ok = two ? ln_rows_q<2, 2, RE, SM>(a, w, ps.ws, w.r, ps.mode, ps.bias, ps.kin, ps.zmask, ps.g, ps.b, ps.act, false)
+               : ln_rows_q<2, 1, RE, SM>(a, w, ps.ws, w.r, ps.mode, ps.bias, ps.kin, ps.zmask, ps.g, ps.b, ps.act, false);
   }
   if (!ok) return false;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -859,7 +968,7 @@ struct HeadBest {
 // last one and are not stored.  Q8: the matrix is in 8-bit fragments (512 B,
 // widened to float16 in registers) followed by its rows' float32 scales
 // ([ceil(M / 16) 16]); each output is scaled by its row's before the bias.
-template <int NT, int RB, int U, bool Q8, bool RE>
+template <int NT, int RB, int U, bool Q8, bool RE, bool SM>
 __device__ __forceinline__ bool gemm_rb(const FusedArgs& a, const Wg& w, const WaitSpec& ws, int epi, int l,
                                         const int* rbs, int rb_first, int nrb, gptr<uint16_t> bias, gptr<u32x4> Wp,
                                         int KC, int M, int kc0, int kc1, const uint16_t* act, int act_kc,
@@ -919,7 +1028,10 @@ __device__ __forceinline__ bool gemm_rb(const FusedArgs& a, const Wg& w, const W
   auto load_a = [&](int s, int u) {
     const int kc = min(kc0 + cw + NCW * s, klast);
 #pragma unroll
-    for (int t = 0; t < NT; ++t) bq[u][t] = ld_x(ab + ((size_t)t * act_kc + kc) * 64);
+    for (int t = 0; t < NT; ++t) {
+      if (SM && !act) bq[u][t] = *((const __attribute__((address_space(3))) u32x4*)(w.lds + SM_ACT) + kc * 64 + lane);
+      else bq[u][t] = ld_x(ab + ((size_t)t * act_kc + kc) * 64);
+    }
   };
   auto load_step = [&](int s, int u) {
     load_w(s, u);
@@ -937,7 +1049,7 @@ __device__ __forceinline__ bool gemm_rb(const FusedArgs& a, const Wg& w, const W
   // (the loads sit in the branch wave 0 does not take, so the weight
   // registers are not live across the pre-stage's code)
   if (wv < QW) {
-    bool ok = do_pre<Q8, RE>(a, w, ps);
+    bool ok = do_pre<Q8, RE, SM>(a, w, ps);
     if (wv == 0) {
       stamp(a, w, ws.sl, ws.sfid, 0);
       if (ok && ws.on) ok = poll_w0(a, w, ws.id, ws.wx, ws.tag);
@@ -1022,11 +1134,11 @@ __device__ __forceinline__ bool gemm_rb(const FusedArgs& a, const Wg& w, const W
 // two keep 6, at three tiles 10 and 7; four row blocks keep 8 at one tile,
 // 5 at two, 4 at three, 3 at four: deeper would spill); three code bodies serve every stage
 // Runs the pre-stage (wave 0) when the workgroup has no GEMM task.
-template <bool Q8, bool RE>
+template <bool Q8, bool RE, bool SM>
 __device__ __forceinline__ bool pre_only(const FusedArgs& a, const Wg& w, const PreSpec& ps) {
   if (ps.kind == 0) return true;
   if (threadIdx.x < QW * 64) {
-    const bool ok = do_pre<Q8, RE>(a, w, ps);
+    const bool ok = do_pre<Q8, RE, SM>(a, w, ps);
     if (threadIdx.x == 0) w.sh[0] = ok;
   }
   lds_barrier();
@@ -1035,20 +1147,20 @@ __device__ __forceinline__ bool pre_only(const FusedArgs& a, const Wg& w, const 
   return ok;
 }
 
-template <int NT, bool Q8, bool RE>
+template <int NT, bool Q8, bool RE, bool SM>
 __device__ __forceinline__ bool gemm_task(const FusedArgs& a, const Wg& w, const WaitSpec& ws, int epi, int l,
                                           const int* rbs, int rb_first, int nrb, gptr<uint16_t> bias,
                                           gptr<u32x4> Wp, int KC, int M, int kc0, int kc1, const uint16_t* act,
                                           int act_kc, float* red, const PreSpec& ps, int wofs,
                                           HeadBest& hb, bool track) {
-  if (nrb <= 0) return pre_only<Q8, RE>(a, w, ps);
+  if (nrb <= 0) return pre_only<Q8, RE, SM>(a, w, ps);
   if (nrb == 1)
-    return gemm_rb<NT, 1, NT <= 3 ? 10 : 8, Q8, RE>(a, w, ws, epi, l, rbs, rb_first, 1, bias, Wp, KC, M, kc0, kc1, act,
+    return gemm_rb<NT, 1, NT <= 3 ? 10 : 8, Q8, RE, SM>(a, w, ws, epi, l, rbs, rb_first, 1, bias, Wp, KC, M, kc0, kc1, act,
                                            act_kc, red, ps, wofs, hb, track);
   if (nrb == 2)
-    return gemm_rb<NT, 2, NT <= 2 ? 10 : NT == 3 ? 7 : 6, Q8, RE>(a, w, ws, epi, l, rbs, rb_first, 2, bias, Wp, KC, M, kc0, kc1, act,
+    return gemm_rb<NT, 2, NT <= 2 ? 10 : NT == 3 ? 7 : 6, Q8, RE, SM>(a, w, ws, epi, l, rbs, rb_first, 2, bias, Wp, KC, M, kc0, kc1, act,
                                            act_kc, red, ps, wofs, hb, track);
-  return gemm_rb<NT, 4, NT == 1 ? 8 : NT == 2 ? 5 : NT == 3 ? 4 : 3, Q8, RE>(a, w, ws, epi, l, rbs, rb_first, nrb, bias, Wp, KC, M, kc0,
+  return gemm_rb<NT, 4, NT == 1 ? 8 : NT == 2 ? 5 : NT == 3 ? 4 : 3, Q8, RE, SM>(a, w, ws, epi, l, rbs, rb_first, nrb, bias, Wp, KC, M, kc0,
                                                             kc1, act, act_kc, red, ps, wofs, hb, track);
 }
 
@@ -1363,7 +1475,7 @@ __device__ __forceinline__ bool att_root_unit(const FusedArgs& a, const Wg& w, c
 
 // ------------------------------------------------------------------ compute workgroups
 
-template <int NT, bool Q8, bool RE>
+template <int NT, bool Q8, bool RE, bool SM>
 __device__ __forceinline__ void compute_wg(const FusedArgs& a, unsigned char* lds) {
   int* sh = (int*)(lds + A_REGION + A_PART_BYTES + A_Q_BYTES);  // 32 words
   int* lplan = sh + 32;                                            // [kPlanStride]
@@ -1489,7 +1601,7 @@ __device__ __forceinline__ void compute_wg(const FusedArgs& a, unsigned char* ld
         const bool ok = part < S ? att_prefix_unit(a, w, wsu, l, h, t, part, lds)
                                  : att_root_unit(a, w, wsu, l, h, t, lds);
         if (!ok) goto out;
-        unit_done(a, w, l, h, t, part);
+        if constexpr (!SM) unit_done(a, w, l, h, t, part);
       }
       signal(a, w, l, FS_ATT, false);
       stamp(a, w, l, FS_ATT, 2);
@@ -1504,10 +1616,19 @@ __device__ __forceinline__ void compute_wg(const FusedArgs& a, unsigned char* ld
       stamp(a, w, l, fid, 0);
       const WaitSpec ws{wo ? FS_ATT : FS_FC, w.x, tag_of(w, l, wo ? FS_ATT : FS_FC), true, l, fid};
       PreSpec nopre{};
-      const bool ok = wo ? gemm_task<NT, Q8, RE>(a, w, ws, FE_WO, l, p + PL_WO + 1, 0, n_wo, G<uint16_t>(nullptr),
-                                         G<u32x4>(lw(w, l, LW_O)), KCd, d, kh0, kh1, a.fo, KCd, red, nopre,
+      if constexpr (SM) {
+        // (the parts of the XCD's heads are merged here, by waves 0..3, which
+        // do the waiting)
+        nopre.kind = wo ? 2 : 0;
+        nopre.l = l;
+        nopre.fid = fid;
+        nopre.ws = ws;
+      }
+      const WaitSpec wsm{ws.id, ws.wx, ws.tag, false, ws.sl, ws.sfid};
+      const bool ok = wo ? gemm_task<NT, Q8, RE, SM>(a, w, SM ? wsm : ws, FE_WO, l, p + PL_WO + 1, 0, n_wo, G<uint16_t>(nullptr),
+                                         G<u32x4>(lw(w, l, LW_O)), KCd, d, kh0, kh1, SM ? nullptr : a.fo, KCd, red, nopre,
                                          wo_staged ? wo_ofs : 0, hbest, false)
-                         : gemm_task<NT, Q8, RE>(a, w, ws, FE_WPR, l, p + PL_WPR + 1, 0, n_wpr, G<uint16_t>(nullptr),
+                         : gemm_task<NT, Q8, RE, SM>(a, w, ws, FE_WPR, l, p + PL_WPR + 1, 0, n_wpr, G<uint16_t>(nullptr),
                                          G<u32x4>(lw(w, l, LW_PR)), KCm, d, kf0, kf1, a.ff, KCm, red, nopre,
                                          wpr_staged ? WST : 0, hbest, false);
       if (!ok) goto out;
@@ -1575,6 +1696,7 @@ __device__ __forceinline__ void compute_wg(const FusedArgs& a, unsigned char* ld
     gptr<uint16_t> bias = G<uint16_t>(nullptr);
     gptr<u32x4> Wm;
     const uint16_t* act = act1;
+    // (SM: the rows are in LDS)
     switch (kind) {
       case 0: gfid = FS_QKV; epi = FE_QKV; nrb = n_qkv; rbs = p + PL_QKV + 1; Wm = G<u32x4>(lw(w, l, LW_QKV));
               Mo = 3 * d; bias = G<uint16_t>(lw(w, l, LB_QKV)); break;
@@ -1586,8 +1708,10 @@ __device__ __forceinline__ void compute_wg(const FusedArgs& a, unsigned char* ld
     {
       // (the first QKV stage waits for every XCD's first LayerNorm, which
       // clears the first two sum buffers: see xs_zero)
-      const WaitSpec gws{ps.fid, (kind == 0 && l == L0) ? -1 : w.x, tag_of(w, l, ps.fid), true, l, gfid};
-      if (!gemm_task<NT, Q8, RE>(a, w, gws, epi, l, rbs, rb_first, nrb, bias, Wm, KCd, Mo, k0, k1, act, KCd, red, ps, 0,
+      if constexpr (SM) act = nullptr;
+      const WaitSpec gws{ps.fid, (kind == 0 && l == L0) ? -1 : w.x, tag_of(w, l, ps.fid),
+                         !SM || (kind == 0 && l == L0), l, gfid};
+      if (!gemm_task<NT, Q8, RE, SM>(a, w, gws, epi, l, rbs, rb_first, nrb, bias, Wm, KCd, Mo, k0, k1, act, KCd, red, ps, 0,
                          hbest, kind == 8))
         goto out;
     }
@@ -1596,8 +1720,8 @@ __device__ __forceinline__ void compute_wg(const FusedArgs& a, unsigned char* ld
       const WaitSpec none{0, 0, 0u, false, l, gfid};
       PreSpec nopre{};
       for (int b0 = hb0 + 4, j = 1; b0 < hb1; b0 += 4, ++j) {
-        if (!gemm_task<NT, Q8, RE>(a, w, none, FE_HEAD, L, nullptr, b0, min(4, hb1 - b0), G<uint16_t>(nullptr),
-                           G<u32x4>(a.p_head), KCd, a.V, 0, KCd, act1, KCd, red, nopre, 0, hbest, true))
+        if (!gemm_task<NT, Q8, RE, SM>(a, w, none, FE_HEAD, L, nullptr, b0, min(4, hb1 - b0), G<uint16_t>(nullptr),
+                           G<u32x4>(a.p_head), KCd, a.V, 0, KCd, SM ? nullptr : act1, KCd, red, nopre, 0, hbest, true))
           goto out;
       }
       // this workgroup's maximum per node: the 16 slots of a node sit in 16
@@ -1637,11 +1761,13 @@ out:
 }
 
 
-// RE: the pass starts at layer a.l0 from the residual stream a.x_in
-template <int NT, bool Q8, bool RE>
+// RE: the pass starts at layer a.l0 from the residual stream a.x_in; SM: at
+// most kFSmallN nodes
+template <int NT, bool Q8, bool RE, bool SM>
 __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void pass_kernel(FusedArgs a) {
+  static_assert(!SM || NT == 1, "small trees are one tile");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  compute_wg<NT, Q8, RE>(a, lds);
+  compute_wg<NT, Q8, RE, SM>(a, lds);
 }
 
 }  // namespace fz
@@ -1767,15 +1893,12 @@ bool fused_plan(int H, int d, int M, int V, int ntiles, int* tab, int* xh, int* 
 
 hipError_t fused_prepare() {
   const int lds = (int)fused_lds_bytes(kFMaxL);
-  const void* fns[] = {
-      (const void*)fz::pass_kernel<1, false, false>, (const void*)fz::pass_kernel<2, false, false>,
-      (const void*)fz::pass_kernel<3, false, false>, (const void*)fz::pass_kernel<4, false, false>,
-      (const void*)fz::pass_kernel<1, true, false>,  (const void*)fz::pass_kernel<2, true, false>,
-      (const void*)fz::pass_kernel<3, true, false>,  (const void*)fz::pass_kernel<4, true, false>,
-      (const void*)fz::pass_kernel<1, false, true>,  (const void*)fz::pass_kernel<2, false, true>,
-      (const void*)fz::pass_kernel<3, false, true>,  (const void*)fz::pass_kernel<4, false, true>,
-      (const void*)fz::pass_kernel<1, true, true>,   (const void*)fz::pass_kernel<2, true, true>,
-      (const void*)fz::pass_kernel<3, true, true>,   (const void*)fz::pass_kernel<4, true, true>};
+#define SSD_PASS(Q8, RE)                                                                             \
+  (const void*)fz::pass_kernel<1, Q8, RE, true>, (const void*)fz::pass_kernel<1, Q8, RE, false>,     \
+      (const void*)fz::pass_kernel<2, Q8, RE, false>, (const void*)fz::pass_kernel<3, Q8, RE, false>, \
+      (const void*)fz::pass_kernel<4, Q8, RE, false>
+  const void* fns[] = {SSD_PASS(false, false), SSD_PASS(true, false), SSD_PASS(false, true), SSD_PASS(true, true)};
+#undef SSD_PASS
   hipError_t e = hipSuccess;
   for (size_t i = 0; i < sizeof(fns) / sizeof(fns[0]) && e == hipSuccess; ++i)
     e = hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -1788,17 +1911,26 @@ size_t fused_lds_bytes(int L) {
   return fz::A_REGION + fz::A_PART_BYTES + fz::A_Q_BYTES + 128 + kPlanStride * 4 + (size_t)L * kLwSlots * 8 +
          fz::WO_FRAGS * 1024;
 }
+static_assert(kFSmallN * 2048 * 4 <= fz::WO_FRAGS * 1024,
+              "a single node keeps its residual row (d <= 2048) where other trees stage the out-projection");
+static_assert(kFSmallN == 1, "the SM instances run one node");
+static_assert(fz::SM_ACT >= (fz::NWV - fz::QW) * 16 * 16 * 4 && fz::SM_ACT + 2048 / 32 * 1024 <= fz::A_REGION + fz::A_PART_BYTES,
+              "its LayerNorm row must lie between the GEMM reduction and the end of the attention's LDS");
 static_assert(fz::A_REGION + fz::A_PART_BYTES + fz::A_Q_BYTES + 128 + kPlanStride * 4 + kFMaxL * kLwSlots * 8 +
                       fz::WO_FRAGS * 1024 <= 160 * 1024,
               "the persistent pass's LDS must fit a gfx950 workgroup (160 KB)");
 
 template <bool Q8, bool RE>
 static void launch_tiles(const FusedArgs& a, int nt, dim3 grid, size_t lds, hipStream_t s) {
+  if (a.N <= kFSmallN) {
+    fz::pass_kernel<1, Q8, RE, true><<<grid, fz::NTH, lds, s>>>(a);  // (a single node)
+    return;
+  }
   switch (nt) {
-    case 1: fz::pass_kernel<1, Q8, RE><<<grid, fz::NTH, lds, s>>>(a); break;
-    case 2: fz::pass_kernel<2, Q8, RE><<<grid, fz::NTH, lds, s>>>(a); break;
-    case 3: fz::pass_kernel<3, Q8, RE><<<grid, fz::NTH, lds, s>>>(a); break;
-    default: fz::pass_kernel<4, Q8, RE><<<grid, fz::NTH, lds, s>>>(a); break;
+    case 1: fz::pass_kernel<1, Q8, RE, false><<<grid, fz::NTH, lds, s>>>(a); break;
+    case 2: fz::pass_kernel<2, Q8, RE, false><<<grid, fz::NTH, lds, s>>>(a); break;
+    case 3: fz::pass_kernel<3, Q8, RE, false><<<grid, fz::NTH, lds, s>>>(a); break;
+    default: fz::pass_kernel<4, Q8, RE, false><<<grid, fz::NTH, lds, s>>>(a); break;
   }
 }
 

@@ -3203,11 +3203,11 @@ __global__ __launch_bounds__(256) void commit_kernel(U* __restrict__ kc, U* __re
     if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(err, 1u);
     return;
   }
-  const size_t total = (size_t)LH * len * units;
-  for (size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (size_t)gridDim.x * 256) {
-    const int c = (int)(idx % units);
-    const size_t row = idx / units;
-    const int t = (int)(row % len), lh = (int)(row / len);
+  // (32-bit indices: launch_commit bounds LH max_nodes units)
+  const unsigned total = (unsigned)LH * len * units;
+  for (unsigned idx = blockIdx.x * 256 + threadIdx.x; idx < total; idx += gridDim.x * 256) {
+    const unsigned row = idx / (unsigned)units;
+    const int c = (int)(idx - row * units), lh = (int)(row / (unsigned)len), t = (int)(row - (unsigned)lh * len);
     const int node = path[t];
     if (node < 0 || node >= max_nodes || P + t >= max_ctx) {
       if (c == 0 && lh == 0) atomicAdd(err, 1u);
@@ -3236,6 +3236,16 @@ hipError_t launch_commit(int f32, void* kc, void* vc, const void* kt, const void
                          int max_nodes, int DH, int P, const int* path, const int* path_len, unsigned* err,
                          hipStream_t s) {
   const int rb = DH * (f32 ? 4 : 2);
+  // (a layer group at a time where one launch's indices would pass 31 bits)
+  const int most = (int)((size_t)0x7fffffff / ((size_t)max_nodes * rb));
+  if (most < 1) return hipErrorInvalidValue;
+  if (LH > most) {
+    const size_t cb = (size_t)most * max_ctx * rb, tb = (size_t)most * max_nodes * rb;
+    const hipError_t e = launch_commit(f32, kc, vc, kt, vt, most, max_ctx, max_nodes, DH, P, path, path_len, err, s);
+    if (e != hipSuccess) return e;
+    return launch_commit(f32, (char*)kc + cb, (char*)vc + cb, (const char*)kt + tb, (const char*)vt + tb, LH - most,
+                         max_ctx, max_nodes, DH, P, path, path_len, err, s);
+  }
   const bool wide = rb % 16 == 0 && (((uintptr_t)kc | (uintptr_t)vc | (uintptr_t)kt | (uintptr_t)vt) & 15) == 0;
   if (wide) commit_go<u32x4>(kc, vc, kt, vt, LH, max_ctx, max_nodes, rb, P, path, path_len, err, s);
   else if (f32) commit_go<float>(kc, vc, kt, vt, LH, max_ctx, max_nodes, rb, P, path, path_len, err, s);
