@@ -188,6 +188,28 @@ __device__ __forceinline__ f32x4 mfma_bf16(const u32x4& a, const u32x4& b, const
                                                   0, 0);
 }
 
+// Max and sum over the four lanes l % 16 + 16 {0, 1, 2, 3}, in each of them:
+// v_permlane16_swap exchanges the odd rows of 16 lanes of its first operand
+// with the even rows of the second, v_permlane32_swap the upper half of the
+// first with the lower half of the second, so of two copies of x they leave
+// the two values a butterfly step combines (vector instructions, where a
+// shuffle goes through LDS).
+typedef unsigned swap_u2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float row4_max(float x) {
+  const unsigned u = __float_as_uint(x);
+  const swap_u2 a = __builtin_bit_cast(swap_u2, __builtin_amdgcn_permlane16_swap(u, u, false, false));
+  const unsigned v = __float_as_uint(fmaxf(__uint_as_float(a.x), __uint_as_float(a.y)));
+  const swap_u2 b = __builtin_bit_cast(swap_u2, __builtin_amdgcn_permlane32_swap(v, v, false, false));
+  return fmaxf(__uint_as_float(b.x), __uint_as_float(b.y));
+}
+__device__ __forceinline__ float row4_sum(float x) {
+  const unsigned u = __float_as_uint(x);
+  const swap_u2 a = __builtin_bit_cast(swap_u2, __builtin_amdgcn_permlane16_swap(u, u, false, false));
+  const unsigned v = __float_as_uint(__uint_as_float(a.x) + __uint_as_float(a.y));
+  const swap_u2 b = __builtin_bit_cast(swap_u2, __builtin_amdgcn_permlane32_swap(v, v, false, false));
+  return __uint_as_float(b.x) + __uint_as_float(b.y);
+}
+
 __device__ __forceinline__ void wave_sync_lds() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -1276,18 +1298,14 @@ __device__ __forceinline__ bool att_prefix_unit(const FusedArgs& a, const Wg& w,
     float mb = sv[0];
 #pragma unroll
     for (int e = 1; e < 8; ++e) mb = fmaxf(mb, sv[e]);
-    mb = fmaxf(mb, __shfl_xor(mb, 16));
-    mb = fmaxf(mb, __shfl_xor(mb, 32));
-    m = mb;
+    m = row4_max(mb);
     float pv[8], ps = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       pv[e] = __expf(sv[e] - m);
       ps += pv[e];
     }
-    ps += __shfl_xor(ps, 16);
-    ps += __shfl_xor(ps, 32);
-    lsum = ps;
+    lsum = row4_sum(ps);
     u32x4 ph, pl;
     pack_hilo8(pv, ph, pl);
 #pragma unroll

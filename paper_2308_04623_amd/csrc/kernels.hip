@@ -1501,6 +1501,7 @@ __device__ __forceinline__ void wave_sync_lds() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// (scores and maxima are in units of log 2, so that a weight is one v_exp_f32)
 // a part record of the bf16 attention: max and sum of exponentials (float32),
 // 8 bytes of padding, then the unnormalised output in float16 (it is rounded
 // to float16 again as the next GEMM's input)
@@ -1508,6 +1509,31 @@ template <int DH> constexpr int part_bytes() { return 16 + 2 * DH; }
 __device__ __forceinline__ uint32_t f16pair(float a, float b) {
   return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)a) | ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)b) << 16);
 }
+
+// Max and sum over the four lanes l % 16 + 16 {0, 1, 2, 3}, in each of them:
+// v_permlane16_swap exchanges the odd rows of 16 lanes of its first operand
+// with the even rows of the second, v_permlane32_swap the upper half of the
+// first with the lower half of the second, so of two copies of x they leave
+// the two values a butterfly step combines (vector instructions, where a
+// shuffle goes through LDS).
+typedef unsigned swap_u2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float row4_max(float x) {
+  const unsigned u = __float_as_uint(x);
+  const swap_u2 a = __builtin_bit_cast(swap_u2, __builtin_amdgcn_permlane16_swap(u, u, false, false));
+  const unsigned v = __float_as_uint(fmaxf(__uint_as_float(a.x), __uint_as_float(a.y)));
+  const swap_u2 b = __builtin_bit_cast(swap_u2, __builtin_amdgcn_permlane32_swap(v, v, false, false));
+  return fmaxf(__uint_as_float(b.x), __uint_as_float(b.y));
+}
+__device__ __forceinline__ float row4_sum(float x) {
+  const unsigned u = __float_as_uint(x);
+  const swap_u2 a = __builtin_bit_cast(swap_u2, __builtin_amdgcn_permlane16_swap(u, u, false, false));
+  const unsigned v = __float_as_uint(__uint_as_float(a.x) + __uint_as_float(a.y));
+  const swap_u2 b = __builtin_bit_cast(swap_u2, __builtin_amdgcn_permlane32_swap(v, v, false, false));
+  return __uint_as_float(b.x) + __uint_as_float(b.y);
+}
+
+// 2^x, one instruction (1 ulp; results below 2^-126 are 0)
+__device__ __forceinline__ float exp2_f(float x) { return __builtin_amdgcn_exp2f(x); }
 
 template <int DH>
 __device__ __forceinline__ void attn_prefix_chunk(const AttnArgs& a, uint16_t* lds, int h, int c) {
@@ -1576,7 +1602,7 @@ __device__ __forceinline__ void attn_prefix_chunk(const AttnArgs& a, uint16_t* l
     u32x4 qh[DH / 32], ql[DH / 32];
 #pragma unroll
     for (int kc2 = 0; kc2 < DH / 32; ++kc2) {
-      const f32x4 f0 = qf[kc2][0], f1 = qf[kc2][1];
+      const f32x4 f0 = qf[kc2][0] * a.scale2, f1 = qf[kc2][1] * a.scale2;
       const float v[8] = {f0[0], f0[1], f0[2], f0[3], f1[0], f1[1], f1[2], f1[3]};
       pack_hilo8(v, qh[kc2], ql[kc2]);
     }
@@ -1598,45 +1624,51 @@ __device__ __forceinline__ void attn_prefix_chunk(const AttnArgs& a, uint16_t* l
         s1 = mfma16(k1, ql[kc2], s1);
       }
       // lane: node 16 t + i, keys 32 sb + 8 g + e (e < 4 from s0, e >= 4 from s1)
-      float sv[8];
+      // (scores come in units of log 2: the scale and log2 e are in q)
+      float sv[8] = {s0[0], s0[1], s0[2], s0[3], s1[0], s1[1], s1[2], s1[3]};
+      if (32 * sb + 32 > nk) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int key = 32 * sb + 8 * g + r;
-        sv[r] = key < nk ? s0[r] * a.scale : -INFINITY;
-        sv[4 + r] = key + 4 < nk ? s1[r] * a.scale : -INFINITY;
+        for (int r = 0; r < 4; ++r) {
+          const int key = 32 * sb + 8 * g + r;
+          if (key >= nk) sv[r] = -INFINITY;
+          if (key + 4 >= nk) sv[4 + r] = -INFINITY;
+        }
       }
       float mb = sv[0];
 #pragma unroll
       for (int e = 1; e < 8; ++e) mb = fmaxf(mb, sv[e]);
-      mb = fmaxf(mb, __shfl_xor(mb, 16));
-      mb = fmaxf(mb, __shfl_xor(mb, 32));
-      const float mn = fmaxf(m, mb);
-      const float alpha = __expf(m - mn);
+      const float mn = fmaxf(m, row4_max(mb));
       float pv[8], ps = 0.f;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        pv[e] = __expf(sv[e] - mn);
+        pv[e] = exp2_f(sv[e] - mn);
         ps += pv[e];
       }
-      ps += __shfl_xor(ps, 16);
-      ps += __shfl_xor(ps, 32);
-      l = fmaf(l, alpha, ps);
-      m = mn;
+      // (l: this lane's keys only, added up over its node's four lanes at the end)
+      if (__any(mn != m)) {
+        // (a wave whose maxima all stay would multiply by 1)
+        const float alpha = exp2_f(m - mn);
+        l *= alpha;
+#pragma unroll
+        for (int tt = 0; tt < DH / 16; ++tt) o[tt] = o[tt] * alpha;
+        m = mn;
+      }
+      l += ps;
       u32x4 ph, pl;
       pack_hilo8(pv, ph, pl);
 #pragma unroll
       for (int tt = 0; tt < DH / 16; ++tt) {
         const u32x4 va = *(const u32x4*)(vts + (16 * tt + i) * VS + ((32 * sb + 8 * g) ^ (8 * (tt & 7))));
-        o[tt] = o[tt] * alpha;
         o[tt] = mfma16(va, ph, o[tt]);
         o[tt] = mfma16(va, pl, o[tt]);
       }
     }
     // part of node 16 t + i: lane (i, g) holds dims 16 tt + 4 g + r
     const int n = 16 * t + i;
+    const float lsum = row4_sum(l);
     if (n < a.N) {
       unsigned char* rec = (unsigned char*)a.part + (((size_t)h * ns + c) * a.N + n) * part_bytes<DH>();
-      if (g == 0) *(f32x2_t*)rec = (f32x2_t){m, l};
+      if (g == 0) *(f32x2_t*)rec = (f32x2_t){m, lsum};
 #pragma unroll
       for (int tt = 0; tt < DH / 16; ++tt)
         *(u32x2*)(rec + 16 + 2 * (16 * tt + 4 * g)) =
@@ -1693,7 +1725,7 @@ __global__ __launch_bounds__(64 * kPathWaves) void attn_path_kernel(AttnArgs a) 
 #pragma unroll
   for (int kc2 = 0; kc2 < DH / 32; ++kc2) {
     const float* qp = a.q + (size_t)nc * a.d + h * DH + 32 * kc2 + 8 * g;
-    const f32x4 f0 = *(const f32x4*)qp, f1 = *(const f32x4*)(qp + 4);
+    const f32x4 f0 = *(const f32x4*)qp * a.scale2, f1 = *(const f32x4*)(qp + 4) * a.scale2;
     const float v[8] = {f0[0], f0[1], f0[2], f0[3], f1[0], f1[1], f1[2], f1[3]};
     pack_hilo8(v, qh[kc2], ql[kc2]);
   }
@@ -1747,22 +1779,20 @@ __global__ __launch_bounds__(64 * kPathWaves) void attn_path_kernel(AttnArgs a) 
     float sv[8];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      sv[r] = s0[r] * a.scale;
-      sv[4 + r] = s1[r] * a.scale;
+      sv[r] = s0[r];
+      sv[4 + r] = s1[r];
     }
     float mb = sv[0];
 #pragma unroll
     for (int e = 1; e < 8; ++e) mb = fmaxf(mb, sv[e]);
-    mb = fmaxf(mb, __shfl_xor(mb, 16));
-    mb = fmaxf(mb, __shfl_xor(mb, 32));
+    mb = row4_max(mb);
     float pv[8], ps = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      pv[e] = __expf(sv[e] - mb);
+      pv[e] = exp2_f(sv[e] - mb);
       ps += pv[e];
     }
-    ps += __shfl_xor(ps, 16);
-    ps += __shfl_xor(ps, 32);
+    ps = row4_sum(ps);
     u32x4 ph, pl;
     pack_hilo8(pv, ph, pl);
 #pragma unroll
@@ -1795,7 +1825,7 @@ __global__ __launch_bounds__(64 * kPathWaves) void attn_path_kernel(AttnArgs a) 
   for (int j = 0; j < kPathWaves; ++j) {
     const float mj = st[j][nl][0];
     if (mj == -INFINITY) continue;  // (not a block of this node's path)
-    const float mn = fmaxf(M, mj), al = __expf(M - mn), wj = __expf(mj - mn);
+    const float mn = fmaxf(M, mj), al = exp2_f(M - mn), wj = exp2_f(mj - mn);
     L = fmaf(L, al, st[j][nl][1] * wj);
 #pragma unroll
     for (int e = 0; e < DP; ++e) O[e] = fmaf(O[e], al, st[j][nl][4 + d0 + e] * wj);
@@ -1855,7 +1885,7 @@ __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnArgs a, P
     for (int j = 0; j < B; ++j) {
       if (c0 + j >= ns) break;
       const float mn = fmaxf(M, ml[j][0]);
-      const float al = __expf(M - mn), wj = __expf(ml[j][0] - mn);
+      const float al = exp2_f(M - mn), wj = exp2_f(ml[j][0] - mn);
       L = fmaf(L, al, ml[j][1] * wj);
       const float o4[DPT] = {h2f((uint16_t)(ov[j][0] & 0xffffu)), h2f((uint16_t)(ov[j][0] >> 16)),
                              h2f((uint16_t)(ov[j][1] & 0xffffu)), h2f((uint16_t)(ov[j][1] >> 16))};
@@ -1872,7 +1902,7 @@ __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnArgs a, P
     const float* pr = prec + (size_t)c * a.N * (DH + 4);
     const f32x2_t ml = *(const f32x2_t*)pr;
     const f32x4 ov = *(const f32x4*)(pr + 4 + d0);
-    const float mn = fmaxf(M, ml[0]), al = __expf(M - mn), wj = __expf(ml[0] - mn);
+    const float mn = fmaxf(M, ml[0]), al = exp2_f(M - mn), wj = exp2_f(ml[0] - mn);
     L = fmaf(L, al, ml[1] * wj);
 #pragma unroll
     for (int e = 0; e < DPT; ++e) O[e] = fmaf(O[e], al, ov[e] * wj);
@@ -1905,14 +1935,14 @@ __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnArgs a, P
     float mb = -INFINITY;
 #pragma unroll
     for (int jj = 0; jj < RK; ++jj) {
-      s[jj] = j0 + jj <= rdep ? s[jj] * a.scale : -INFINITY;
+      s[jj] = j0 + jj <= rdep ? s[jj] * a.scale2 : -INFINITY;
       mb = fmaxf(mb, s[jj]);
     }
-    const float mn = fmaxf(M, mb), al = __expf(M - mn);
+    const float mn = fmaxf(M, mb), al = exp2_f(M - mn);
     float ps = 0.f, po[DPT] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int jj = 0; jj < RK; ++jj) {
-      const float p = __expf(s[jj] - mn);
+      const float p = exp2_f(s[jj] - mn);
       ps += p;
       const float v[DPT] = {__uint_as_float(v4[jj][0] << 16), __uint_as_float(v4[jj][0] & 0xffff0000u),
                             __uint_as_float(v4[jj][1] << 16), __uint_as_float(v4[jj][1] & 0xffff0000u)};

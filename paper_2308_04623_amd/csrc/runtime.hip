@@ -913,6 +913,7 @@ static ssd_status enqueue_verify(const ssd_model* m, ssd_kv* kv, int32_t P, int3
     a.max_ctx = kv->max_ctx;
     a.max_nodes = maxn;
     a.scale = 1.0f / std::sqrt((float)DH);
+    a.scale2 = (float)(1.4426950408889634 / std::sqrt((double)DH));
     a.ppart = kv->ppart;
     a.npath = f32 ? 0 : npath;
     a.CL = attn_chunk(P, H);

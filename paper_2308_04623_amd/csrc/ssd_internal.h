@@ -126,7 +126,7 @@ struct AttnArgs {
                         // float32, 8 bytes of padding, output float16), one per prefix chunk
   int S;                // fp32 models: prefix tiles of 64 cache rows
   int N, P, d, H, max_ctx, max_nodes;
-  float scale;
+  float scale, scale2;  // 1/sqrt(head_dim); times log2 e
   // bf16 models
   int CL;               // cache rows per prefix chunk (attn_chunk(P, H))
   int nsplit;           // prefix chunks (attn_nsplit(P, H))
