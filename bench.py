@@ -82,8 +82,9 @@ def cpu_model():
 COPY_BYTES = 256 << 20
 def fc_kernel(n):
     """The MLP up-projection + GELU GEMM's kernel at n nodes (matrix cores):
-    one-or-two-row-block tiles up to 64 nodes, the wide-tree kernel above."""
-    return "gemm2d_kernel<2, 2, 2, 4," if n > 64 else "gemm_kernel<2, 2, 2,"
+    one-or-two-row-block tiles up to 64 nodes, the wide-tree kernel above (the
+    probe launches no other GEMM)."""
+    return "gemm_wide_kernel<" if n > 64 else "gemm_kernel<2, 2, 2,"
 PASS_KERNEL = "pass_kernel"         # the persistent single-launch pass
 
 
@@ -570,7 +571,7 @@ def main():
         roofline = {"bound": "hbm", "achieved": round(B / us_pass / 1e3, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                     "frac": round(B / us_pass / 1e3 / PEAK_HBM_GBS, 4),
                     "traffic": None if args.q8 else stored_traffic(True, N),
-                    "kernel": f"ssd::fz::pass_kernel<{min((N + 15) // 16, 2) if N <= 32 else 4}> "
+                    "kernel": f"ssd::fz::pass_kernel<{(N + 15) // 16}> "
                               "(persistent single-launch verification pass)",
                     "bytes_per_launch": B, "us_per_launch": round(us_pass, 2)}
     else:

@@ -82,7 +82,7 @@ struct GemmGeom {
 
 // ---- weight prefetch from a second stream
 //
-// Every kernel of a bfloat16 pass bumps a signal counter when it starts
+// Every kernel of a bfloat16 pass of at most 64 nodes bumps a signal counter when it starts
 // (block 0): the embedding, then per layer LN1, QKV GEMM, attention split,
 // attention merge, attention-out GEMM, LN2, MLP up, MLP down.  A prefetcher
 // kernel launched on another stream beside the pass waits for these signals
