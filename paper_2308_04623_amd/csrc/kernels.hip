@@ -33,6 +33,9 @@ typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+// for callers' buffers, which promise the alignment of one element only
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned u32x2_u __attribute__((ext_vector_type(2), aligned(2)));
 
 // ------------------------------------------------------------------ helpers
 
@@ -413,7 +416,7 @@ __global__ __launch_bounds__(1024) void gemm_f32_kernel(const float* __restrict_
     // (rows past the matrix or the tree repeat the last one; not stored)
     for (int i = tid; i < 16 * u; i += 1024) {
       const int r = i / u, c = 4 * (i - r * u);
-      *(f32x4*)&wl[r][c] = *(const f32x4*)(W + (size_t)min(o0 + r, M - 1) * K + k0 + c);
+      *(f32x4*)&wl[r][c] = *(const f32x4_u*)(W + (size_t)min(o0 + r, M - 1) * K + k0 + c);
       *(f32x4*)&al[r][c] = *(const f32x4*)(act + (size_t)min(n0 + r, ep.N - 1) * lda + k0 + c);
     }
     __syncthreads();
@@ -729,7 +732,6 @@ __device__ __forceinline__ void epilogue4(const Epi& e, int kind, int sk, int nn
     return;
   }
   if (kind == EPI_LOGITS) {
-    typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
     float* p = e.logits + (size_t)nn * e.ldl + o;
     if (o + 4 <= e.M) {
       *(f32x4_u*)p = v;
@@ -741,9 +743,9 @@ __device__ __forceinline__ void epilogue4(const Epi& e, int kind, int sk, int nn
     return;
   }
   if (e.bias) {
-    float bv[4];
-    ld4((const uint16_t*)e.bias, o, bv);
-    v += (f32x4){bv[0], bv[1], bv[2], bv[3]};
+    const u32x2 b = *(const u32x2_u*)((const uint16_t*)e.bias + o);
+    v += (f32x4){__uint_as_float(b.x << 16), __uint_as_float(b.x & 0xffff0000u), __uint_as_float(b.y << 16),
+                 __uint_as_float(b.y & 0xffff0000u)};
   }
   if (kind == EPI_GELU) {
     const float g[4] = {gelu_tanh(v[0]), gelu_tanh(v[1]), gelu_tanh(v[2]), gelu_tanh(v[3])};
@@ -753,7 +755,7 @@ __device__ __forceinline__ void epilogue4(const Epi& e, int kind, int sk, int nn
   } else {
     const int oo = o < 2 * e.d ? o - e.d : o - 2 * e.d, h = oo / e.DH, j = oo - h * e.DH;
     uint16_t* dst = (uint16_t*)(o < 2 * e.d ? e.kt : e.vt);
-    *(u32x2*)(dst + ((size_t)h * e.max_nodes + nn) * e.DH + j) = (u32x2){f2bf2(v[0], v[1]), f2bf2(v[2], v[3])};
+    *(u32x2_u*)(dst + ((size_t)h * e.max_nodes + nn) * e.DH + j) = (u32x2){f2bf2(v[0], v[1]), f2bf2(v[2], v[3])};
   }
 }
 
