@@ -1780,10 +1780,12 @@ __global__ __launch_bounds__(64 * kPathWaves) void attn_path_kernel(AttnArgs a) 
 #pragma unroll
     for (int e = 1; e < 8; ++e) mb = fmaxf(mb, sv[e]);
     mb = row4_max(mb);
+    // (no score above -inf: weights of 0, or NaN where a score is)
+    const float ref = mb == -INFINITY ? 0.f : mb;
     float pv[8], ps = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      pv[e] = exp2_f(sv[e] - mb);
+      pv[e] = exp2_f(sv[e] - ref);
       ps += pv[e];
     }
     ps = row4_sum(ps);
@@ -1809,24 +1811,28 @@ __global__ __launch_bounds__(64 * kPathWaves) void attn_path_kernel(AttnArgs a) 
 #pragma unroll
   for (int tt = 0; tt < DH / 16; ++tt) *(f32x4*)&st[w][i][4 + 16 * tt + 4 * g] = o[tt];
   __syncthreads();
-  // the waves' states in wave order: 16 threads per node, DH / 16 dims each
+  // the waves' states in wave order: 16 threads per node, DH / 16 dims each.
+  // A node's blocks are told by its depth, not by their maxima: the merge reads
+  // a record for every chunk that holds a block, and a block of NaN scores has
+  // a maximum of -inf.
   constexpr int DP = DH / 16;
-  const int nl = tid >> 4, d0 = DP * (tid & 15);
+  const int nl = tid >> 4, d0 = DP * (tid & 15), nm = 16 * t + nl;
+  const int blocks = nm < a.N ? (a.depth[nm] + 1) / 32 - kPathWaves * c : 0;
   float M = -INFINITY, L = 0.f, O[DP];
 #pragma unroll
   for (int e = 0; e < DP; ++e) O[e] = 0.f;
 #pragma unroll
   for (int j = 0; j < kPathWaves; ++j) {
-    const float mj = st[j][nl][0];
-    if (mj == -INFINITY) continue;  // (not a block of this node's path)
-    const float mn = fmaxf(M, mj), al = exp2_f(M - mn), wj = exp2_f(mj - mn);
+    if (j >= blocks) break;
+    const float mj = st[j][nl][0], mn = fmaxf(M, mj), ref = mn == -INFINITY ? 0.f : mn;
+    const float al = exp2_f(M - ref), wj = exp2_f(mj - ref);
     L = fmaf(L, al, st[j][nl][1] * wj);
 #pragma unroll
     for (int e = 0; e < DP; ++e) O[e] = fmaf(O[e], al, st[j][nl][4 + d0 + e] * wj);
     M = mn;
   }
-  if (16 * t + nl < a.N && M != -INFINITY) {
-    float* rec = a.ppart + (((size_t)h * a.npath + c) * a.N + 16 * t + nl) * REC;
+  if (blocks > 0) {
+    float* rec = a.ppart + (((size_t)h * a.npath + c) * a.N + nm) * REC;
     if (d0 == 0) {
       rec[0] = M;
       rec[1] = L;
