@@ -1483,6 +1483,27 @@ __device__ __forceinline__ void pack_hilo8(const float (&v)[8], u32x4& hi, u32x4
   }
 }
 
+// v cut into three bfloat16 pieces whose sum is v exactly (each takes the
+// leading 8 of the significant bits that are left; only what lies below
+// bfloat16's smallest subnormal is lost)
+__device__ __forceinline__ void pack_exact8(const float (&v)[8], u32x4& hi, u32x4& mid, u32x4& lo) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    float a = v[2 * e], b = v[2 * e + 1];
+    uint32_t w[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b) & 0xffff0000u;
+      w[k] = (ua >> 16) | ub;
+      a -= __uint_as_float(ua & 0xffff0000u);
+      b -= __uint_as_float(ub);
+    }
+    hi[e] = w[0];
+    mid[e] = w[1];
+    lo[e] = w[2];
+  }
+}
+
 __device__ __forceinline__ f32x4 mfma16(const u32x4& a, const u32x4& b, const f32x4& c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
                                                   0, 0);
@@ -1689,8 +1710,13 @@ __global__ __launch_bounds__(64 * AT_MAXW) void attn_split_kernel(AttnArgs a, Pr
 // have the same block, so the wave serves its tile one distinct block at a
 // time (in a chain: one for all 16 nodes), keeping the others' state as it
 // is; the four waves' states are merged in wave order into a float32 record
-// (max, sum, -, -, output) per node.  The arithmetic of a node depends on its
-// own path only.  The merge walks what is left of the path, at most 31 keys.
+// (max, sum, -, -, output) per node.  Queries and softmax weights keep their
+// float32 value (three bfloat16 pieces each; K and V are bfloat16), as in the
+// merge's walk: with two pieces, 16 bits, scores that are small differences of
+// large products left the logits 6.7e-3 off, with three 2.8e-4, at no cost (a
+// 512-token chain: 3657 and 3658 us a pass).  The arithmetic of a node depends
+// on its own path only.  The merge walks what is left of the path, at most 31
+// keys.
 // A 512-token chain, per layer: the merge alone, 8 keys of one node at a time,
 // 124 us (64 dependent rounds for the last nodes); this kernel and the merge
 // 13.8 + 15.5 us.
@@ -1715,13 +1741,13 @@ __global__ __launch_bounds__(64 * kPathWaves) void attn_path_kernel(AttnArgs a) 
   const bool mine = fb > b;
   const int last = mine ? a.ancl[off + 32 * b + 31] : -1;
   unsigned pend = (unsigned)__builtin_amdgcn_ballot_w64(mine) & 0xffffu;
-  u32x4 qh[DH / 32], ql[DH / 32];
+  u32x4 qh[DH / 32], qm[DH / 32], ql[DH / 32];
 #pragma unroll
   for (int kc2 = 0; kc2 < DH / 32; ++kc2) {
     const float* qp = a.q + (size_t)nc * a.d + h * DH + 32 * kc2 + 8 * g;
     const f32x4 f0 = *(const f32x4*)qp * a.scale2, f1 = *(const f32x4*)(qp + 4) * a.scale2;
     const float v[8] = {f0[0], f0[1], f0[2], f0[3], f1[0], f1[1], f1[2], f1[3]};
-    pack_hilo8(v, qh[kc2], ql[kc2]);
+    pack_exact8(v, qh[kc2], qm[kc2], ql[kc2]);
   }
   const uint16_t* ktb = (const uint16_t*)a.kt + (size_t)h * a.max_nodes * DH;
   const uint16_t* vtb = (const uint16_t*)a.vt + (size_t)h * a.max_nodes * DH;
@@ -1765,8 +1791,10 @@ __global__ __launch_bounds__(64 * kPathWaves) void attn_path_kernel(AttnArgs a) 
 #pragma unroll
     for (int kc2 = 0; kc2 < DH / 32; ++kc2) {
       s0 = mfma16(k0[kc2], qh[kc2], s0);
+      s0 = mfma16(k0[kc2], qm[kc2], s0);
       s0 = mfma16(k0[kc2], ql[kc2], s0);
       s1 = mfma16(k1[kc2], qh[kc2], s1);
+      s1 = mfma16(k1[kc2], qm[kc2], s1);
       s1 = mfma16(k1[kc2], ql[kc2], s1);
     }
     // lane: node 16 t + i, path entries 32 b + 8 g + e (e < 4 from s0)
@@ -1789,13 +1817,14 @@ __global__ __launch_bounds__(64 * kPathWaves) void attn_path_kernel(AttnArgs a) 
       ps += pv[e];
     }
     ps = row4_sum(ps);
-    u32x4 ph, pl;
-    pack_hilo8(pv, ph, pl);
+    u32x4 ph, pm, pl;
+    pack_exact8(pv, ph, pm, pl);
 #pragma unroll
     for (int tt = 0; tt < DH / 16; ++tt) {
       const int d = 16 * tt + i;
       const u32x4 va = *(const u32x4*)(vl + d * VROW + 32 * (d / DPL) + 8 * g);
       f32x4 r = mfma16(va, ph, (f32x4){0, 0, 0, 0});
+      r = mfma16(va, pm, r);
       r = mfma16(va, pl, r);
       // (nodes of another block keep theirs, whatever these keys hold)
 #pragma unroll
