@@ -357,8 +357,8 @@ ssd_status ssd_tree_prep(const int32_t *parent_idx, int32_t n, int32_t *depth, u
  *     into the L2 of the XCD whose workgroups will read them, a few kernels
  *     ahead.  The pass never waits for it; it stops waiting for signals 50 ms
  *     after it starts.  In wider trees' passes the LayerNorm and attention
- *     kernels load the next weight GEMMs' fragments themselves (a captured
- *     graph keeps the setting it was captured with).  0 = off.
+ *     kernels load the next weight GEMMs' fragments themselves.  0 = off.  The
+ *     setting in force when a pass is enqueued or a graph launched counts.
  *     Results are bitwise the same either way.  ssd_kv_destroy waits for the
  *     session's prefetchers.
  * A captured graph keeps the pass mode and GEMM path in force when it was

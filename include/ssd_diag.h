@@ -29,6 +29,11 @@ ssd_status ssd_launch_gemm(const ssd_model *m, ssd_kv *kv, int32_t which, int32_
  * SSD_E_INVALID_ARG (null pointer, n outside [1, max_nodes]). */
 ssd_status ssd_verify_path(const ssd_model *m, const ssd_kv *kv, int32_t n, int32_t *path);
 
+/* Host-only: *inside = 1 if ssd_graph_launch(g) under its session's current
+ * options replays kernels that load later weights themselves (more than 64
+ * nodes, weight_prefetch on), else 0.  Errors: SSD_E_INVALID_ARG. */
+ssd_status ssd_graph_prefetch(const ssd_graph *g, int32_t *inside);
+
 /* Host-only: the persistent launch's work split for a model shape and a
  * count of 16-node tiles (1..4), as the session computes it.  tab receives
  * [256][32] int32 rows, one per compute workgroup (XCD x, rank r at row

@@ -138,8 +138,10 @@ struct ssd_kv {
 };
 
 struct ssd_graph {
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
+  // the pass without [0] and with [1] weight prefetch inside its kernels (wide
+  // trees; other passes are captured once, without)
+  hipGraph_t graph[2] = {};
+  hipGraphExec_t exec[2] = {};
   char* pinned = nullptr;
   const ssd_model* m = nullptr;  // the pass it replays
   ssd_kv* kv = nullptr;
@@ -736,6 +738,10 @@ static bool pass_signals(const ssd_model* m, int path, int n) { return !m->f32 &
 // stream first (the pass never waits for it).
 static bool use_fused(const ssd_model* m, const ssd_kv* kv, int n);
 
+// Whether the kernels of a per-sub-layer pass can bring later weights in
+// themselves (wide trees, see enqueue_verify).
+static bool pass_prefetches(const ssd_model* m, int path, int n) { return !m->f32 && gemm_wide(gemm_vec(path, n), n); }
+
 static ssd_status start_pass_prefetch(const ssd_model* m, ssd_kv* kv, int n, bool fused, int path) {
   if (fused || !pass_signals(m, path, n)) return SSD_OK;
   const unsigned long long base = kv->sig_count;
@@ -781,7 +787,7 @@ static int resid_splits(const ssd_model* m, int path, int n, int rows, int K) {
 // ([n][d] fp32, device), the tree scratch already holding the nodes' K/V of
 // layers below l0.
 static ssd_status enqueue_verify(const ssd_model* m, ssd_kv* kv, int32_t P, int32_t n, const char* stage_host,
-                                 size_t stage_used, float* logits, hipStream_t s, int l0 = 0,
+                                 size_t stage_used, float* logits, hipStream_t s, bool prefetch_on, int l0 = 0,
                                  const float* x_in = nullptr) {
   const ssd_config& c = m->cfg;
   const int d = c.d_model, H = c.n_head, DH = m->dh, M = c.d_mlp, V = c.vocab, L = c.n_layer;
@@ -860,7 +866,7 @@ static ssd_status enqueue_verify(const ssd_model* m, ssd_kv* kv, int32_t P, int3
   // the attention split the out-projection's, the merge the MLP
   // down-projection's and LayerNorm 2 the up-projection's.
   Prefetch pf_qkv{}, pf_o{}, pf_fc{}, pf_pr{};
-  const bool pf_on = kv->prefetch && !f32 && gemm_wide(gemm_vec(gp, n), n);
+  const bool pf_on = prefetch_on && pass_prefetches(m, gp, n);
   if (pf_on) {
     pf_qkv = wide_prefetch(EPI_QKV, nullptr, 3 * d, d, n, q8);
     pf_o = wide_prefetch(EPI_PARTIAL, nullptr, d, d, n, q8);
@@ -1013,7 +1019,7 @@ static ssd_status verify_entry(const ssd_model* m, ssd_kv* kv, int32_t prefix_le
   // (a pass from a later layer runs without the weight prefetcher, whose
   // signal schedule assumes every layer)
   if (l0 == 0) st = start_pass_prefetch(m, kv, n_nodes, fused, kv->gemm_path);
-  if (st == SSD_OK) st = enqueue_verify(m, kv, prefix_len, n_nodes, host, used, logits, s, l0, x_in);
+  if (st == SSD_OK) st = enqueue_verify(m, kv, prefix_len, n_nodes, host, used, logits, s, kv->prefetch, l0, x_in);
   if (st == SSD_OK && accepted_path)
     st = enqueue_greedy_after_pass(m, kv, n_nodes, fused, logits, accepted_path, path_len, next_token, s);
   ssd_status st2 = release_slot(kv, slot, s);
@@ -1087,41 +1093,52 @@ static ssd_status capture_pass(const ssd_model* m, ssd_kv* kv, int32_t prefix_le
     return fail(SSD_E_DEVICE, std::string("hipHostMalloc: ") + hipGetErrorString(e));
   }
   const size_t used = fill_stage(g->pinned, prefix_len, tree_tokens, parent_idx, n_nodes, kv->max_nodes);
-  // capture on a private stream (the legacy null stream cannot be captured);
-  // the graph is later launched on the caller's stream
-  hipStream_t cs = nullptr;
-  e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
-  if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-  if (e != hipSuccess) {
-    if (cs) (void)hipStreamDestroy(cs);
-    ssd_graph_destroy(g);
-    return fail(SSD_E_DEVICE, std::string("hipStreamBeginCapture: ") + hipGetErrorString(e));
-  }
-  st = enqueue_verify(m, kv, prefix_len, n_nodes, g->pinned, used, logits, cs, 0, nullptr);
-  if (st == SSD_OK && path) st = enqueue_greedy_after_pass(m, kv, n_nodes, g->fused, logits, path, path_len, next, cs);
-  hipGraph_t graph = nullptr;
-  e = hipStreamEndCapture(cs, &graph);
-  (void)hipStreamDestroy(cs);
-  if (st != SSD_OK || e != hipSuccess) {
-    if (graph) (void)hipGraphDestroy(graph);
-    ssd_graph_destroy(g);
-    return st != SSD_OK ? st : fail(SSD_E_DEVICE, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
-  }
-  g->graph = graph;
-  e = hipGraphInstantiate(&g->exec, graph, nullptr, nullptr, 0);
-  if (e != hipSuccess) {
-    ssd_graph_destroy(g);
-    return fail(SSD_E_DEVICE, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
+  // Weight prefetch is an option of each launch, and a wide pass does it inside
+  // its kernels: both kinds are captured, and the launch takes the one in force.
+  const int kinds = !g->fused && pass_prefetches(m, g->gemm_path, n_nodes) ? 2 : 1;
+  for (int k = 0; k < kinds; ++k) {
+    // capture on a private stream (the legacy null stream cannot be captured);
+    // the graph is later launched on the caller's stream
+    hipStream_t cs = nullptr;
+    e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
+    if (e != hipSuccess) {
+      if (cs) (void)hipStreamDestroy(cs);
+      ssd_graph_destroy(g);
+      return fail(SSD_E_DEVICE, std::string("hipStreamBeginCapture: ") + hipGetErrorString(e));
+    }
+    st = enqueue_verify(m, kv, prefix_len, n_nodes, g->pinned, used, logits, cs, k == 1);
+    if (st == SSD_OK && path)
+      st = enqueue_greedy_after_pass(m, kv, n_nodes, g->fused, logits, path, path_len, next, cs);
+    e = hipStreamEndCapture(cs, &g->graph[k]);
+    (void)hipStreamDestroy(cs);
+    if (st != SSD_OK || e != hipSuccess) {
+      ssd_graph_destroy(g);
+      return st != SSD_OK ? st : fail(SSD_E_DEVICE, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
+    }
+    e = hipGraphInstantiate(&g->exec[k], g->graph[k], nullptr, nullptr, 0);
+    if (e != hipSuccess) {
+      ssd_graph_destroy(g);
+      return fail(SSD_E_DEVICE, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
+    }
   }
   *out = g;
   return SSD_OK;
 }
 
+static bool graph_prefetches(const ssd_graph* g) { return g->kv->prefetch && g->exec[1]; }
+
+extern "C" ssd_status ssd_graph_prefetch(const ssd_graph* g, int32_t* inside) {
+  if (!g || !inside) return fail(SSD_E_INVALID_ARG, "null argument");
+  *inside = graph_prefetches(g);
+  return SSD_OK;
+}
+
 extern "C" ssd_status ssd_graph_launch(ssd_graph* g, void* stream) {
-  if (!g || !g->exec) return fail(SSD_E_INVALID_ARG, "null graph");
+  if (!g || !g->exec[0]) return fail(SSD_E_INVALID_ARG, "null graph");
   const ssd_status st = start_pass_prefetch(g->m, g->kv, g->n, g->fused, g->gemm_path);
   if (st != SSD_OK) return st;
-  HIP_TRY(hipGraphLaunch(g->exec, (hipStream_t)stream));
+  HIP_TRY(hipGraphLaunch(g->exec[graph_prefetches(g)], (hipStream_t)stream));
   g->kv->resid_fused = g->fused;
   g->kv->last_n = g->n;
   g->kv->last_layers = g->m->cfg.n_layer;
@@ -1130,8 +1147,10 @@ extern "C" ssd_status ssd_graph_launch(ssd_graph* g, void* stream) {
 
 extern "C" void ssd_graph_destroy(ssd_graph* g) {
   if (!g) return;
-  if (g->exec) (void)hipGraphExecDestroy(g->exec);
-  if (g->graph) (void)hipGraphDestroy(g->graph);
+  for (int k = 0; k < 2; ++k) {
+    if (g->exec[k]) (void)hipGraphExecDestroy(g->exec[k]);
+    if (g->graph[k]) (void)hipGraphDestroy(g->graph[k]);
+  }
   if (g->pinned) (void)hipHostFree(g->pinned);
   delete g;
 }

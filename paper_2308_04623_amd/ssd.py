@@ -34,7 +34,8 @@ EXPORTS = ("ssd_model_create", "ssd_model_create_q8", "ssd_model_destroy", "ssd_
            "ssd_graph_capture_verify_greedy", "ssd_uniform", "ssd_cdf_pick", "ssd_tree_verify_from",
            "ssd_tree_reuse")
 # and every function include/ssd_diag.h declares (measurement and diagnostics)
-DIAG_EXPORTS = ("ssd_launch_gemm", "ssd_verify_path", "ssd_fused_plan", "ssd_kv_set_trace", "ssd_model_q8_matrix")
+DIAG_EXPORTS = ("ssd_launch_gemm", "ssd_verify_path", "ssd_fused_plan", "ssd_kv_set_trace", "ssd_model_q8_matrix",
+                "ssd_graph_prefetch")
 
 
 class SSDError(RuntimeError):
@@ -104,6 +105,7 @@ def lib():
             "ssd_kv_set_options": [vp, C.POINTER(_Options)],
             "ssd_kv_get_options": [vp, C.POINTER(_Options)],
             "ssd_verify_path": [vp, vp, C.c_int32, C.POINTER(C.c_int32)],
+            "ssd_graph_prefetch": [vp, C.POINTER(C.c_int32)],
             "ssd_fused_plan": [C.c_int32] * 5 + [vp, vp, vp],
             "ssd_kv_set_trace": [vp, vp],
             "ssd_launch_gemm": [vp, vp, C.c_int32, C.c_int32, C.c_int32, vp],
@@ -332,6 +334,12 @@ class Graph:
 
     def launch(self, stream=None):
         _check(lib().ssd_graph_launch(self.handle, _stream(stream)), "ssd_graph_launch")
+
+    def prefetches(self) -> bool:
+        """ssd_graph_prefetch: whether a launch now replays kernels that load later weights themselves."""
+        v = C.c_int32()
+        _check(lib().ssd_graph_prefetch(self.handle, C.byref(v)), "ssd_graph_prefetch")
+        return bool(v.value)
 
     def close(self):
         if getattr(self, "handle", None):
