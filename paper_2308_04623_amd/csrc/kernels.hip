@@ -3265,21 +3265,24 @@ hipError_t launch_sample_accept(const int* tokens, const int* parents, int N, in
 // unit), so one token's commit takes a few blocks and a prompt's fills the
 // chip.  512 rows of GPT-2-L (189 MB moved): 147 us with one 2-byte element
 // per thread and step and a block per layer and head, now 33 us.
+// Block column y takes the layer-heads [y per, y per + per), few enough for
+// 32-bit indices.
 template <typename U>
 __global__ __launch_bounds__(256) void commit_kernel(U* __restrict__ kc, U* __restrict__ vc, const U* __restrict__ kt,
-                                                     const U* __restrict__ vt, int LH, int max_ctx, int max_nodes,
+                                                     const U* __restrict__ vt, int LH, int per, int max_ctx, int max_nodes,
                                                      int units, int P, const int* __restrict__ path,
                                                      const int* __restrict__ path_len, unsigned* __restrict__ err) {
   const int len = *path_len;
   if (len < 0 || len > max_nodes) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(err, 1u);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) atomicAdd(err, 1u);
     return;
   }
-  // (32-bit indices: launch_commit bounds LH max_nodes units)
-  const unsigned total = (unsigned)LH * len * units;
+  const int lh0 = blockIdx.y * per;
+  const unsigned total = (unsigned)min(per, LH - lh0) * len * units;
   for (unsigned idx = blockIdx.x * 256 + threadIdx.x; idx < total; idx += gridDim.x * 256) {
     const unsigned row = idx / (unsigned)units;
-    const int c = (int)(idx - row * units), lh = (int)(row / (unsigned)len), t = (int)(row - (unsigned)lh * len);
+    const int c = (int)(idx - row * units), l = (int)(row / (unsigned)len), t = (int)(row - (unsigned)l * len);
+    const int lh = lh0 + l;
     const int node = path[t];
     if (node < 0 || node >= max_nodes || P + t >= max_ctx) {
       if (c == 0 && lh == 0) atomicAdd(err, 1u);
@@ -3296,28 +3299,20 @@ __global__ __launch_bounds__(256) void commit_kernel(U* __restrict__ kc, U* __re
 template <typename U>
 static void commit_go(void* kc, void* vc, const void* kt, const void* vt, int LH, int max_ctx, int max_nodes,
                       int row_bytes, int P, const int* path, const int* path_len, unsigned* err, hipStream_t s) {
-  // blocks for a path of max_nodes at four units a thread, within 64 .. 2048
   const int units = row_bytes / (int)sizeof(U);
-  const size_t want = (size_t)LH * max_nodes * units / 1024;
+  const int per = (int)min((size_t)LH, (size_t)0x7fffffff / ((size_t)max_nodes * units));  // (max_nodes <= 1024)
+  const int groups = (LH + per - 1) / per;
+  // blocks for a path of max_nodes at four units a thread, within 64 .. 2048
+  const size_t want = (size_t)per * max_nodes * units / 1024;
   const int blocks = (int)(want < 64 ? 64 : want > 2048 ? 2048 : want);
-  commit_kernel<U><<<blocks, 256, 0, s>>>((U*)kc, (U*)vc, (const U*)kt, (const U*)vt, LH, max_ctx, max_nodes, units, P,
-                                          path, path_len, err);
+  commit_kernel<U><<<dim3(blocks, groups), 256, 0, s>>>((U*)kc, (U*)vc, (const U*)kt, (const U*)vt, LH, per, max_ctx,
+                                                        max_nodes, units, P, path, path_len, err);
 }
 
 hipError_t launch_commit(int f32, void* kc, void* vc, const void* kt, const void* vt, int LH, int max_ctx,
                          int max_nodes, int DH, int P, const int* path, const int* path_len, unsigned* err,
                          hipStream_t s) {
   const int rb = DH * (f32 ? 4 : 2);
-  // (a layer group at a time where one launch's indices would pass 31 bits)
-  const int most = (int)((size_t)0x7fffffff / ((size_t)max_nodes * rb));
-  if (most < 1) return hipErrorInvalidValue;
-  if (LH > most) {
-    const size_t cb = (size_t)most * max_ctx * rb, tb = (size_t)most * max_nodes * rb;
-    const hipError_t e = launch_commit(f32, kc, vc, kt, vt, most, max_ctx, max_nodes, DH, P, path, path_len, err, s);
-    if (e != hipSuccess) return e;
-    return launch_commit(f32, (char*)kc + cb, (char*)vc + cb, (const char*)kt + tb, (const char*)vt + tb, LH - most,
-                         max_ctx, max_nodes, DH, P, path, path_len, err, s);
-  }
   const bool wide = rb % 16 == 0 && (((uintptr_t)kc | (uintptr_t)vc | (uintptr_t)kt | (uintptr_t)vt) & 15) == 0;
   if (wide) commit_go<u32x4>(kc, vc, kt, vt, LH, max_ctx, max_nodes, rb, P, path, path_len, err, s);
   else if (f32) commit_go<float>(kc, vc, kt, vt, LH, max_ctx, max_nodes, rb, P, path, path_len, err, s);
