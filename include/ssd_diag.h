@@ -29,6 +29,13 @@ ssd_status ssd_launch_gemm(const ssd_model *m, ssd_kv *kv, int32_t which, int32_
  * SSD_E_INVALID_ARG (null pointer, n outside [1, max_nodes]). */
 ssd_status ssd_verify_path(const ssd_model *m, const ssd_kv *kv, int32_t n, int32_t *path);
 
+/* Host-only: the tile that one workgroup of a weight GEMM over more than 64
+ * nodes owns on the matrix cores, and its k-splits: tile[0] row blocks of 16,
+ * tile[1] node tiles of 16, tile[2] splits (1, 2, 4 or 8) for a matrix of rows x
+ * cols; which = 0 QKV, 1 attention output, 2 MLP up, 3 MLP down, 4 the LM head;
+ * q8: 8-bit weights.  Errors: SSD_E_INVALID_ARG (null, sizes out of range). */
+ssd_status ssd_wide_tile(int32_t which, int32_t rows, int32_t cols, int32_t n_nodes, int32_t q8, int32_t *tile);
+
 /* Host-only: *inside = 1 if ssd_graph_launch(g) under its session's current
  * options replays kernels that load later weights themselves (more than 64
  * nodes, weight_prefetch on), else 0.  Errors: SSD_E_INVALID_ARG. */

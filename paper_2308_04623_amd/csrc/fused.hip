@@ -33,7 +33,7 @@
 //    poll still waits behind the other waves' loads.  With two or more node
 //    tiles, waves 1..3 also copy into LDS the weights of a GEMM two stages
 //    on: the out-projection's during LN1 + QKV, and the down-projection's
-//    during the up-projection (at four tiles already during LN2's wait).
+//    during the up-projection (from three tiles on already during LN2's wait).
 //  * Hand-offs are per-workgroup stage flags carrying a monotonically
 //    increasing tag (pass, layer, stage).  A workgroup writes its outputs,
 //    waits for its stores, then stores its flag; consumers poll the 32 flags
@@ -1653,7 +1653,7 @@ __device__ __forceinline__ void compute_wg(const FusedArgs& a, unsigned char* ld
       signal(a, w, l, fid, true);
       stamp(a, w, l, fid, 2);
       if (wo && wpr_early && threadIdx.x >= 64) {
-        // at four node tiles the down-projection's weights are copied into
+        // from three node tiles on the down-projection's weights are copied into
         // LDS from here (waves 1..7), inside the LayerNorm's cross-XCD wait,
         // rather than after the LayerNorm's rows (measured: 3 % faster at
         // 64 nodes, neutral or slower at 32)
@@ -1779,11 +1779,11 @@ out:
 }
 
 
-// RE: the pass starts at layer a.l0 from the residual stream a.x_in; SM: at
-// most kFSmallN nodes
+// RE: the pass starts at layer a.l0 from the residual stream a.x_in; SM: a
+// single node
 template <int NT, bool Q8, bool RE, bool SM>
 __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void pass_kernel(FusedArgs a) {
-  static_assert(!SM || NT == 1, "small trees are one tile");
+  static_assert(!SM || NT == 1, "a single node is one tile");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   compute_wg<NT, Q8, RE, SM>(a, lds);
 }

@@ -124,8 +124,8 @@ __device__ __forceinline__ void pass_signal(unsigned long long* sig) {
     __hip_atomic_fetch_add(sig, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// XCDs that one k-split of a wide GEMM keeps to
-__host__ __device__ __forceinline__ int wide_xcds(int gy) { return 8 % gy == 0 ? 8 / gy : 8; }
+// XCDs that one k-split of a wide GEMM keeps to (1, 2, 4 or 8 splits)
+__host__ __device__ __forceinline__ int wide_xcds(int gy) { return 8 / gy; }
 
 // Extra blocks (pf.first on) of the small kernels between the wide GEMMs read
 // a later GEMM's weights, so that it finds them in L2: a GEMM over 128 nodes
@@ -142,9 +142,8 @@ __device__ __forceinline__ void prefetch_weights(const Prefetch& pf, unsigned ch
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int waves = (((int)gridDim.x - pf.first) >> 3) * nw, w = (b >> 3) * nw + wv;
   const int X = wide_xcds(pf.gy);
-  const bool own = 8 % pf.gy == 0;  // (another split count: an XCD reads every split)
-  const size_t off = own ? (size_t)(x % pf.gy) * pf.step : 0;
-  const int i0 = own ? x / pf.gy : x, run = (int)min((size_t)(own ? pf.step : pf.row_bytes), pf.row_bytes - off);
+  const size_t off = (size_t)(x % pf.gy) * pf.step;
+  const int i0 = x / pf.gy, run = (int)min((size_t)pf.step, pf.row_bytes - off);
   const int per = (run + 1023) >> 10, rows = i0 < pf.gx ? (pf.gx - i0 + X - 1) / X * pf.rbt : 0;
   if (run < 1024) return;
   for (int f = w; f < rows * per; f += waves) {
@@ -733,8 +732,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
 // the XCDs, so an XCD reads only its splits' part of the activations (MLP
 // down over 512 nodes: 1.3 of 5.2 MB per XCD, against a 4 MB L2).  Block b: XCD
 // x = b % 8, split x % gy, and b / 8 names (group i = x / gy + (8 / gy) (b / 8
-// / gt), node-tile group j); groups past gx exit.  Another split count takes
-// splits in turn inside each XCD.
+// / gt), node-tile group j); groups past gx exit.
 
 // four consecutive outputs o .. o + 3 of node nn (o % 4 == 0, all below M
 // except in the LM head, whose row count is any)
@@ -779,18 +777,13 @@ struct WidePos {
 };
 __device__ __forceinline__ bool wide_pos(int gx, int gt, int gy, WidePos& p) {
   const int x = blockIdx.x & 7, q = blockIdx.x >> 3, X = wide_xcds(gy);
-  if (8 % gy == 0) {
-    p = WidePos{x / gy + X * (q / gt), q % gt, x % gy};
-  } else {
-    const int rem = q % (gt * gy);
-    p = WidePos{x + 8 * (q / (gt * gy)), rem / gy, rem % gy};
-  }
+  p = WidePos{x / gy + X * (q / gt), q % gt, x % gy};
   return p.i < gx;
 }
 // workgroups of a launch (per XCD, times 8)
 static int wide_blocks(int gx, int gt, int gy) {
   const int X = wide_xcds(gy);
-  return 8 * ((gx + X - 1) / X) * gt * (8 % gy == 0 ? 1 : gy);
+  return 8 * ((gx + X - 1) / X) * gt;
 }
 
 template <int RBT, int TT, int NW, int U, bool Q8>
@@ -987,9 +980,10 @@ static WideCfg wide_cfg(int kind, int RB, int KC, int N, bool q8) {
   for (int S = 1; S <= (kind == EPI_PARTIAL ? kMaxSplits : 1); S *= 2)
     for (int rbt = 4; rbt <= 5; ++rbt)
       for (int tt : {2, 3, 4, 6, 8}) {
-        if (S > KC) continue;
         const int gx = (RB + rbt - 1) / rbt, gt = (NT + tt - 1) / tt, kcs = (KC + S - 1) / S;
-        const int rounds = (wide_blocks(gx, gt, (KC + kcs - 1) / kcs) + 255) / 256;
+        const int gy = (KC + kcs - 1) / kcs;
+        if (8 % gy) continue;  // (steps that do not cut into S ranges; a split must keep to its XCDs)
+        const int rounds = (wide_blocks(gx, gt, gy) + 255) / 256;
         const double c =
             (double)rounds * (kcs * (rbt + tt) + rbt * tt) + (kind == EPI_PARTIAL ? 0.22 * S * N : 0.0);
         if (c < bc) {
@@ -1000,6 +994,13 @@ static WideCfg wide_cfg(int kind, int RB, int KC, int N, bool q8) {
   return best;
 }
 
+void wide_tile(int kind, int M, int K, int N, bool q8, int* tile) {
+  const WideCfg c = wide_cfg(kind, (M + 15) / 16, K / 32, N, q8);
+  tile[0] = c.rbt;
+  tile[1] = c.tt;
+  tile[2] = c.S;
+}
+
 // Tile shape per node count and GEMM kind (measured on the GPT-2-L shapes:
 // K = 1280 for QKV / MLP up / attention out, 5120 for MLP down).  At 17-32
 // nodes: QKV one row block per workgroup (240 workgroups), the others two;
@@ -1007,7 +1008,6 @@ static WideCfg wide_cfg(int kind, int RB, int KC, int N, bool q8) {
 GemmCfg gemm_cfg(int N, int vec, int kind) {
   GemmCfg c{};
   c.rb = 1;
-  c.ck = 1;
   c.nw = 4;
   if (vec) {
     int nv = 1;
@@ -1114,16 +1114,16 @@ static void wide_go(int grid, const void* Wp, int KC, int RBtot, int NT, int kcs
     gemm_wide_kernel<RBT, TT, NW, U, false><<<grid, 64 * NW, 0, s>>>(Wp, KC, RBtot, NT, kcs, gx, gt, gy, act, kind, ep);
 }
 
-// Waves and k-steps in flight per tile: 8 waves where the sums of their tiles
-// fit LDS at once (MLP up over 256 nodes: 10.6 us, 4 waves 10.9), 4 at 8 node
-// tiles; as many k-steps as registers allow.  The 8-bit LM head, whose many
+// Waves and k-steps in flight per tile: 8 waves up to 6 node tiles (MLP up over
+// 256 nodes: 10.6 us, 4 waves 10.9; at 6 their tiles are summed in two rounds of
+// LDS), 4 at 8 node tiles; as many k-steps as registers allow.  The 8-bit LM head, whose many
 // workgroups come in rounds, runs 4 waves (128 nodes 34 us, 8 waves 42 us).
 static hipError_t launch_gemm_wide(int kind, const void* Wp, int M, int K, const uint16_t* act, int kcs,
                                    const Epi& ep, hipStream_t s) {
   const int KC = K / 32, RB = (M + 15) / 16, NT = (ep.N + 15) / 16;
   const WideCfg c = wide_cfg(kind, RB, KC, ep.N, ep.wscale != nullptr);
   const int gx = (RB + c.rbt - 1) / c.rbt, gt = (NT + c.tt - 1) / c.tt, gy = (KC + kcs - 1) / kcs;
-  if (kind != EPI_PARTIAL && gy != 1) return hipErrorInvalidValue;
+  if (8 % gy || (kind != EPI_PARTIAL && gy != 1)) return hipErrorInvalidValue;
   const int grid = wide_blocks(gx, gt, gy);
   if (kind == EPI_LOGITS) {
     if (ep.wscale) wide_go<5, 4, 4, 4>(grid, Wp, KC, RB, NT, kcs, gx, gt, gy, act, kind, ep, s);
@@ -2928,7 +2928,6 @@ __global__ __launch_bounds__(SW_THREADS) void sample_accept_kernel(SwArgs a) {
   __shared__ double red[16];
   __shared__ unsigned hl[256];
   __shared__ int shi[8];
-  __shared__ double shd[4];
   __shared__ SwGather gb[2];
   __shared__ int par_l[SW_MAXN], fail;
   const int tid = threadIdx.x, g = blockIdx.x >> 3, G = a.G, V = a.V;

@@ -498,6 +498,15 @@ static bool use_fused(const ssd_model* m, const ssd_kv* kv, int n) {
   return kv->pass_mode == 2 ? n <= kFMaxN : n <= kFAutoMaxN;
 }
 
+extern "C" ssd_status ssd_wide_tile(int32_t which, int32_t rows, int32_t cols, int32_t n_nodes, int32_t q8,
+                                    int32_t* tile) {
+  static const int kinds[5] = {EPI_QKV, EPI_PARTIAL, EPI_GELU, EPI_PARTIAL, EPI_LOGITS};
+  if (!tile || which < 0 || which > 4 || rows < 1 || cols < 32 || cols % 32 || n_nodes <= 64 || n_nodes > kMaxNodes)
+    return fail(SSD_E_INVALID_ARG, "bad argument");
+  wide_tile(kinds[which], rows, cols, n_nodes, q8 != 0, tile);
+  return SSD_OK;
+}
+
 extern "C" ssd_status ssd_verify_path(const ssd_model* m, const ssd_kv* kv, int32_t n, int32_t* path) {
   if (!m || !kv || !path || n < 1 || n > kv->max_nodes) return fail(SSD_E_INVALID_ARG, "bad argument");
   *path = use_fused(m, kv, n) ? 2 : 1;
@@ -519,14 +528,14 @@ extern "C" ssd_status ssd_kv_create(const ssd_model* m, int32_t max_ctx, int32_t
   kv->vc = v_cache;
   kv->kt = k_tree;
   kv->vt = v_tree;
-  // GEMMs read activation rows in power-of-two node tiles (16..256), or in
-  // groups of 256 beyond that, so pad the row count to cover the last tile.
-  if (max_nodes <= 256) {
+  // GEMMs read activation rows in node tiles of 16: a power of two of them up
+  // to 64 nodes, as many as the tree has above.
+  if (max_nodes <= 64) {
     int p2 = 16;
     while (p2 < max_nodes) p2 *= 2;
     kv->npad = p2;
   } else {
-    kv->npad = round_up(max_nodes, 256);
+    kv->npad = round_up(max_nodes, 16);
   }
   const size_t es = m->f32 ? 4 : 2;
   const int d = c.d_model, M = c.d_mlp, V = c.vocab;

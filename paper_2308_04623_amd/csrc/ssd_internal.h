@@ -52,9 +52,9 @@ struct Epi {
 };
 
 // tile shape of the bf16 GEMM for a node count: node tiles of 16, row blocks
-// per workgroup, k-steps per staged chunk, nodes of the vector path
+// per workgroup, nodes of the vector path, waves per workgroup
 struct GemmCfg {
-  int nt, rb, ck, nv, nw;  // nw: waves per workgroup
+  int nt, rb, nv, nw;
 };
 
 // tile of the wide-tree GEMM (more than 64 nodes): row blocks and node tiles
@@ -72,6 +72,9 @@ struct Prefetch {
   int RBtot, rbt, gx, gy;  // the launch: row blocks, per group, groups, k-splits
   int first;               // the first block that prefetches (a multiple of 8)
 };
+
+// its choice for a GEMM: {row blocks, node tiles, k-splits}
+void wide_tile(int kind, int M, int K, int N, bool q8, int* tile);
 
 // launch geometry of one bf16 GEMM: block (bx, by) owns weight row blocks
 // bx RB .. bx RB + RB - 1 (rows past RBtot read row block RBtot - 1 and are

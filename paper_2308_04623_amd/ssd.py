@@ -35,7 +35,7 @@ EXPORTS = ("ssd_model_create", "ssd_model_create_q8", "ssd_model_destroy", "ssd_
            "ssd_tree_reuse")
 # and every function include/ssd_diag.h declares (measurement and diagnostics)
 DIAG_EXPORTS = ("ssd_launch_gemm", "ssd_verify_path", "ssd_fused_plan", "ssd_kv_set_trace", "ssd_model_q8_matrix",
-                "ssd_graph_prefetch")
+                "ssd_graph_prefetch", "ssd_wide_tile")
 
 
 class SSDError(RuntimeError):
@@ -106,6 +106,7 @@ def lib():
             "ssd_kv_get_options": [vp, C.POINTER(_Options)],
             "ssd_verify_path": [vp, vp, C.c_int32, C.POINTER(C.c_int32)],
             "ssd_graph_prefetch": [vp, C.POINTER(C.c_int32)],
+            "ssd_wide_tile": [C.c_int32] * 5 + [i32p],
             "ssd_fused_plan": [C.c_int32] * 5 + [vp, vp, vp],
             "ssd_kv_set_trace": [vp, vp],
             "ssd_launch_gemm": [vp, vp, C.c_int32, C.c_int32, C.c_int32, vp],
@@ -175,6 +176,14 @@ def fused_plan(n_head: int, d_model: int, d_mlp: int, vocab: int, n_tiles: int):
     _check(lib().ssd_fused_plan(n_head, d_model, d_mlp, vocab, n_tiles, tab.ctypes.data, xh.ctypes.data,
                                 xf.ctypes.data), "ssd_fused_plan")
     return tab, xh, xf
+
+
+def wide_tile(which: int, rows: int, cols: int, n: int, q8: bool = False) -> Tuple[int, int, int]:
+    """The tile of a weight GEMM over n > 64 nodes (host-only): (row blocks, node tiles, k-splits); which 0 QKV,
+    1 attention output, 2 MLP up, 3 MLP down, 4 LM head."""
+    t = np.zeros(3, np.int32)
+    _check(lib().ssd_wide_tile(which, rows, cols, n, int(q8), _p32(t)), "ssd_wide_tile")
+    return tuple(int(v) for v in t)
 
 
 def accept_noalloc(tokens, parent_idx, logits, out, mode: int = GREEDY, draft_probs=None,

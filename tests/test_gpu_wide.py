@@ -20,7 +20,7 @@ SHAPES = {
     "dh64": W.GPT2Config(n_layer=2, d_model=192, n_head=3, d_mlp=352, vocab=515, n_pos=1200, dtype="bf16"),
     # 48, 16 and 64 row blocks, 8 and 32 k-steps
     "dh32": W.GPT2Config(n_layer=2, d_model=256, n_head=8, d_mlp=1024, vocab=1030, n_pos=1200, dtype="bf16"),
-    # enough row blocks that the tile grows with the tree (4 or 5 row blocks x 2, 3, 4, 6 or 8 node tiles)
+    # enough row blocks that the tile grows with the tree (to 4 x 8 and 5 x 6; every tile by name: test_gpu_wide_tiles)
     "mlp5120": W.GPT2Config(n_layer=1, d_model=128, n_head=4, d_mlp=5120, vocab=515, n_pos=1200, dtype="bf16"),
     "mlp3840": W.GPT2Config(n_layer=1, d_model=128, n_head=4, d_mlp=3840, vocab=515, n_pos=1200, dtype="bf16"),
     "d1280": W.GPT2Config(n_layer=1, d_model=1280, n_head=20, d_mlp=1280, vocab=515, n_pos=1200, dtype="bf16"),
