@@ -60,3 +60,36 @@ def test_many_calls_on_one_exchange_area(session):
     for seed in range(60):
         check(session, 4096 if seed % 3 else 9, "SAMPLE_DET", 3 if seed % 2 else 0, 0.8, seed, bool(seed % 5))
     assert session.error_count() == 0
+
+
+def test_exchange_words_after_the_call_counter_wraps(session):
+    """Calls 65,536 apart carry the same tags; the words of the earlier ones are
+    cleared in between.  Calls over three slices leave words, one-slice calls
+    advance the counter around its 16 bits, and the same calls on other logits
+    must not read the old words."""
+    import torch
+    from paper_2308_04623_amd import ssd
+    V, n = 5000, 8
+    par = W.chain_tree(n)
+    g = np.random.default_rng(11)
+    rows = [(g.standard_normal((n, V)) * 3).astype(np.float32) for _ in range(2)]
+    toks = [np.concatenate([[0], r.argmax(1)[:-1]]).astype(np.int32) for r in rows]
+    dev = [torch.from_numpy(r).cuda() for r in rows]
+    small = torch.zeros((1, 9), dtype=torch.float32, device="cuda")
+    out = tuple(torch.zeros(k, dtype=torch.int32, device="cuda") for k in (n, 1, 1))
+    one = (np.zeros(1, np.int32), np.full(1, -1, np.int32))
+
+    def run(which, seed):
+        path, plen, nxt = session.accept(toks[which], par, dev[which], mode=ssd.SAMPLE_DET, seed=seed, top_k=20, out=out)
+        m = int(plen.item())
+        want = oracle.tree_accept(oracle.SAMPLE_DET, toks[which], par, rows[which], temperature=1.0, seed=seed, top_k=20)
+        assert path[:m].cpu().numpy().tolist() == want[0].tolist() and int(nxt.item()) == want[1]
+
+    calls = 40
+    for seed in range(calls):
+        run(0, seed)
+    for i in range(65536 - calls):
+        session.accept(*one, small, mode=ssd.SAMPLE_DET, seed=i, out=out)
+    for seed in range(calls):
+        run(1, seed)
+    assert session.error_count() == 0

@@ -33,3 +33,18 @@ def test_nan_keys_reach_every_node_below_them(lost, P):
     s = ssd.Session(ssd.Model(CFG, w), ctx, n, ssd.to_device(kc, CFG), ssd.to_device(vc, CFG))
     assert np.isfinite(s.verify(far, toks, par).cpu().numpy()).all()
     assert np.isnan(s.verify(P, toks, par).cpu().numpy()).all()
+
+
+@pytest.mark.parametrize("n", [70, 160])
+def test_nan_in_the_cache_reaches_every_node(n):
+    """Cached rows of NaN: a whole 32-row block, and one row of another chunk."""
+    from paper_2308_04623_amd import ssd
+    w = W.make_weights(CFG, 3, perturb_affine=True)
+    P, ctx = 300, 320
+    par = W.branching_tree([4, 2, 2, 1], n)
+    toks = W.tree_tokens(par, CFG.vocab, seed=n)
+    for rows in (slice(0, 32), slice(270, 271)):
+        kc, vc = W.random_kv_cache(CFG, ctx, P, seed=3)
+        kc[:, :, rows] = NAN_BF16
+        s = ssd.Session(ssd.Model(CFG, w), ctx, n, ssd.to_device(kc, CFG), ssd.to_device(vc, CFG))
+        assert np.isnan(s.verify(P, toks, par).cpu().numpy()).all()
