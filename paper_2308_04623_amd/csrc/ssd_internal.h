@@ -70,6 +70,7 @@ struct Prefetch {
   size_t row_bytes;        // of one 16-row block over all k-steps
   int step;                // bytes of a row block in one k-split
   int RBtot, rbt, gx, gy;  // the launch: row blocks, per group, groups, k-splits
+  int own;                 // the kernel's own blocks (LayerNorm)
   int first;               // the first block that prefetches (a multiple of 8)
 };
 
@@ -164,7 +165,7 @@ inline int attn_max_nsplit(int max_ctx, int H) {
 // bf16 attention: chunks of kPathChunk root-path entries that hold a full
 // 32-entry block of the path of a node at the given depth
 constexpr int kPathChunk = 128;
-inline int attn_npath(int depth) { return ((depth + 1) / 32 * 32 + kPathChunk - 1) / kPathChunk; }
+__host__ __device__ inline int attn_npath(int depth) { return ((depth + 1) / 32 * 32 + kPathChunk - 1) / kPathChunk; }
 
 // ---- launchers (kernels.hip); all enqueue on `s` and return the launch status
 hipError_t launch_embed(int f32, const void* wte, const void* wpe, const int* tokens, const int* pos, int N, int d,
