@@ -558,7 +558,7 @@ extern "C" ssd_status ssd_kv_create(const ssd_model* m, int32_t max_ctx, int32_t
   const size_t o_apart = take((m->f32 ? ap_f32 : ap_bf16) * 4);
   // root-path records of the bf16 kernels (a node's depth is below max_nodes)
   const size_t o_ppart =
-      take(m->f32 ? 0 : (size_t)c.n_head * attn_npath(max_nodes - 1) * max_nodes * (m->dh + 4) * 4);
+      take(m->f32 || max_nodes <= kPathNodes ? 0 : (size_t)c.n_head * attn_npath(max_nodes - 1) * max_nodes * (m->dh + 4) * 4);
   const size_t o_tree = take(stage_bytes(max_nodes));
   const size_t o_at = take((size_t)3 * max_nodes * 4), o_am = take((size_t)max_nodes * 4);
   const size_t o_amw = take(
@@ -869,7 +869,7 @@ static ssd_status enqueue_verify(const ssd_model* m, ssd_kv* kv, int32_t P, int3
 
   // (the staged depths, see fill_stage)
   const int32_t* dep_h = (const int32_t*)stage_host + 2 * maxn;
-  const int npath = attn_npath(*std::max_element(dep_h, dep_h + n));
+  const int npath = n > kPathNodes ? attn_npath(*std::max_element(dep_h, dep_h + n)) : 0;
 
   // Wide passes with weight prefetch on: LayerNorm 1 brings in the QKV weights,
   // the attention split the out-projection's, the merge the MLP

@@ -162,8 +162,15 @@ inline int attn_max_nsplit(int max_ctx, int H) {
   return attn_nsplit(max_ctx, H) > mx ? attn_nsplit(max_ctx, H) : mx;
 }
 
-// bf16 attention: chunks of kPathChunk root-path entries that hold a full
-// 32-entry block of the path of a node at the given depth
+// bf16 attention over more than kPathNodes nodes: chunks of kPathChunk root-path
+// entries that hold a full 32-entry block of the path of a node at the given
+// depth.  Trees of fewer nodes are at most 64 deep, eight steps of the merge's
+// walk, and a launch costs what the path kernel saves (12 GPT-2-L layers, chains,
+// with it / without: 32 nodes 605 / 548 us, 40: 730 / 697, 56: 760 / 758, 64:
+// 788 / 786; 80 nodes, near the start of the range: 681 / 735).  The line is on the node
+// count, not on the tree's depth, so that a node's result does not depend on how
+// deep the others are.
+constexpr int kPathNodes = 64;
 constexpr int kPathChunk = 128;
 __host__ __device__ inline int attn_npath(int depth) { return ((depth + 1) / 32 * 32 + kPathChunk - 1) / kPathChunk; }
 
