@@ -140,6 +140,7 @@ struct ssd_kv {
 struct ssd_graph {
   // the pass without [0] and with [1] weight prefetch inside its kernels (wide
   // trees; other passes are captured once, without)
+  bool wide = false;
   hipGraph_t graph[2] = {};
   hipGraphExec_t exec[2] = {};
   char* pinned = nullptr;
@@ -148,6 +149,10 @@ struct ssd_graph {
   int n = 0;
   bool fused = false;   // captured as the persistent single launch
   int gemm_path = 0;    // the session's GEMM path at capture (fixes the prefetcher's plan)
+  int P = 0;
+  size_t used = 0;  // bytes of the staged tree
+  float* logits = nullptr;
+  int32_t *path = nullptr, *path_len = nullptr, *next = nullptr;  // outputs of the greedy walk (or none)
 };
 
 // ------------------------------------------------------------------ small host helpers
@@ -1083,6 +1088,35 @@ extern "C" ssd_status ssd_graph_capture_verify_greedy(const ssd_model* m, ssd_kv
                       next_token, out);
 }
 
+// Captures g's pass with (1) or without (0) weight prefetch inside its kernels,
+// on a private stream (the legacy null stream cannot be captured); the graph
+// is later launched on the caller's stream.
+static ssd_status capture_kind(ssd_graph* g, int kind) {
+  ssd_kv* kv = g->kv;
+  hipStream_t cs = nullptr;
+  hipError_t e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
+  if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
+  if (e != hipSuccess) {
+    if (cs) (void)hipStreamDestroy(cs);
+    return fail(SSD_E_DEVICE, std::string("hipStreamBeginCapture: ") + hipGetErrorString(e));
+  }
+  ssd_status st = enqueue_verify(g->m, kv, g->P, g->n, g->pinned, g->used, g->logits, cs, kind == 1);
+  if (st == SSD_OK && g->path)
+    st = enqueue_greedy_after_pass(g->m, kv, g->n, g->fused, g->logits, g->path, g->path_len, g->next, cs);
+  hipGraph_t graph = nullptr;
+  e = hipStreamEndCapture(cs, &graph);
+  (void)hipStreamDestroy(cs);
+  if (st == SSD_OK && e != hipSuccess)
+    st = fail(SSD_E_DEVICE, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
+  if (st == SSD_OK) {
+    e = hipGraphInstantiate(&g->exec[kind], graph, nullptr, nullptr, 0);
+    if (e != hipSuccess) st = fail(SSD_E_DEVICE, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
+  }
+  if (st == SSD_OK) g->graph[kind] = graph;
+  else if (graph) (void)hipGraphDestroy(graph);
+  return st;
+}
+
 static ssd_status capture_pass(const ssd_model* m, ssd_kv* kv, int32_t prefix_len, const int32_t* tree_tokens,
                                const int32_t* parent_idx, int32_t n_nodes, float* logits, int32_t* path,
                                int32_t* path_len, int32_t* next, ssd_graph** out) {
@@ -1103,39 +1137,25 @@ static ssd_status capture_pass(const ssd_model* m, ssd_kv* kv, int32_t prefix_le
   }
   const size_t used = fill_stage(g->pinned, prefix_len, tree_tokens, parent_idx, n_nodes, kv->max_nodes);
   // Weight prefetch is an option of each launch, and a wide pass does it inside
-  // its kernels: both kinds are captured, and the launch takes the one in force.
-  const int kinds = !g->fused && pass_prefetches(m, g->gemm_path, n_nodes) ? 2 : 1;
-  for (int k = 0; k < kinds; ++k) {
-    // capture on a private stream (the legacy null stream cannot be captured);
-    // the graph is later launched on the caller's stream
-    hipStream_t cs = nullptr;
-    e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-    if (e != hipSuccess) {
-      if (cs) (void)hipStreamDestroy(cs);
-      ssd_graph_destroy(g);
-      return fail(SSD_E_DEVICE, std::string("hipStreamBeginCapture: ") + hipGetErrorString(e));
-    }
-    st = enqueue_verify(m, kv, prefix_len, n_nodes, g->pinned, used, logits, cs, k == 1);
-    if (st == SSD_OK && path)
-      st = enqueue_greedy_after_pass(m, kv, n_nodes, g->fused, logits, path, path_len, next, cs);
-    e = hipStreamEndCapture(cs, &g->graph[k]);
-    (void)hipStreamDestroy(cs);
-    if (st != SSD_OK || e != hipSuccess) {
-      ssd_graph_destroy(g);
-      return st != SSD_OK ? st : fail(SSD_E_DEVICE, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
-    }
-    e = hipGraphInstantiate(&g->exec[k], g->graph[k], nullptr, nullptr, 0);
-    if (e != hipSuccess) {
-      ssd_graph_destroy(g);
-      return fail(SSD_E_DEVICE, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
-    }
+  // its kernels: the kind in force is captured now, the other when a launch
+  // first asks for it.
+  g->P = prefix_len;
+  g->used = used;
+  g->logits = logits;
+  g->path = path;
+  g->path_len = path_len;
+  g->next = next;
+  g->wide = !g->fused && pass_prefetches(m, g->gemm_path, n_nodes);
+  st = capture_kind(g, g->wide && kv->prefetch);
+  if (st != SSD_OK) {
+    ssd_graph_destroy(g);
+    return st;
   }
   *out = g;
   return SSD_OK;
 }
 
-static bool graph_prefetches(const ssd_graph* g) { return g->kv->prefetch && g->exec[1]; }
+static bool graph_prefetches(const ssd_graph* g) { return g->wide && g->kv->prefetch; }
 
 extern "C" ssd_status ssd_graph_prefetch(const ssd_graph* g, int32_t* inside) {
   if (!g || !inside) return fail(SSD_E_INVALID_ARG, "null argument");
@@ -1144,10 +1164,22 @@ extern "C" ssd_status ssd_graph_prefetch(const ssd_graph* g, int32_t* inside) {
 }
 
 extern "C" ssd_status ssd_graph_launch(ssd_graph* g, void* stream) {
-  if (!g || !g->exec[0]) return fail(SSD_E_INVALID_ARG, "null graph");
-  const ssd_status st = start_pass_prefetch(g->m, g->kv, g->n, g->fused, g->gemm_path);
+  if (!g || (!g->exec[0] && !g->exec[1])) return fail(SSD_E_INVALID_ARG, "null graph");
+  const int kind = graph_prefetches(g);
+  ssd_status st = SSD_OK;
+  if (!g->exec[kind]) {
+    // (a wide pass: one kernel per sub-layer, under the GEMM path of its capture)
+    ssd_kv* kv = g->kv;
+    const int mode = kv->pass_mode, path = kv->gemm_path;
+    kv->pass_mode = 1;
+    kv->gemm_path = g->gemm_path;
+    st = capture_kind(g, kind);
+    kv->pass_mode = mode;
+    kv->gemm_path = path;
+  }
+  if (st == SSD_OK) st = start_pass_prefetch(g->m, g->kv, g->n, g->fused, g->gemm_path);
   if (st != SSD_OK) return st;
-  HIP_TRY(hipGraphLaunch(g->exec[graph_prefetches(g)], (hipStream_t)stream));
+  HIP_TRY(hipGraphLaunch(g->exec[kind], (hipStream_t)stream));
   g->kv->resid_fused = g->fused;
   g->kv->last_n = g->n;
   g->kv->last_layers = g->m->cfg.n_layer;

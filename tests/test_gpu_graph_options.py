@@ -31,7 +31,8 @@ def test_prefetch_option_at_launch(n, captured, q8):
     greedy = s.capture_verify_greedy(P, toks, par, lg, out)
     path, plen, nxt = s.accept(toks, par, torch.from_numpy(want).cuda())
     for on in (1, 0, 0, 1):
-        s.set_options(weight_prefetch=on)
+        # (the pass mode and GEMM path of the capture hold, whatever they are at a launch)
+        s.set_options(pass_mode=ssd.PASS_AUTO, gemm_path=on, weight_prefetch=on)
         for g in (plain, greedy):
             assert g.prefetches() == (bool(on) and n > 64)
             lg.zero_()
@@ -39,4 +40,5 @@ def test_prefetch_option_at_launch(n, captured, q8):
             assert np.array_equal(lg.cpu().numpy(), want)
         m = int(plen.item())
         assert int(out[1].item()) == m and torch.equal(out[0][:m], path[:m]) and torch.equal(out[2], nxt.reshape(1))
+        assert s.get_options() == {"pass_mode": ssd.PASS_AUTO, "gemm_path": on, "weight_prefetch": on}
     assert s.error_count() == 0
