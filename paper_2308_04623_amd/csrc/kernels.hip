@@ -2515,29 +2515,36 @@ __device__ __forceinline__ double scan256(double v, double* red4, double& total)
   return before + (inc - v);
 }
 
-__global__ __launch_bounds__(256) void cdf_part_kernel(CdfPickArgs a) {
-  __shared__ double red[4];
-  const int c = blockIdx.x, r = blockIdx.y, tid = threadIdx.x, V = a.V;
-  const float* row = a.logits + (size_t)a.rows[r] * V;
-  const int v0 = c * kPickChunk;
+// chunk c of a row of V: its maximum and its sum of exp(x / T - maximum), in
+// every thread
+__device__ __forceinline__ void cdf_chunk(const float* row, int V, float T, int c, double* red4, double& mx,
+                                          double& tot) {
+  const int tid = threadIdx.x, v0 = c * kPickChunk;
   float x[kPickPer];
 #pragma unroll
   for (int k = 0; k < kPickPer; ++k) x[k] = row[min(v0 + tid + 256 * k, V - 1)];
-  double mx = -INFINITY;
+  mx = -INFINITY;
 #pragma unroll
   for (int k = 0; k < kPickPer; ++k)
-    if (v0 + tid + 256 * k < V) mx = fmax(mx, (double)x[k] / a.T);
+    if (v0 + tid + 256 * k < V) mx = fmax(mx, (double)x[k] / T);
   for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
-  if ((tid & 63) == 0) red[tid >> 6] = mx;
+  if ((tid & 63) == 0) red4[tid >> 6] = mx;
   __syncthreads();
-  mx = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+  mx = fmax(fmax(red4[0], red4[1]), fmax(red4[2], red4[3]));
   __syncthreads();
-  double e = 0.0, tot;
+  double e = 0.0;
 #pragma unroll
   for (int k = 0; k < kPickPer; ++k)
-    if (v0 + tid + 256 * k < V && mx != -INFINITY) e += exp((double)x[k] / a.T - mx);
-  scan256(e, red, tot);
-  if (tid == 0) {
+    if (v0 + tid + 256 * k < V && mx != -INFINITY) e += exp((double)x[k] / T - mx);
+  scan256(e, red4, tot);
+}
+
+__global__ __launch_bounds__(256) void cdf_part_kernel(CdfPickArgs a) {
+  __shared__ double red[4];
+  const int c = blockIdx.x, r = blockIdx.y;
+  double mx, tot;
+  cdf_chunk(a.logits + (size_t)a.rows[r] * a.V, a.V, a.T, c, red, mx, tot);
+  if (threadIdx.x == 0) {
     double* p = a.part + ((size_t)r * a.C + c) * 2;
     p[0] = mx;
     p[1] = tot;
@@ -2550,11 +2557,18 @@ __global__ __launch_bounds__(256) void cdf_pick_kernel(CdfPickArgs a) {
   const int q = blockIdx.x, tid = threadIdx.x, V = a.V, C = a.C, r = a.qrow[q];
   const float* row = a.logits + (size_t)a.rows[r] * V;
   const double U = a.U[q];
-  // the chunks' (maximum, sum): in LDS, or past 2M ids where they lie
+  // the chunks' (maximum, sum): in LDS, or past 2M ids where they lie; a row
+  // of one chunk takes its own here (50 ids: 13.6 us a call with a launch for
+  // it, 11.2 without)
   const double* part = a.part + (size_t)r * C * 2;
   const bool in_lds = C <= kPickMaxChunks;
   double M = -INFINITY, S = 0.0, run = 0.0;
-  if (in_lds) {
+  if (C == 1) {
+    double tot;
+    cdf_chunk(row, V, a.T, 0, red, M, tot);
+    if (tid == 0) ps[0] = tot * exp(M - M);  // (as below: NaN where no entry is finite)
+    __syncthreads();
+  } else if (in_lds) {
     for (int c = tid; c < C; c += 256) {
       pm[c] = part[2 * c];
       ps[c] = part[2 * c + 1];
@@ -2627,7 +2641,7 @@ hipError_t launch_cdf_pick(const CdfPickArgs& a, hipStream_t s) {
   if (a.n < 1 || a.n > kMaxPicks || a.nrows < 1 || a.nrows > a.n || a.V < 1 || !(a.T > 0.f) || !a.part)
     return hipErrorInvalidValue;
   if (a.C != (a.V + kPickChunk - 1) / kPickChunk) return hipErrorInvalidValue;
-  cdf_part_kernel<<<dim3(a.C, a.nrows), 256, 0, s>>>(a);
+  if (a.C > 1) cdf_part_kernel<<<dim3(a.C, a.nrows), 256, 0, s>>>(a);
   cdf_pick_kernel<<<a.n, 256, 0, s>>>(a);
   return hipGetLastError();
 }
