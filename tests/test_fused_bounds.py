@@ -32,6 +32,7 @@ A_Q = NWV * 2 * DH * 4
 WST = 16 * 1024
 WST_FRAGS = (73728 + 34816 + 4096 - WST) // 1024
 WO_FRAGS = 24
+SM_ACT = 16 * 1024
 LW_SLOTS = 12
 PLAN_STRIDE = 32
 
@@ -63,7 +64,7 @@ def check_pass(H, d, M, V, L, N, P, max_ctx, max_nodes, q8=False):
     c = Check()
     FB = 512 if q8 else 1024                        # fragment bytes
     nt = (N + 15) // 16
-    NT = 1 if nt == 1 else 2 if nt == 2 else 4          # the kernel template serving nt tiles
+    NT = nt                                         # the kernel template serving nt tiles
     tab, xh, xf = ssd.fused_plan(H, d, M, V, nt)
     KCd, KCm, RBd = d // 32, M // 32, d // 16
     att_parts = (max_ctx + ATT_ROWS - 1) // ATT_ROWS + 1
@@ -78,6 +79,22 @@ def check_pass(H, d, M, V, L, N, P, max_ctx, max_nodes, q8=False):
     }
     c.rng("LDS size", 0, lds_bytes(L) - 1, LDS_LIMIT + 1)
     c.rng("GEMM reduction below the staged weights", 0, (QW - 1) * 64 * 16 * 4 - 1 + 0, WST + 1)
+    if N == 1:
+        # a single node: every workgroup keeps the residual row above the parameter table, and the GEMM inputs
+        # (LayerNorm row, merged heads; one fragment tile, of which the node's slots are written) from SM_ACT on
+        ofs = A_REGION + A_PART + A_Q + 128 + PLAN_STRIDE * 4 + L * LW_SLOTS * 8
+        c.rng("one node: residual row (LDS)", ofs, ofs + 4 * d - 1, lds_bytes(L))
+        c.rng("one node: GEMM reduction below its input", 0, (NWV - QW) * 16 * 16 * 4 - 1, SM_ACT)
+        c.rng("one node: LayerNorm row (LDS)", SM_ACT + 2 * act_index(0, 0, KCd),
+              SM_ACT + 2 * (act_index(0, d - 4, KCd) + 3) + 1, A_REGION + A_PART)
+        c.rng("one node: GEMM input fragments (LDS)", SM_ACT, SM_ACT + (KCd - 1) * 1024 + 1023, A_REGION + A_PART)
+        for x in range(XCD):
+            for h in range(xh[2 * x], xh[2 * x + 1]):
+                word = lambda k: ((k >> 5) * 512 + 128 * ((k & 31) >> 3) + (k & 7)) >> 1
+                c.rng("one node: merged head (LDS)", SM_ACT + 4 * word(h * DH), SM_ACT + 4 * word(h * DH + DH - 2) + 3,
+                      SM_ACT + KCd * 1024)
+                c.rng("one node: merge parts", h * 4 * (S + 1) * 16 * AREC, (h * 4 * (S + 1) + S) * 16 * AREC + AREC - 1,
+                      sizes["apart"])
     for x in range(XCD):
         act_base = x * MAXN * d
         kh0, kh1 = 2 * xh[2 * x], 2 * xh[2 * x + 1]
