@@ -351,14 +351,15 @@ ssd_status ssd_tree_prep(const int32_t *parent_idx, int32_t n, int32_t *depth, u
  *   gemm_path: the per-sub-layer kernels' weight GEMMs, bfloat16 models
  *     only: 0 = automatic (by node count), 1 = vector ALU, 2 = matrix cores.
  *   weight_prefetch: 1 = every per-sub-layer bfloat16 pass of at most 64
- *     nodes that the session enqueues (or a graph of it replays) gets a
- *     prefetcher kernel on a stream of the session's own; it follows progress
- *     signals the pass's kernels raise and loads each weight GEMM's fragments
- *     into the L2 of the XCD whose workgroups will read them, a few kernels
- *     ahead.  The pass never waits for it; it stops waiting for signals 50 ms
- *     after it starts.  In wider trees' passes the LayerNorm and attention
- *     kernels load the next weight GEMMs' fragments themselves.  0 = off.  The
- *     setting in force when a pass is enqueued or a graph launched counts.
+ *     nodes, or with its GEMMs on the vector ALU, that the session enqueues (or
+ *     a graph of it replays) gets a prefetcher kernel on a stream of the
+ *     session's own; it follows progress signals the pass's kernels raise and
+ *     loads each weight GEMM's fragments into the L2 of the XCD whose workgroups
+ *     will read them, a few kernels ahead.  The pass never waits for it; it
+ *     stops waiting for signals 50 ms after it starts.  In the other passes
+ *     (wider trees on the matrix cores) the LayerNorm and attention kernels load
+ *     the next weight GEMMs' fragments themselves.  0 = off.  The setting in
+ *     force when a pass is enqueued or a graph launched counts.
  *     Results are bitwise the same either way.  ssd_kv_destroy waits for the
  *     session's prefetchers.
  * A captured graph keeps the pass mode and GEMM path in force when it was

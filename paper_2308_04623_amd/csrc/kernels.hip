@@ -1493,13 +1493,14 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
 //   operand.  Each leaves a part (max, sum of exponentials, unnormalised
 //   output) per (head, chunk, node).
 // attn_merge_kernel: DH / 4 threads (four output dims each) per (node, head): the
-//   chunks' parts merged in chunk order, then the records of its root path's
-//   full 32-key blocks, then the rest of that path (its ancestors and itself
-//   in the tree scratch, root first) folded in RK keys
+//   chunks' parts merged in chunk order, then (more than kPathNodes nodes) the
+//   records of its root path's full 32-key blocks, then the rest of that path
+//   (its ancestors and itself in the tree scratch, root first) folded in RK keys
 //   at a time, each score four products per thread then a butterfly sum
 //   over the pair's threads; the output is written in the next GEMM's input
 //   layout, four columns per store.  The chunking depends on P
-//   only, so a node's result does not depend on the rest of the tree.
+//   only, the use of records on a node's depth and the node count, so a node's
+//   result does not depend on which other nodes the tree holds.
 
 constexpr int AT_STAGE = kAttnMaxChunk;  // cache rows staged per block
 constexpr int AT_MAXW = 8;               // waves per block
@@ -1750,8 +1751,8 @@ __global__ __launch_bounds__(64 * AT_MAXW) void attn_split_kernel(AttnArgs a, Pf
 // on its own path only.  The merge walks what is left of the path, at most 31
 // keys.
 // A 512-token chain, per layer: the merge alone, 8 keys of one node at a time,
-// 124 us (64 dependent rounds for the last nodes); this kernel and the merge
-// 13.8 + 15.5 us.
+// 124 us (64 dependent rounds for the last nodes); this kernel and the merge,
+// which then also brings in the down-projection's weights, 14.0 + 17.4 us.
 constexpr int kPathWaves = kPathChunk / 32;
 
 template <int DH>

@@ -62,6 +62,8 @@ struct GemmCfg {
 struct WideCfg {
   int rbt, tt, S;
 };
+// the choice for a GEMM: tile = {rbt, tt, S}
+void wide_tile(int kind, int M, int K, int N, bool q8, int* tile);
 
 // A later wide GEMM's weights, for the kernels before it to bring into the
 // L2s that will be read (see prefetch_weights in kernels.hip)
@@ -73,9 +75,6 @@ struct Prefetch {
   int own;                 // the kernel's own blocks (LayerNorm)
   int first;               // the first block that prefetches (a multiple of 8)
 };
-
-// its choice for a GEMM: {row blocks, node tiles, k-splits}
-void wide_tile(int kind, int M, int K, int N, bool q8, int* tile);
 
 // launch geometry of one bf16 GEMM: block (bx, by) owns weight row blocks
 // bx RB .. bx RB + RB - 1 (rows past RBtot read row block RBtot - 1 and are
