@@ -562,8 +562,8 @@ extern "C" ssd_status ssd_kv_create(const ssd_model* m, int32_t max_ctx, int32_t
   const size_t ap_bf16 = (size_t)c.n_head * attn_max_nsplit(max_ctx, c.n_head) * max_nodes * (m->dh + 4);
   const size_t o_apart = take((m->f32 ? ap_f32 : ap_bf16) * 4);
   // root-path records of the bf16 kernels (a node's depth is below max_nodes)
-  const size_t o_ppart =
-      take(m->f32 || max_nodes <= kPathNodes ? 0 : (size_t)c.n_head * attn_npath(max_nodes - 1) * max_nodes * (m->dh + 4) * 4);
+  const size_t pp = (size_t)c.n_head * attn_npath(max_nodes - 1) * max_nodes * (m->dh + 4) * 4;
+  const size_t o_ppart = take(m->f32 || max_nodes <= kPathNodes ? 0 : pp);
   const size_t o_tree = take(stage_bytes(max_nodes));
   const size_t o_at = take((size_t)3 * max_nodes * 4), o_am = take((size_t)max_nodes * 4);
   const size_t o_amw = take(
