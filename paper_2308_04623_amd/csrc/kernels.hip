@@ -1045,25 +1045,21 @@ GemmCfg gemm_cfg(int N, int vec, int kind) {
   return c;
 }
 
-int gemm_split_kc(int M, int K, int N, int vec, int want_split, int* splits) {
-  const int KC = K / 32;
-  if (!want_split) {
-    *splits = 1;
-    return KC;
-  }
+GemmPlan gemm_plan(int kind, int vec, int M, int K, int N, bool q8) {
+  GemmPlan p{};
+  const int KC = K / 32, RB = (M + 15) / 16;
+  int S = 1;
   if (gemm_wide(vec, N)) {
-    const int S = wide_cfg(EPI_PARTIAL, (M + 15) / 16, KC, N, false).S;
-    const int kcs = (KC + S - 1) / S;
-    *splits = (KC + kcs - 1) / kcs;
-    return kcs;
+    p.wide = wide_cfg(kind, RB, KC, N, q8);
+    S = p.wide.S;
+  } else if (kind == EPI_PARTIAL) {
+    const int rb = gemm_cfg(N, vec, EPI_PARTIAL).rb;
+    const int gx = (RB + rb - 1) / rb;
+    while (S * gx < 256 && S < kMaxSplits) S *= 2;  // a power of two with S * gx >= 256 workgroups
   }
-  const int rb = gemm_cfg(N, vec, EPI_PARTIAL).rb;
-  const int gx = ((M + 15) / 16 + rb - 1) / rb;
-  int S = 1;  // a power of two with S * gx >= 256 workgroups
-  while (S * gx < 256 && S < kMaxSplits) S *= 2;
-  const int kcs = (KC + S - 1) / S;
-  *splits = (KC + kcs - 1) / kcs;
-  return kcs;
+  p.kcs = (KC + S - 1) / S;
+  p.S = (KC + p.kcs - 1) / p.kcs;
+  return p;
 }
 
 // row blocks per workgroup of the LM head (EPI_LOGITS on the matrix cores):
@@ -1107,18 +1103,15 @@ static void gemm_go(int kind, const GemmGeom& g, const void* Wp, const uint16_t*
   }
 }
 
-Prefetch wide_prefetch(int kind, const void* Wp, int M, int K, int N, bool q8) {
+Prefetch wide_prefetch(const GemmPlan& p, int M, int K, bool q8) {
   const int KC = K / 32, RB = (M + 15) / 16, frag = q8 ? 512 : 1024;
-  const WideCfg c = wide_cfg(kind, RB, KC, N, q8);
-  const int kcs = (KC + c.S - 1) / c.S;
   Prefetch pf{};
-  pf.W = (const unsigned char*)Wp;
   pf.row_bytes = (size_t)KC * frag;
-  pf.step = kcs * frag;
+  pf.step = p.kcs * frag;
   pf.RBtot = RB;
-  pf.rbt = c.rbt;
-  pf.gx = (RB + c.rbt - 1) / c.rbt;
-  pf.gy = (KC + kcs - 1) / kcs;
+  pf.rbt = p.wide.rbt;
+  pf.gx = (RB + p.wide.rbt - 1) / p.wide.rbt;
+  pf.gy = p.S;
   return pf;
 }
 
@@ -1135,10 +1128,11 @@ static void wide_go(int grid, const void* Wp, int KC, int RBtot, int NT, int kcs
 // 256 nodes: 10.6 us, 4 waves 10.9; at 6 their tiles are summed in two rounds of
 // LDS), 4 at 8 node tiles; as many k-steps as registers allow.  The 8-bit LM head, whose many
 // workgroups come in rounds, runs 4 waves (128 nodes 34 us, 8 waves 42 us).
-static hipError_t launch_gemm_wide(int kind, const void* Wp, int M, int K, const uint16_t* act, int kcs,
+static hipError_t launch_gemm_wide(int kind, const void* Wp, int M, int K, const uint16_t* act, const GemmPlan& p,
                                    const Epi& ep, hipStream_t s) {
-  const int KC = K / 32, RB = (M + 15) / 16, NT = (ep.N + 15) / 16;
-  const WideCfg c = wide_cfg(kind, RB, KC, ep.N, ep.wscale != nullptr);
+  const WideCfg& c = p.wide;
+  if (c.rbt < 1 || c.tt < 1) return hipErrorInvalidValue;
+  const int KC = K / 32, RB = (M + 15) / 16, NT = (ep.N + 15) / 16, kcs = p.kcs;
   const int gx = (RB + c.rbt - 1) / c.rbt, gt = (NT + c.tt - 1) / c.tt, gy = (KC + kcs - 1) / kcs;
   if (8 % gy || (kind != EPI_PARTIAL && gy != 1)) return hipErrorInvalidValue;
   const int grid = wide_blocks(gx, gt, gy);
@@ -1167,12 +1161,12 @@ static hipError_t launch_gemm_wide(int kind, const void* Wp, int M, int K, const
   return hipGetLastError();
 }
 
-hipError_t launch_gemm_bf16(int kind, int vec, const void* Wp, int M, int K, const uint16_t* act, int kcs,
-                            const Epi& ep, hipStream_t s) {
-  if (kcs <= 0) return hipErrorInvalidValue;
+hipError_t launch_gemm_bf16(int kind, int vec, const void* Wp, int M, int K, const uint16_t* act,
+                            const GemmPlan& p, const Epi& ep, hipStream_t s) {
+  if (p.kcs <= 0) return hipErrorInvalidValue;
   if (ep.N > (vec ? 16 : 1024)) return hipErrorInvalidValue;
-  if (gemm_wide(vec, ep.N)) return launch_gemm_wide(kind, Wp, M, K, act, kcs, ep, s);
-  const GemmGeom g = gemm_geom(kind, vec, M, K, ep.N, kcs);
+  if (gemm_wide(vec, ep.N)) return launch_gemm_wide(kind, Wp, M, K, act, p, ep, s);
+  const GemmGeom g = gemm_geom(kind, vec, M, K, ep.N, p.kcs);
   if (kind == EPI_LOGITS && !vec) {
     switch (gemm_cfg(ep.N, 0, kind).nt) {
       case 1: gemm_launch<1, 8, EPI_LOGITS, false, 0, 3>(g, Wp, act, ep, s); break;

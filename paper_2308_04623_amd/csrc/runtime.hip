@@ -707,12 +707,12 @@ static size_t fill_stage(char* host, int P, const int32_t* tokens, const int32_t
 // (in node groups of 16) and the matrix-core kernels otherwise.
 static int gemm_vec(int path, int n) { return (path == 0 ? (n <= kVecMaxNodes ? 1 : 2) : path) == 1; }
 
-// k-steps per split of a weight GEMM over n nodes (one k-split for every
-// node group, so all nodes leave the same partials)
-static int gemm_kcs(int path, int n, int kind, int rows, int K) {
+// the plan of a bf16 weight GEMM over n nodes (one k-split for every node
+// group, so all nodes leave the same partials; float32 models have none)
+static GemmPlan plan_gemm(const ssd_model* m, int path, int n, int kind, int rows, int K) {
+  if (m->f32) return GemmPlan{};
   const int vec = gemm_vec(path, n);
-  int S = 1;
-  return gemm_split_kc(rows, K, vec ? std::min(n, 16) : n, vec, kind == EPI_PARTIAL, &S);
+  return gemm_plan(kind, vec, rows, K, vec ? std::min(n, 16) : n, m->q8);
 }
 
 // The prefetcher's plan for a bf16 pass over n nodes: the launch geometry of
@@ -725,7 +725,8 @@ static PrefetchPlan prefetch_plan(const ssd_model* m, const ssd_kv* kv, int path
   const int kinds[4] = {EPI_QKV, EPI_PARTIAL, EPI_GELU, EPI_PARTIAL};
   const int rows[4] = {3 * d, d, M, d}, Ks[4] = {d, d, d, M};
   for (int k = 0; k < 4; ++k) {
-    const GemmGeom g = gemm_geom(kinds[k], vec, rows[k], Ks[k], nn, gemm_kcs(path, n, kinds[k], rows[k], Ks[k]));
+    const GemmGeom g = gemm_geom(kinds[k], vec, rows[k], Ks[k], nn,
+                                 plan_gemm(m, path, n, kinds[k], rows[k], Ks[k]).kcs);
     // (the prefetcher reads 1 KB fragments: an 8-bit row block is KC / 2 of
     // them, K being a multiple of 64; a split's range rounds to whole ones)
     if (m->q8) pp.geo[k] = PfGeom{g.KC / 2, g.RBtot, g.RB, (g.kcs + 1) / 2, g.gx, g.gx * g.gy};
@@ -768,12 +769,12 @@ static ssd_status start_pass_prefetch(const ssd_model* m, ssd_kv* kv, int n, boo
   return SSD_OK;
 }
 
-static hipError_t run_gemm(const ssd_model* m, int path, int n, int kind, const void* Wraw, const void* Wp,
-                           const float* wscale, int rows, int K, const void* act, const Epi& ep, hipStream_t s) {
+static hipError_t run_gemm(const ssd_model* m, int path, int n, int kind, const GemmPlan& plan, const void* Wraw,
+                           const void* Wp, const float* wscale, int rows, int K, const void* act, const Epi& ep,
+                           hipStream_t s) {
   if (m->f32) return launch_gemm_f32(kind, (const float*)Wraw, rows, K, (const float*)act, K, ep, s);
   const int vec = gemm_vec(path, n);
   const int group = vec ? 16 : n;
-  const int kcs = gemm_kcs(path, n, kind, rows, K);
   for (int n0 = 0; n0 < n; n0 += group) {
     Epi e2 = ep;
     e2.node0 = n0;
@@ -782,19 +783,10 @@ static hipError_t run_gemm(const ssd_model* m, int path, int n, int kind, const 
     const uint16_t* a = (const uint16_t*)act + (size_t)(n0 / 16) * (K / 32) * 512;
     e2.sig = n0 == 0 ? ep.sig : nullptr;  // one signal per GEMM
     e2.wscale = m->q8 ? wscale : nullptr;
-    hipError_t r = launch_gemm_bf16(kind, vec, Wp, rows, K, a, kcs, e2, s);
+    hipError_t r = launch_gemm_bf16(kind, vec, Wp, rows, K, a, plan, e2, s);
     if (r != hipSuccess) return r;
   }
   return hipSuccess;
-}
-
-// number of split-K partials a residual GEMM leaves for the next LayerNorm
-static int resid_splits(const ssd_model* m, int path, int n, int rows, int K) {
-  if (m->f32) return 0;
-  const int vec = gemm_vec(path, n);
-  int S = 1;
-  gemm_split_kc(rows, K, vec ? std::min(n, 16) : n, vec, 1, &S);
-  return S;
 }
 
 // l0 > 0: the pass starts at layer l0 from the residual stream x_in
@@ -869,7 +861,9 @@ static ssd_status enqueue_verify(const ssd_model* m, ssd_kv* kv, int32_t P, int3
   // fp32 models add residuals inside the GEMM; bf16 models leave split-K
   // partials that the next LayerNorm adds (with the bias)
   const int kind_res = f32 ? EPI_RESID : EPI_PARTIAL;
-  const int s_o = resid_splits(m, gp, n, d, d), s_pr = resid_splits(m, gp, n, d, M);
+  const GemmPlan pl_qkv = plan_gemm(m, gp, n, EPI_QKV, 3 * d, d), pl_o = plan_gemm(m, gp, n, kind_res, d, d),
+                 pl_fc = plan_gemm(m, gp, n, EPI_GELU, M, d), pl_pr = plan_gemm(m, gp, n, kind_res, d, M),
+                 pl_head = plan_gemm(m, gp, n, EPI_LOGITS, V, d);
   const size_t kv_layer = (size_t)H * DH;  // elements per K/V row across heads
 
   // (the staged depths, see fill_stage)
@@ -882,10 +876,10 @@ static ssd_status enqueue_verify(const ssd_model* m, ssd_kv* kv, int32_t P, int3
   Prefetch pf_qkv{}, pf_o{}, pf_fc{}, pf_pr{};
   const bool pf_on = prefetch_on && pass_prefetches(m, gp, n);
   if (pf_on) {
-    pf_qkv = wide_prefetch(EPI_QKV, nullptr, 3 * d, d, n, q8);
-    pf_o = wide_prefetch(EPI_PARTIAL, nullptr, d, d, n, q8);
-    pf_fc = wide_prefetch(EPI_GELU, nullptr, M, d, n, q8);
-    pf_pr = wide_prefetch(EPI_PARTIAL, nullptr, d, M, n, q8);
+    pf_qkv = wide_prefetch(pl_qkv, 3 * d, d, q8);
+    pf_o = wide_prefetch(pl_o, d, d, q8);
+    pf_fc = wide_prefetch(pl_fc, M, d, q8);
+    pf_pr = wide_prefetch(pl_pr, d, M, q8);
   }
   auto prefetch = [&](Prefetch pf, const std::vector<const void*>& w, int l) {
     if (pf_on) pf.W = (const unsigned char*)w[l];
@@ -909,7 +903,7 @@ static ssd_status enqueue_verify(const ssd_model* m, ssd_kv* kv, int32_t P, int3
     e.H = H;
     e.DH = DH;
     e.max_nodes = maxn;
-    HIP_TRY(run_gemm(m, gp, n, EPI_QKV, m->w_qkv[l], f32 ? nullptr : m->p_qkv[l], q8 ? m->s_qkv[l] : nullptr,
+    HIP_TRY(run_gemm(m, gp, n, EPI_QKV, pl_qkv, m->w_qkv[l], f32 ? nullptr : m->p_qkv[l], q8 ? m->s_qkv[l] : nullptr,
                      3 * d, d, kv->act_a, e, s));
 
     AttnArgs a{};
@@ -952,10 +946,10 @@ static ssd_status enqueue_verify(const ssd_model* m, ssd_kv* kv, int32_t P, int3
     eo.x = kv->x;
     eo.part = kv->part;
     eo.part_stride = (long long)pstride;
-    HIP_TRY(run_gemm(m, gp, n, kind_res, m->w_o[l], f32 ? nullptr : m->p_o[l], q8 ? m->s_o[l] : nullptr, d, d,
-                     kv->act_o, eo, s));
+    HIP_TRY(run_gemm(m, gp, n, kind_res, pl_o, m->w_o[l], f32 ? nullptr : m->p_o[l], q8 ? m->s_o[l] : nullptr, d,
+                     d, kv->act_o, eo, s));
 
-    HIP_TRY(launch_ln(f32, kv->x, n, d, kv->part, f32 ? 0 : s_o, pstride, m->b_o[l], m->ln2_g[l], m->ln2_b[l],
+    HIP_TRY(launch_ln(f32, kv->x, n, d, kv->part, f32 ? 0 : pl_o.S, pstride, m->b_o[l], m->ln2_g[l], m->ln2_b[l],
                       c.ln_eps, kv->act_a, ld_d, sig, kv->d_err, prefetch(pf_fc, m->p_fc, l), s));
     Epi ef{};
     ef.sig = sig;
@@ -966,8 +960,8 @@ static ssd_status enqueue_verify(const ssd_model* m, ssd_kv* kv, int32_t P, int3
     ef.d = d;
     ef.out = kv->act_f;
     ef.ldo = ld_m;
-    HIP_TRY(run_gemm(m, gp, n, EPI_GELU, m->w_fc[l], f32 ? nullptr : m->p_fc[l], q8 ? m->s_fc[l] : nullptr, M, d,
-                     kv->act_a, ef, s));
+    HIP_TRY(run_gemm(m, gp, n, EPI_GELU, pl_fc, m->w_fc[l], f32 ? nullptr : m->p_fc[l], q8 ? m->s_fc[l] : nullptr, M,
+                     d, kv->act_a, ef, s));
 
     Epi ep{};
     ep.sig = sig;
@@ -978,9 +972,9 @@ static ssd_status enqueue_verify(const ssd_model* m, ssd_kv* kv, int32_t P, int3
     ep.x = kv->x;
     ep.part = kv->part;
     ep.part_stride = (long long)pstride;
-    HIP_TRY(run_gemm(m, gp, n, kind_res, m->w_pr[l], f32 ? nullptr : m->p_pr[l], q8 ? m->s_pr[l] : nullptr, d, M,
-                     kv->act_f, ep, s));
-    pend_S = f32 ? 0 : s_pr;
+    HIP_TRY(run_gemm(m, gp, n, kind_res, pl_pr, m->w_pr[l], f32 ? nullptr : m->p_pr[l], q8 ? m->s_pr[l] : nullptr, d,
+                     M, kv->act_f, ep, s));
+    pend_S = f32 ? 0 : pl_pr.S;
     pend_bias = m->b_pr[l];
   }
   HIP_TRY(launch_ln(f32, kv->x, n, d, kv->part, pend_S, pstride, pend_bias, m->lnf_g, m->lnf_b, c.ln_eps, kv->act_a,
@@ -992,7 +986,7 @@ static ssd_status enqueue_verify(const ssd_model* m, ssd_kv* kv, int32_t P, int3
   eh.d = d;
   eh.logits = logits;
   eh.ldl = V;
-  HIP_TRY(run_gemm(m, gp, n, EPI_LOGITS, m->wte, f32 ? nullptr : m->p_head, m->s_head, V, d, kv->act_a, eh, s));
+  HIP_TRY(run_gemm(m, gp, n, EPI_LOGITS, pl_head, m->wte, f32 ? nullptr : m->p_head, m->s_head, V, d, kv->act_a, eh, s));
   return SSD_OK;
 }
 
@@ -1247,7 +1241,8 @@ extern "C" ssd_status ssd_launch_gemm(const ssd_model* m, ssd_kv* kv, int32_t wh
   }
   e.M = rows;
   (void)lda;
-  HIP_TRY(run_gemm(m, kv->gemm_path, n_nodes, kind, Wraw, Wp, wscale, rows, K, act, e, (hipStream_t)stream));
+  HIP_TRY(run_gemm(m, kv->gemm_path, n_nodes, kind, plan_gemm(m, kv->gemm_path, n_nodes, kind, rows, K), Wraw, Wp, wscale,
+                   rows, K, act, e, (hipStream_t)stream));
   return SSD_OK;
 }
 

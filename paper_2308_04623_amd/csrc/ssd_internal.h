@@ -62,6 +62,11 @@ struct GemmCfg {
 struct WideCfg {
   int rbt, tt, S;
 };
+// what every launch of one weight GEMM in a pass shares (gemm_plan)
+struct GemmPlan {
+  int kcs, S;    // k-steps per split, splits (1 unless EPI_PARTIAL)
+  WideCfg wide;  // more than 64 nodes on the matrix cores
+};
 // the choice for a GEMM: tile = {rbt, tt, S}
 void wide_tile(int kind, int M, int K, int N, bool q8, int* tile);
 
@@ -184,22 +189,24 @@ hipError_t launch_ln(int f32, float* x, int N, int d, const float* part, int S, 
 hipError_t launch_gemm_f32(int kind, const float* W, int M, int K, const float* act, int lda, const Epi& ep,
                            hipStream_t s);
 GemmCfg gemm_cfg(int N, int vec, int kind);
-// k-steps per split and number of splits (EPI_PARTIAL only; 1 otherwise)
-int gemm_split_kc(int M, int K, int N, int vec, int want_split, int* splits);
+// (the search for a wide tile takes 0.2 us of host time at GPT-2-L's residual
+// GEMMs: a pass plans each of its GEMMs once, not per layer)
+GemmPlan gemm_plan(int kind, int vec, int M, int K, int N, bool q8);
 // whether a matrix-core GEMM over N nodes (of one launch) takes the
 // wide-tree kernel (row blocks x node tiles per workgroup)
 bool gemm_wide(int vec, int N);
 GemmGeom gemm_geom(int kind, int vec, int M, int K, int N, int kcs);
 // Wp: weights packed in 16x32 float16 fragments (see pack), or, with
 // ep.wscale set, in 16x32 8-bit fragments (see pack_q8); act: activations of
-// this launch's first node in fragment order (see st_act); kcs k-steps per
-// split (grid.y = ceil(K/32 / kcs))
-hipError_t launch_gemm_bf16(int kind, int vec, const void* Wp, int M, int K, const uint16_t* act, int kcs,
-                            const Epi& ep, hipStream_t s);
+// this launch's first node in fragment order (see st_act); p: gemm_plan's for
+// this launch's node count (one plan for every node group of the vector path)
+hipError_t launch_gemm_bf16(int kind, int vec, const void* Wp, int M, int K, const uint16_t* act,
+                            const GemmPlan& p, const Epi& ep, hipStream_t s);
 // pf: what the split and the merge kernel of a bf16 model prefetch
 hipError_t launch_attn(int f32, int DH, const AttnArgs& a, const Prefetch (&pf)[2], hipStream_t s);
-// the prefetch of a wide GEMM (more than 64 nodes) of M x K packed weights
-Prefetch wide_prefetch(int kind, const void* Wp, int M, int K, int N, bool q8);
+// the prefetch of a wide GEMM (more than 64 nodes) of M x K packed weights (W
+// to be filled in)
+Prefetch wide_prefetch(const GemmPlan& p, int M, int K, bool q8);
 hipError_t launch_prefetcher(const PrefetchPlan& pp, hipStream_t s);
 // bad: device counter of packed 16-byte groups holding a weight past float16's range
 hipError_t launch_pack_bf16(const uint16_t* W, int M, int K, void* out, unsigned* bad, hipStream_t s);
