@@ -2145,6 +2145,10 @@ __global__ __launch_bounds__(64) void argmax_final_kernel(const float* __restric
 // k rounds of "best not yet taken" (ties to the lower index).
 // 32 rows of 50257, k = 2: 13.1 + 10.8 us with every chunk selecting kTopKMax
 // and one lane reading the chunks' sums one after the other; now 5.7 + 5.0 us.
+// The merge holds the lists in registers and moves one up per round: with the
+// next entry loaded in each round a call over 50 ids took 16.5 us for k = 8 (1
+// row; 64 rows 17.5), 1 us more than with every chunk selecting kTopKMax; now
+// 15.2 (16.1), and k = 2 over 64 rows of 50257 11.8 -> 11.2 us.
 struct TopkPart {
   float v[kTopKMax];
   int i[kTopKMax];
@@ -2231,28 +2235,33 @@ __global__ __launch_bounds__(256) void topk_part_kernel(const float* __restrict_
   }
 }
 
+// MAXC: chunks per lane (1 up to 64 chunks, 131,072 ids)
+template <int MAXC>
 __global__ __launch_bounds__(64) void topk_final_kernel(const TopkPart* __restrict__ parts, int V, int C, int k,
                                                         int* __restrict__ idx, float* __restrict__ val,
                                                         float* __restrict__ lse) {
   const int n = blockIdx.x, lane = threadIdx.x;
   const TopkPart* p = parts + (size_t)n * C;
-  // lane takes chunks lane, lane + 64, ...: their (max, sum), and the head of
-  // each chunk's sorted list, all loaded at once
-  constexpr int MAXC = 4;  // chunks per lane (vocab up to 64 * 4 * kArgmaxChunk)
-  int cur[MAXC], hi[MAXC];
-  float hv[MAXC], cm[MAXC], cs[MAXC];
+  // lane takes chunks lane, lane + 64, ...: their (max, sum) and sorted lists,
+  // all loaded at once; list j's next entry is hv[j][0], hi[j][0]
+  int hi[MAXC][kTopKMax];
+  float hv[MAXC][kTopKMax], cm[MAXC], cs[MAXC];
 #pragma unroll
   for (int j = 0; j < MAXC; ++j) {
-    const int c = min(lane + 64 * j, C - 1);
-    cur[j] = 0;
-    hv[j] = p[c].v[0];
-    hi[j] = p[c].i[0];
-    cm[j] = p[c].m;
-    cs[j] = p[c].s;
-    if (lane + 64 * j >= C) {
-      hv[j] = cm[j] = -INFINITY;
-      hi[j] = V;
-      cs[j] = 0.f;
+    const TopkPart& pc = p[min(lane + 64 * j, C - 1)];
+    const bool own = lane + 64 * j < C;
+    cm[j] = own ? pc.m : -INFINITY;
+    cs[j] = own ? pc.s : 0.f;
+#pragma unroll
+    for (int e = 0; e < kTopKMax; ++e) {
+      hv[j][e] = -INFINITY;
+      hi[j][e] = V;
+      if (e < k) {  // (the others are not written)
+        const float v = pc.v[e];
+        const int i = pc.i[e];
+        hv[j][e] = own ? v : -INFINITY;
+        hi[j][e] = own ? i : V;
+      }
     }
   }
   if (lse) {
@@ -2274,9 +2283,9 @@ __global__ __launch_bounds__(64) void topk_final_kernel(const TopkPart* __restri
     int bi = V, bj = -1;
 #pragma unroll
     for (int j = 0; j < MAXC; ++j)
-      if (better(hv[j], hi[j], bv, bi)) {
-        bv = hv[j];
-        bi = hi[j];
+      if (better(hv[j][0], hi[j][0], bv, bi)) {
+        bv = hv[j][0];
+        bi = hi[j][0];
         bj = j;
       }
     float gv = bv;
@@ -2291,14 +2300,17 @@ __global__ __launch_bounds__(64) void topk_final_kernel(const TopkPart* __restri
       }
     }
     if (bj >= 0 && gi == bi) {
-      // the taken list's next entry
+      // (the taken list moves up)
 #pragma unroll
       for (int j = 0; j < MAXC; ++j)
         if (j == bj) {
-          const int c = lane + 64 * j;
-          const bool more = ++cur[j] < k;
-          hv[j] = more ? p[c].v[cur[j]] : -INFINITY;
-          hi[j] = more ? p[c].i[cur[j]] : V;
+#pragma unroll
+          for (int e = 0; e + 1 < kTopKMax; ++e) {
+            hv[j][e] = hv[j][e + 1];
+            hi[j][e] = hi[j][e + 1];
+          }
+          hv[j][kTopKMax - 1] = -INFINITY;
+          hi[j][kTopKMax - 1] = V;
         }
     }
     if (lane == 0) {
@@ -2318,7 +2330,8 @@ hipError_t launch_topk(const float* logits, int N, int V, int k, int* idx, float
   if (k < 1 || k > kTopKMax || C > 64 * 4) return hipErrorInvalidValue;
   TopkPart* parts = (TopkPart*)work;
   topk_part_kernel<<<dim3(C, N), 256, 0, s>>>(logits, V, C, k, parts);
-  topk_final_kernel<<<N, 64, 0, s>>>(parts, V, C, k, idx, val, lse);
+  if (C <= 64) topk_final_kernel<1><<<N, 64, 0, s>>>(parts, V, C, k, idx, val, lse);
+  else topk_final_kernel<4><<<N, 64, 0, s>>>(parts, V, C, k, idx, val, lse);
   return hipGetLastError();
 }
 

@@ -66,3 +66,29 @@ def test_topk_across_chunks(session, k):
     hi, hv, hl = host_topk(lg, k)
     assert np.array_equal(idx.cpu().numpy(), hi) and np.array_equal(val.cpu().numpy(), hv)
     assert np.abs(lse.cpu().numpy() - hl).max() < 1e-5 * np.abs(hl).max() + 1e-5
+
+
+@pytest.mark.parametrize("V", [131072, 131073, 300000])
+def test_topk_chunks_per_lane(V):
+    """64 chunks, one a lane of the wave that merges them, and more; k of 1, 3 and the most allowed, the first
+    eight of a row in one chunk, in one lane's chunks and anywhere, most of a row -inf, half of one NaN."""
+    import torch
+    from paper_2308_04623_amd import ssd
+    cfg = W.GPT2Config(n_layer=1, d_model=64, n_head=2, d_mlp=64, vocab=V, n_pos=64, dtype="bf16")
+    s = ssd.Session(ssd.Model(cfg, W.make_weights(cfg, 0)), 0, 8)
+    g = np.random.default_rng(V)
+    lg = np.round(g.standard_normal((5, V)) * 2, 1).astype(np.float32)
+    lg[1, 2040:2060] = 50.0
+    lg[2, 5 * 2048::64 * 2048] = 60.0  # (every chunk of lane 5)
+    lg[2, 7 + 5 * 2048::64 * 2048] = 61.0
+    lg[3, np.arange(V) % 700 > 0] = -np.inf
+    lg[3, V - 1] = 0.0
+    lg[4, : V // 2] = np.nan
+    for k in (1, 3, 8):
+        idx, val, lse = (t.cpu().numpy() for t in s.topk(torch.from_numpy(lg).cuda(), k))
+        hi, hv, hl = host_topk(lg[:4], k)
+        assert np.array_equal(idx[:4], hi) and np.array_equal(val[:4], hv)
+        assert np.abs(lse[:4] - hl).max() < 1e-5 * np.abs(hl).max() + 1e-5
+        # (NaN entries are never chosen)
+        hi, hv, _ = host_topk(lg[4:, V // 2:], k)
+        assert np.array_equal(idx[4:], hi + V // 2) and np.array_equal(val[4:], hv) and np.isnan(lse[4])
